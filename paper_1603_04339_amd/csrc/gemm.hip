@@ -26,7 +26,7 @@
 
 namespace sparc {
 
-sparc_ctx* g_timer_ctx = nullptr;
+thread_local sparc_ctx* g_timer_ctx = nullptr;
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
