@@ -13,7 +13,7 @@
 #include <mutex>
 #include <vector>
 
-#include "devmath.hpp"
+#include "hstep_api.hpp"
 
 namespace sparc {
 
@@ -28,6 +28,7 @@ struct sparc_filter_plan {
   sparc_dtype dt;
   int n_o, tile, n_prob, max_deg;
   int dir;   // some problem has a Dirichlet direction
+  std::vector<sparc::RowPlan> row;  // row form: per problem (empty: the tiled form)
   std::vector<sparc_ham*> H;
   std::vector<void*> X, W, alpha;
   std::vector<char> fused;        // the problem applies its projectors inside the step
@@ -73,8 +74,19 @@ static int plan_enqueue(sparc_filter_plan* P) {
     const size_t t0 = (size_t)j * P->n_prob, o0 = (size_t)j * (P->n_prob + 1);
     SPARC_TRY(nl_gather_batched(P->ctx, P->dt, P->maxp, P->dev_gather + t0, P->dev_goff + o0, P->n_gather[j],
                                 P->gather_wg[j]));
-    SPARC_TRY(step_table_launch(P->ctx, P->dt, P->n_o, P->tile, P->dev_tables + P->table_off[j],
-                                P->dev_wg + P->wg_off[j], (int)mem.size(), P->total_wg[j], P->dir, P->nl_lds[j]));
+    if (!P->row.empty()) {
+      // one launch per chunk width (the step's problems are in that order)
+      for (size_t a = 0, b; a < mem.size(); a = b) {
+        const RowCfg& c = P->row[mem[a]].cfg;
+        for (b = a + 1; b < mem.size() && P->row[mem[b]].cfg.vx == c.vx;) ++b;
+        const int* wg = P->host_wg.data() + P->wg_off[j];
+        SPARC_TRY(row_table_launch(P->ctx, P->dt, c, P->dev_tables + P->table_off[j] + a * step_args_bytes(P->dt),
+                                   P->dev_wg + P->wg_off[j] + a, (int)(b - a), wg[b] - wg[a], j > 0));
+      }
+    } else {
+      SPARC_TRY(step_table_launch(P->ctx, P->dt, P->n_o, P->tile, P->dev_tables + P->table_off[j],
+                                  P->dev_wg + P->wg_off[j], (int)mem.size(), P->total_wg[j], P->dir, P->nl_lds[j]));
+    }
     // projector scatters of the problems that do not apply them inside the step (one launch)
     SPARC_TRY(nl_scatter_batched(P->ctx, P->dt, P->dev_scatter + t0, P->dev_soff + o0, P->n_scatter[j],
                                  P->scatter_wg[j], P->dev_a + (size_t)j * P->n_prob));
@@ -116,6 +128,7 @@ static int plan_tables(sparc_filter_plan* P, const double* lcut, const double* l
         s.a = 2.0 / e; s.b = -2.0 * c / e; s.c = -1.0;
       }
       s.alpha = P->fused[p] ? P->alpha[p] : nullptr;
+      s.row = P->row.empty() ? nullptr : &P->row[p];
       P->host_a[(size_t)j * P->n_prob + p] = s.a;
       d.push_back(s);
       hs.push_back(P->H[p]);
@@ -316,9 +329,19 @@ int sparc_filter_plan_create(sparc_ctx* ctx, int32_t n_prob, sparc_ham* const* H
   P->nl_lds.assign(P->max_deg, 0);
   P->members.resize(P->max_deg);
   P->total_wg.assign(P->max_deg, 0);
+  // the row form where every problem allows it, else the tiled form; the problems of a step
+  // are ordered by chunk width, each width being one launch
+  if (!row_batch_plan(P->H.data(), P->n_s.data(), n_prob, &P->row)) P->row.clear();
+  std::vector<int> order(n_prob);
+  for (int p = 0; p < n_prob; ++p) order[p] = p;
+  if (!P->row.empty())
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+      const RowPlan &x = P->row[a], &y = P->row[b];   // long work-groups first
+      return x.cfg.vx != y.cfg.vx ? x.cfg.vx > y.cfg.vx : x.dur > y.dur;
+    });
   size_t toff = 0, woff = 0;
   for (int j = 0; j < P->max_deg; ++j) {
-    for (int p = 0; p < n_prob; ++p)
+    for (int p : order)
       if (degree[p] > j) P->members[j].push_back(p);
     P->table_off.push_back(toff);
     P->wg_off.push_back(woff);
@@ -335,11 +358,11 @@ int sparc_filter_plan_create(sparc_ctx* ctx, int32_t n_prob, sparc_ham* const* H
   P->tile = heuristic_tile(H[big]->grid.n[0], H[big]->grid.n[1], elem_bytes(P->dt));
   P->dir = 0;
   for (int p = 0; p < n_prob; ++p) P->dir |= dirichlet_mask(H[p]->grid) != 0 ? 1 : 0;
-  if (ctx->autotune) {
+  if (ctx->autotune && P->row.empty()) {
     int rc = plan_tune_tile(P);
     if (rc != SPARC_OK) { delete P; return rc; }
   }
-  for (int p = 0; p < n_prob; ++p) P->fused.push_back(nl_step_fused(H[p], P->tile) ? 1 : 0);
+  for (int p = 0; p < n_prob; ++p) P->fused.push_back(P->row.empty() && nl_step_fused(H[p], P->tile) ? 1 : 0);
   P->use_graph = use_graph != 0;
   P->cap_stream = nullptr;
   P->graph = nullptr;

@@ -801,6 +801,92 @@ int cg_residual_norm(sparc_ham* H, const CgIter& C) {
   return check_launch("cg_norm_kernel");
 }
 
+// ------------------------------------------------------------ row form
+// The row form (hrow_impl.hpp) serves cells that are periodic in every direction with the
+// 12th-order stencil and at least 16 nodes per direction (its halos wrap at most once); a
+// forced tile shape and the fused projector scatter keep the tiled kernel.  So do wide
+// complex128 grids that 16 x 16 tiles cover exactly: their rows leave a work-group 16 rows
+// only (80^3 x 60: tiled 403 us, rows 431; at 64^3 x 60 202 and 184, at 48^3 x 1000 1450 and
+// 1430, and rows win wherever the tiles do not fit, 45 x 37 x 50 x 40: 79 and 74).
+static bool row_form(const sparc_ham* H) {
+  const sparc_grid& g = H->grid;
+  if (H->dtype == SPARC_C128 && g.n[0] > 64 && g.n[0] % 16 == 0 && g.n[1] % 16 == 0) return false;
+  return g.n_o == kRowNO && dirichlet_mask(g) == 0 && g.n[0] >= 16 && g.n[1] >= 16 && g.n[2] >= 16 && !H->nl_fused &&
+         !getenv("SPARC_HSTEP_TILE");
+}
+
+static int real_bytes(const sparc_ham* H) { return dtype_single(H->dtype) ? 4 : 8; }
+
+// plan of a single problem; the search is remembered per thread by the sizes it depends on
+static const RowPlan& row_single_plan(const sparc_ham* H, int32_t n_s) {
+  struct Entry {
+    int key[6] = {0, 0, 0, 0, 0, 0};
+    RowPlan plan;
+  };
+  static thread_local Entry cache[16];
+  const int key[6] = {H->grid.n[0], H->grid.n[1], H->grid.n[2], n_s, (int)H->dtype + 1, H->ctx->n_cu};
+  unsigned h = 0;
+  for (int k : key) h = h * 31u + (unsigned)k;
+  Entry& e = cache[h % 16];
+  if (!std::equal(key, key + 6, e.key)) {
+    const int cp = dtype_complex(H->dtype) ? 2 : 1, rb = real_bytes(H);
+    int vx, vy;
+    row_chunk(key[0], cp, rb, &vx, &vy);
+    e.plan = row_plan(key[0], key[1], key[2], cp, rb, vx, vy, n_s, H->ctx->n_cu, kRowThreads, false);
+    std::copy(key, key + 6, e.key);
+  }
+  return e.plan;
+}
+
+// Problems of one chunk width share a launch, and its work-group size: the one of the
+// group's largest problem.  Each is planned as if its launch were copies of it.
+static bool row_group_plan(sparc_ham* const* H, const int* n_s, const std::vector<int>& mem, int vx, int vy,
+                           std::vector<RowPlan>& out) {
+  const int cp = dtype_complex(H[0]->dtype) ? 2 : 1, rb = real_bytes(H[0]);
+  double total = 0;
+  int big = mem[0];
+  auto size = [&](int p) { return (double)H[p]->n_d * n_s[p]; };
+  for (int p : mem) {
+    total += size(p);
+    if (size(p) > size(big)) big = p;
+  }
+  auto plan = [&](int p, int max_nt) {
+    const sparc_grid& g = H[p]->grid;
+    const int64_t ns = std::max<int64_t>(n_s[p], (int64_t)(total / (double)H[p]->n_d));
+    return row_plan(g.n[0], g.n[1], g.n[2], cp, rb, vx, vy, ns, H[p]->ctx->n_cu, max_nt, true);
+  };
+  int nt = plan(big, kRowThreads).cfg.nt;
+  for (int p : mem)
+    if (plan(p, nt).cfg.vx == 0) nt = kRowThreads;   // a problem that needs more threads than the largest one
+  RowCfg c{vx, vy, 1, 1, 0, 0};
+  for (int p : mem) {
+    out[p] = plan(p, nt);
+    if (out[p].cfg.vx == 0) return false;
+    c.hm = std::max(c.hm, out[p].cfg.hm);
+    c.full = c.full && out[p].cfg.full;
+    c.nt = std::max(c.nt, out[p].cfg.nt);
+    c.lds = std::max(c.lds, out[p].cfg.lds);
+  }
+  for (int p : mem) out[p].cfg = c;
+  return true;
+}
+
+bool row_batch_plan(sparc_ham* const* H, const int* n_s, int n, std::vector<RowPlan>* out) {
+  const int cp = dtype_complex(H[0]->dtype) ? 2 : 1, rb = real_bytes(H[0]);
+  std::map<int, std::pair<int, std::vector<int>>> group;   // by chunk width: rows per thread, members
+  for (int p = 0; p < n; ++p) {
+    if (!row_form(H[p])) return false;
+    int vx, vy;
+    row_chunk(H[p]->grid.n[0], cp, rb, &vx, &vy);
+    group[vx].first = vy;
+    group[vx].second.push_back(p);
+  }
+  out->assign(n, RowPlan());
+  for (const auto& g : group)
+    if (!row_group_plan(H, n_s, g.second.second, g.first, g.second.first, *out)) return false;
+  return true;
+}
+
 template <typename E>
 static int ham_step_t(sparc_ham* H, const void* x, int64_t ldx, const void* z, int64_t ldz, void* out, int64_t ldo,
                       int32_t n_s, double a, double b, double c, const void* alpha, int flags) {
@@ -826,12 +912,27 @@ static int ham_step_t(sparc_ham* H, const void* x, int64_t ldx, const void* z, i
   A.va = (flags & STEP_NO_VEFF) ? (R)0 : (R)a;
   A.vb = (R)b;
   A.zc = (R)c;
-  for (int s = 0; s < 3; ++s) A.kl[s] = H->grid.kpt[s] * H->grid.L[s];
+  for (int s = 0; s < 3; ++s) {
+    A.kl[s] = H->grid.kpt[s] * H->grid.L[s];
+    A.pc[s] = (R)H->ph_re[s];
+    A.ps[s] = (R)H->ph_im[s];
+  }
   A.dmask = dirichlet_mask(H->grid);
   A.zplane = (const E*)H->zplane;
   const bool nonlocal = H->n_proj > 0 && H->n_nlpts > 0 && !(flags & STEP_NO_NONLOCAL);
   if (nonlocal && !alpha) return fail(SPARC_EINVAL, "ham_step: projections missing");
   const void* al = nonlocal ? alpha : nullptr;
+  if (row_form(H)) {
+    // too few work-groups for a quarter of the CUs (one orbital of a small grid: a step takes
+    // 7 us in either form) leave the point form below
+    const RowPlan& p = row_single_plan(H, n_s);
+    if (p.cfg.vx && p.wg(n_s) >= H->ctx->n_cu / 4) {
+      row_fill(A, p, n_s);
+      SPARC_TRY(hrow_single<E>(H->ctx, A, p.cfg, p.wg(n_s)));
+      if (nonlocal) SPARC_TRY(nl_scatter(H, alpha, n_s, a, nullptr, out, ldo));
+      return SPARC_OK;
+    }
+  }
   int t = heuristic_tile(A.n1, A.n2, sizeof(E));
   if (use_point_form(H, A, n_s, t)) {
     SPARC_TRY(hstep_point<E>(H->ctx, A, n_s, H->grid.n_o));
@@ -870,7 +971,11 @@ static void fill_args(sparc_ham* H, const StepDesc& d, StepArgs<E>& A) {
   A.va = (R)d.a;
   A.vb = (R)d.b;
   A.zc = (R)d.c;
-  for (int s = 0; s < 3; ++s) A.kl[s] = H->grid.kpt[s] * H->grid.L[s];
+  for (int s = 0; s < 3; ++s) {
+    A.kl[s] = H->grid.kpt[s] * H->grid.L[s];
+    A.pc[s] = (R)H->ph_re[s];
+    A.ps[s] = (R)H->ph_im[s];
+  }
   A.dmask = dirichlet_mask(H->grid);
   A.zplane = (const E*)H->zplane;
   A.nl_val = nullptr;
@@ -886,7 +991,7 @@ size_t step_args_bytes(sparc_dtype dt) {
   return 0;
 }
 
-// Builds the step table of n problems.  A problem whose StepDesc carries projections
+// Builds the step table of n problems (d[p].row: the row form's plans).  A problem whose StepDesc carries projections
 // (alpha) applies its projectors inside the step when its Hamiltonian has tables for
 // the tile shape.  *nl_lds: dynamic LDS bytes of the widest fused problem.
 template <typename E>
@@ -898,6 +1003,11 @@ static int64_t build_t(sparc_ham* const* H, const StepDesc* d, int n, int tile, 
   for (int p = 0; p < n; ++p) {
     fill_args<E>(H[p], d[p], T[p]);
     wg[p] = (int)total;
+    if (d[p].row) {
+      row_fill(T[p], *d[p].row, d[p].n_s);
+      total += (d[p].row->wg(d[p].n_s) + 7) / 8 * 8;   // an eighth per XCD
+      continue;
+    }
     total += plan_problem(T[p], kTiles[tile].tx, kTiles[tile].ty, H[p]->grid.n_o, d[p].n_s, H[p]->ctx->n_cu);
     if (d[p].alpha) nl_fill(H[p], T[p], tile, d[p].a, d[p].alpha, d[p].n_s);
     lds = std::max(lds, nl_lds_bytes(T[p], kTiles[tile].tx * kTiles[tile].ty));
@@ -916,6 +1026,17 @@ int64_t step_table_build(sparc_ham* const* H, const StepDesc* d, int n, int tile
     case SPARC_C64: return build_t<cf>(H, d, n, tile, table, wg, nl_lds);
   }
   return -1;
+}
+
+int row_table_launch(sparc_ctx* ctx, sparc_dtype dt, const RowCfg& c, const void* dev_table, const int* dev_wg, int n,
+                     int64_t total, int hasz) {
+  switch (dt) {
+    case SPARC_R64: return hrow_batched<double>(ctx, dev_table, dev_wg, n, total, c, hasz);
+    case SPARC_R32: return hrow_batched<float>(ctx, dev_table, dev_wg, n, total, c, hasz);
+    case SPARC_C128: return hrow_batched<cd>(ctx, dev_table, dev_wg, n, total, c, hasz);
+    case SPARC_C64: return hrow_batched<cf>(ctx, dev_table, dev_wg, n, total, c, hasz);
+  }
+  return fail(SPARC_EINVAL, "batched step: bad dtype");
 }
 
 int step_table_launch(sparc_ctx* ctx, sparc_dtype dt, int no, int tile, const void* dev_table, const int* dev_wg,

@@ -1,6 +1,8 @@
 // Stencil step kernels: shared declarations (argument block, tile shapes, launch
 // planning) between the launch code and the per-element-type kernel instances.
 #pragma once
+#include <algorithm>
+#include <cmath>
 #include <cstdlib>
 
 #include "devmath.hpp"
@@ -38,6 +40,9 @@ struct StepArgs {
   const E* alpha;           // projections of x: alpha[P * lda + orbital] (dV included)
   int lda;
   R nla;                    // scale of the projector term (the step's a)
+  // row form (hrow_impl.hpp): threads along x and y of a tile, LDS row pitch in chunks
+  int txt, tyt, px;
+  R pc[3], ps[3];    // e^{i k_s L_s}
 };
 
 // dynamic LDS bytes of a fused step launch (after plan_problem): the tile's scaled
@@ -83,6 +88,119 @@ inline int64_t plan_problem(StepArgs<E>& A, int tx, int ty, int no, int n_s, int
   A.ns = n_s;
   return (int64_t)A.tiles * A.nz * n_s;
 }
+
+// ------------------------------------------------------------ row form
+// Step kernel over tiles of whole grid rows (hrow_impl.hpp).  A thread owns a chunk of vx
+// reals along x (up to 16 bytes) in each of vy neighbouring rows.
+constexpr int kRowNO = 6;          // stencil half-width of the row form's kernels
+constexpr int kRowThreads = 768;   // most threads of a row-form work-group (168 registers each)
+constexpr size_t kRowLds = 163840; // LDS of a CU
+struct RowCfg {
+  int vx, vy;   // reals along x and rows per thread
+  int hm;       // y-halo chunks per thread (1 or 2)
+  int full;     // every thread and every row of every tile is inside the grid
+  int nt;       // threads per work-group
+  size_t lds;   // dynamic LDS bytes
+};
+
+// Chunk shape for rows of n1 nodes (cp reals of rb bytes each): the widest chunk up to 16
+// bytes that divides a row, in two rows, or a narrower one in four (13 z planes of it live
+// in registers either way).
+inline void row_chunk(int n1, int cp, int rb, int* vx, int* vy) {
+  const int wide = 16 / rb;
+  int v = wide;
+  while (v > cp && (n1 * cp) % v) v /= 2;
+  *vx = v;
+  *vy = v == wide ? 2 : 4;
+}
+
+// Tile of one problem of n1 x n2 x n3 nodes and n_s orbitals (vx = 0: no tile fits).
+struct RowPlan {
+  RowCfg cfg{};
+  int txt = 0, tyt = 0, px = 0, tiles = 0, zchunk = 0, nz = 0;
+  double dur = 0;   // modelled time of a work-group
+  int64_t wg(int n_s) const { return (int64_t)tiles * nz * n_s; }
+};
+
+// Tile height and z chunks for chunk shape (vx, vy); work-groups of at most max_nt threads.
+// The cost of a candidate is its rounds of resident work-groups (k per CU) times its plane
+// steps, a step taking the longer of its latency, 1.3 us + 0.3 ns per 16 bytes of the tile,
+// and the CU's rate, k times (1.9 ns per 16 bytes of the tile, 2.7 in chunks narrower than
+// that, + 0.43 ns per 16 bytes of its y halo; complex double, whose x taps read a chunk each,
+// 2.4 and 1.1); more than four waves that do not fill the four SIMDs evenly cost 12 %.  Fitted
+// to 1200 timed (tile, chunk) pairs of 41 blocks, 24^3 x 1 to 96^3 x 192 in all four types,
+// over which the choice costs 3 % on average against the fastest pair (80^3 x 60 complex64 at
+// worst, 233 against 174 us; tiled form 241).
+// shared: the launch holds other problems too, so rounds need not be whole, and what is lost
+// is part of the last work-groups' time.
+inline RowPlan row_plan(int n1, int n2, int n3, int cp, int rb, int vx, int vy, int64_t n_s, int n_cu, int max_nt,
+                        bool shared) {
+  RowPlan best;
+  const int txt = n1 * cp / vx;
+  const int hc = (kRowNO * cp + vx - 1) / vx;
+  const int px = txt + 2 * hc;
+  const size_t cb = (size_t)vx * rb;
+  const bool c128 = cp == 2 && rb == 8;
+  const double rate = c128 ? 2.4e-3 : (cb < 16 ? 2.7e-3 : 1.9e-3), halo_rate = c128 ? 1.1e-3 : 0.43e-3;
+  double best_cost = 1e300;
+  int last = 0;
+  for (int tiles = 1; tiles <= n2; ++tiles) {
+    const int ty = ((n2 + tiles - 1) / tiles + vy - 1) / vy * vy;
+    if (ty == last) continue;
+    last = ty;
+    const int tyt = ty / vy, tl = (n2 + ty - 1) / ty;
+    const int nt = (txt * tyt + 63) / 64 * 64;
+    if (nt > max_nt) continue;
+    const int hm = (2 * kRowNO * txt + nt - 1) / nt;
+    if (hm > 2) break;   // lower tiles need more
+    const size_t lds = (size_t)(2 * (ty + 2 * kRowNO) * px + 1) * cb;
+    if (lds > kRowLds) continue;
+    const int64_t occ = std::max(1, std::min<int>(12 / (nt / 64), (int)(kRowLds / lds)));
+    const double chunks = (double)nt * vy * (double)cb / 16.0, halo = 2.0 * kRowNO * txt * (double)cb / 16.0;
+    const double uneven = nt > 256 && nt % 256 ? 1.12 : 1.0;
+    for (int nz = 1; nz == 1 || n3 / nz >= 3; ++nz) {
+      const int zc = (n3 + nz - 1) / nz, nzr = (n3 + zc - 1) / zc;
+      const int64_t wg = (int64_t)tl * nzr * n_s;
+      const int64_t k = std::max<int64_t>(1, std::min<int64_t>(occ, (wg + n_cu - 1) / n_cu));
+      const double r = (double)wg / ((double)n_cu * k);
+      const double step = uneven * std::max(1.3 + 0.3e-3 * chunks, k * (rate * chunks + halo_rate * halo));
+      const double rounds = shared ? std::max(1.0, r) + 0.7 : (r < 6 ? std::ceil(r) : r + 0.5);
+      const double dur = (zc + 1) * step, cost = 2.0 + rounds * dur;
+      if (cost < best_cost * 0.999) {
+        best_cost = cost;
+        best.cfg = RowCfg{vx, vy, hm, (n2 % ty == 0 && txt * tyt == nt) ? 1 : 0, nt, lds};
+        best.txt = txt;
+        best.tyt = tyt;
+        best.px = px;
+        best.tiles = tl;
+        best.zchunk = zc;
+        best.nz = nzr;
+        best.dur = dur / k;
+      }
+      if (wg > 16 * (int64_t)n_cu) break;
+    }
+  }
+  return best;
+}
+
+// the plan's fields of a step's arguments
+template <typename E>
+inline void row_fill(StepArgs<E>& A, const RowPlan& p, int n_s) {
+  A.txt = p.txt;
+  A.tyt = p.tyt;
+  A.px = p.px;
+  A.tiles = p.tiles;
+  A.zchunk = p.zchunk;
+  A.nz = p.nz;
+  A.ns = n_s;
+}
+
+// one launch of the row form: a single problem, or a device table of n problems with
+// their work-group offsets (hasz: the steps read the recurrence operand)
+template <typename E>
+int hrow_single(sparc_ctx* ctx, const StepArgs<E>& A, const RowCfg& c, int64_t total);
+template <typename E>
+int hrow_batched(sparc_ctx* ctx, const void* dprobs, const int* dwg, int n, int64_t total, const RowCfg& c, int hasz);
 
 // one stencil step launch (single problem) with stencil order no and tile shape t
 template <typename E>

@@ -267,6 +267,7 @@ struct StepDesc {
   int n_s;
   double a, b, c;
   const void* alpha;  // projections of x (the projectors are applied inside the step), or nullptr
+  const struct RowPlan* row = nullptr;  // the row form's plan of the problem, or nullptr: the tiled form
 };
 size_t step_args_bytes(sparc_dtype dt);
 //   nl_lds: dynamic LDS bytes of the launch (the widest fused problem)
@@ -274,6 +275,12 @@ int64_t step_table_build(sparc_ham* const* H, const StepDesc* d, int n, int tile
                          size_t* nl_lds = nullptr);
 int step_table_launch(sparc_ctx* ctx, sparc_dtype dt, int no, int tile, const void* dev_table, const int* dev_wg,
                       int n, int64_t total, int dir, size_t nl_lds = 0);
+// row form of the step (hstep_api.hpp): plans of n problems that share one launch (false:
+// some problem needs the tiled form), and the launch of such a table (hasz: every step of
+// it reads the recurrence operand)
+bool row_batch_plan(sparc_ham* const* H, const int* n_s, int n, std::vector<struct RowPlan>* out);
+int row_table_launch(sparc_ctx* ctx, sparc_dtype dt, const struct RowCfg& c, const void* dev_table, const int* dev_wg,
+                     int n, int64_t total, int hasz);
 int tuned_tile(sparc_ham* H, int32_t n_s, int* t);
 // stencil tile shapes (hstep_api.hpp): count and threads per work-group of shape t
 int tile_shape_count();
