@@ -16,12 +16,12 @@
 // then b[C_out]; the host-side parameter vector uses W[C_out][C_in][kz][ky][kx]
 // and is transposed on set/get.
 //
-// Kernels: one thread per output voxel keeps all C_out sums in registers and
-// reads the (wave-uniform) weights through the scalar cache; the input gradient
-// is the same kernel with the transposed, mirrored weights and the ReLU mask of
-// the layer below fused; weight gradients stage a chunk of voxels of both
-// operands in LDS and reduce per (tap, group) into partials that a second pass
-// sums in a fixed order.
+// Kernels: the wide layers (16 or 32 channels on both sides) are implicit GEMMs on the FP32
+// matrix cores, voxels by output channels; the input gradient is the same kernel with the
+// transposed, mirrored weights and the ReLU mask of the layer below fused; weight gradients
+// are contractions over the voxels, (tap, input channel) by output channel, with the voxels
+// split over waves and summed in a fixed order.  The layers with one or two channels on one
+// side run on the vector units.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -34,8 +34,8 @@ namespace sparc {
 static constexpr int kLayers = 4;
 static constexpr int kCh[kLayers + 1] = {2, 16, 32, 32, 1};
 static constexpr int kDil[kLayers] = {1, 2, 4, 8};
-static constexpr int kGroups = 64;   // weight-gradient partial groups
-static constexpr int kChunk = 64;    // voxels staged per weight-gradient iteration
+static constexpr int kGroups = 85;   // weight-gradient partial groups of the wide layers (x 3 kz: a work-group per CU)
+static constexpr int kGroupsThin = 256;  // and of the layers with one or two channels on a side
 static constexpr int kRedBlocks = 256;
 
 static int64_t layer_w(int l) { return 27LL * kCh[l] * kCh[l + 1]; }
@@ -199,97 +199,427 @@ __global__ void transpose_w_kernel(int ci_n, int co_n, const float* __restrict__
   WT[((26 - t) * co_n + co) * ci_n + ci] = W[idx];
 }
 
-// partial weight gradients: part[g][t][ci*CO + co] = sum over the voxels of group g of
-// a(v + offset_t)[ci] * gz(v)[co]
-template <int CI, int CO>
-__global__ __launch_bounds__(256) void wgrad_kernel(int n1, int n2, int n3, int q, int B, const float* __restrict__ a,
-                                                    const float* __restrict__ gz, float* __restrict__ part) {
-  constexpr int P = CI * CO;
-  constexpr int PPT = (P + 255) / 256;
-  __shared__ float xs[kChunk][CI + 1];
-  __shared__ float gs[kChunk][CO];
-  const int t = blockIdx.x, g = blockIdx.y;
-  const int oz = q * (t / 9 - 1), oy = q * ((t / 3) % 3 - 1), ox = q * (t % 3 - 1);
-  const int64_t V = (int64_t)n1 * n2 * n3, total = V * B;
-  const int64_t nchunks = (total + kChunk - 1) / kChunk;
-  float acc[PPT];
+// ---------------------------------------------------------------- matrix-core forms
+// FP32 MFMA with FP32 accumulation.  v_mfma_f32_32x32x2: A[m][k] in lane m + 32 k, B[k][n] in
+// lane n + 32 k, result element r of lane l is D[8 (r/4) + 4 (l/32) + r%4][l%32];
+// v_mfma_f32_16x16x4: A[m][k] in lane m + 16 k, B[k][n] in lane n + 16 k, element r of lane l is
+// D[4 (l/16) + r][l%16].
+typedef float v4f_t __attribute__((ext_vector_type(4)));
+typedef float v16f_t __attribute__((ext_vector_type(16)));
+
+template <int N> struct mf;
+template <> struct mf<32> {
+  typedef v16f_t acc;
+  static constexpr int K = 2, R = 16;
+  static __device__ __forceinline__ acc step(float a, float b, acc c) {
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int l, int r) { return 8 * (r / 4) + 4 * (l / 32) + r % 4; }
+};
+template <> struct mf<16> {
+  typedef v4f_t acc;
+  static constexpr int K = 4, R = 4;
+  static __device__ __forceinline__ acc step(float a, float b, acc c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int l, int r) { return 4 * (l / 16) + r; }
+};
+
+// conv_kernel for CI, CO in {16, 32}: a wave owns MT tiles of CO consecutive voxels by CO
+// output channels.  Per tap a lane holds CI / K channels of its voxel (contiguous in memory;
+// the K slices of the product are its channel groups) and as many weights of its output
+// channel, and the next tap's are loaded while the current one's products run.  Bound by the
+// matrix cores: 64 cycles per product of 4096 flops, 40^3 x 32 -> 32 channels 155 -> 49 us for
+// one cell, 651 -> 324 us for eight (the vector form waited for its loads; 22.5 us per cell at
+// the FP32 peak).
+template <int CI, int CO, int MODE, int MT>
+__global__ __launch_bounds__(256) void conv_mfma_kernel(int n1, int n2, int n3, int q, const float* __restrict__ in,
+                                                        const float* __restrict__ W, const float* __restrict__ bias,
+                                                        const float* __restrict__ mask, float* __restrict__ out) {
+  typedef mf<CO> M;
+  constexpr int KPL = CI / M::K;   // channels per lane
+  static_assert(KPL % 4 == 0, "channels per lane come in float4");
+  const int64_t V = (int64_t)n1 * n2 * n3;
+  const int lane = threadIdx.x & 63, m = lane % CO, h = lane / CO;
+  const int64_t v0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * CO * MT;
+  const int64_t b = blockIdx.y;
+  const float* __restrict__ inb = in + b * V * CI + h * KPL;
+  const float* __restrict__ Wl = W + h * KPL * CO + m;
+  int vi[MT], vj[MT], vk[MT];
 #pragma unroll
-  for (int u = 0; u < PPT; ++u) acc[u] = 0.0f;
-  for (int64_t c = g; c < nchunks; c += gridDim.y) {
-    const int64_t base = c * kChunk;
-    for (int e = threadIdx.x; e < kChunk * CO; e += 256) {
-      const int vv = e / CO, co = e % CO;
-      const int64_t gv = base + vv;
-      gs[vv][co] = gv < total ? gz[gv * CO + co] : 0.0f;
-    }
-    for (int e = threadIdx.x; e < kChunk * CI; e += 256) {
-      const int vv = e / CI, ci = e % CI;
-      const int64_t gv = base + vv;
-      float val = 0.0f;
-      if (gv < total) {
-        const int64_t b = gv / V, v = gv % V;
-        const int i = (int)(v % n1), j = (int)((v / n1) % n2), k = (int)(v / ((int64_t)n1 * n2));
-        const int64_t src = ((int64_t)wrapi(k + oz, n3) * n2 + wrapi(j + oy, n2)) * n1 + wrapi(i + ox, n1);
-        val = a[(b * V + src) * CI + ci];
-      }
-      xs[vv][ci] = val;
-    }
-    __syncthreads();
+  for (int t = 0; t < MT; ++t) {
+    int64_t v = v0 + t * CO + m;
+    if (v >= V) v = V - 1;   // rows past the cell are computed and not stored
+    vi[t] = (int)(v % n1);
+    vj[t] = (int)((v / n1) % n2);
+    vk[t] = (int)(v / ((int64_t)n1 * n2));
+  }
+  typename M::acc acc[MT];
 #pragma unroll
-    for (int u = 0; u < PPT; ++u) {
-      const int p = threadIdx.x + 256 * u;
-      if (p < P) {
-        const int ci = p / CO, co = p % CO;
-        float s = acc[u];
-        for (int vv = 0; vv < kChunk; ++vv) s = fmaf(xs[vv][ci], gs[vv][co], s);
-        acc[u] = s;
-      }
+  for (int t = 0; t < MT; ++t)
+#pragma unroll
+    for (int r = 0; r < M::R; ++r) acc[t][r] = MODE != 2 ? bias[m] : 0.0f;
+  float4 xa[MT][KPL / 4];
+  float wb[KPL];
+  auto fetch = [&](int tap) {
+    const int oz = q * (tap / 9 - 1), oy = q * ((tap / 3) % 3 - 1), ox = q * (tap % 3 - 1);
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      const int64_t src = ((int64_t)wrapi(vk[t] + oz, n3) * n2 + wrapi(vj[t] + oy, n2)) * n1 + wrapi(vi[t] + ox, n1);
+#pragma unroll
+      for (int c = 0; c < KPL / 4; ++c) xa[t][c] = *(const float4*)(inb + src * CI + 4 * c);
     }
-    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < KPL; ++c) wb[c] = Wl[(tap * CI + c) * CO];
+  };
+  fetch(0);
+  for (int tap = 0; tap < 27; ++tap) {
+    float4 x[MT][KPL / 4];
+    float w[KPL];
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+      for (int c = 0; c < KPL / 4; ++c) x[t][c] = xa[t][c];
+#pragma unroll
+    for (int c = 0; c < KPL; ++c) w[c] = wb[c];
+    if (tap + 1 < 27) fetch(tap + 1);
+#pragma unroll
+    for (int c = 0; c < KPL / 4; ++c)
+#pragma unroll
+      for (int t = 0; t < MT; ++t) {
+        acc[t] = M::step(x[t][c].x, w[4 * c], acc[t]);
+        acc[t] = M::step(x[t][c].y, w[4 * c + 1], acc[t]);
+        acc[t] = M::step(x[t][c].z, w[4 * c + 2], acc[t]);
+        acc[t] = M::step(x[t][c].w, w[4 * c + 3], acc[t]);
+      }
   }
 #pragma unroll
-  for (int u = 0; u < PPT; ++u) {
-    const int p = threadIdx.x + 256 * u;
-    if (p < P) part[((int64_t)g * 27 + t) * P + p] = acc[u];
+  for (int t = 0; t < MT; ++t)
+#pragma unroll
+    for (int r = 0; r < M::R; ++r) {
+      const int64_t v = v0 + t * CO + M::row(lane, r);
+      if (v < V) {
+        const int64_t o = (b * V + v) * CO + m;
+        float x = acc[t][r];
+        if (MODE == 1) x = x < 0.0f ? 0.0f : x;   // ReLU that keeps a NaN a NaN
+        if (MODE == 2) x = mask[o] > 0.0f ? x : 0.0f;
+        out[o] = x;
+      }
+    }
+}
+
+// conv_kernel<32, 1, 0>: eight lanes per voxel, four channels each, so that a voxel's 32
+// channels are one 128-byte line (one thread per voxel read 64 lines per load and waited for
+// them one by one: 33 -> 16 us on 40^3, 341 -> 108 us for eight cells)
+__global__ __launch_bounds__(256) void conv_32to1_kernel(int n1, int n2, int n3, int q, const float* __restrict__ in,
+                                                         const float* __restrict__ W, const float* __restrict__ bias,
+                                                         float* __restrict__ out) {
+  const int64_t V = (int64_t)n1 * n2 * n3;
+  int64_t v = (int64_t)blockIdx.x * 32 + (threadIdx.x >> 3);
+  const int c = (threadIdx.x & 7) * 4;
+  const bool ok = v < V;
+  if (!ok) v = V - 1;
+  const int i = (int)(v % n1), j = (int)((v / n1) % n2), k = (int)(v / ((int64_t)n1 * n2));
+  const float* __restrict__ inb = in + (int64_t)blockIdx.y * V * 32 + c;
+  float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
+#pragma unroll 9
+  for (int t = 0; t < 27; ++t) {
+    const int64_t src = ((int64_t)wrapi(k + q * (t / 9 - 1), n3) * n2 + wrapi(j + q * ((t / 3) % 3 - 1), n2)) * n1 +
+                        wrapi(i + q * (t % 3 - 1), n1);
+    const float4 x = *(const float4*)(inb + src * 32), w = *(const float4*)(W + t * 32 + c);
+    s0 = fmaf(x.x, w.x, s0);
+    s1 = fmaf(x.y, w.y, s1);
+    s2 = fmaf(x.z, w.z, s2);
+    s3 = fmaf(x.w, w.w, s3);
+  }
+  float s = (s0 + s1) + (s2 + s3);
+  s += __shfl_xor(s, 1, 64);
+  s += __shfl_xor(s, 2, 64);
+  s += __shfl_xor(s, 4, 64);
+  if (ok && c == 0) out[(int64_t)blockIdx.y * V + v] = s + bias[0];
+}
+
+// A voxel walked in steps along the batch: coordinates and sample of the global voxel gv
+struct Walk {
+  int i, j, k;
+  int64_t base;   // first voxel of the sample
+  __device__ __forceinline__ Walk(int64_t gv, int n1, int n2, int64_t V) {
+    base = gv / V * V;
+    const int64_t v = gv - base;
+    i = (int)(v % n1);
+    j = (int)((v / n1) % n2);
+    k = (int)(v / ((int64_t)n1 * n2));
+  }
+  __device__ __forceinline__ void advance(int step, int n1, int n2, int n3, int64_t V) {
+    i += step;
+    while (i >= n1) {
+      i -= n1;
+      if (++j == n2) {
+        j = 0;
+        if (++k == n3) {
+          k = 0;
+          base += V;
+        }
+      }
+    }
+  }
+  // voxel at offset (ox, oy, oz), periodic in the sample
+  __device__ __forceinline__ int64_t at(int ox, int oy, int oz, int n1, int n2, int n3) const {
+    return base + ((int64_t)wrapi(k + oz, n3) * n2 + wrapi(j + oy, n2)) * n1 + wrapi(i + ox, n1);
+  }
+};
+
+// Partial weight gradients part[g][t][ci * CO + co] = sum over the voxels of group g of
+// a(v + offset_t)[ci] * gz(v)[co], one kz (9 taps) per blockIdx.y.  The 32 rows of a product
+// are the CI channels of 32 / CI taps, its columns the CO = 32 output channels, its two
+// slices two neighbouring voxels; a wave keeps all 9 taps of its voxels in accumulators, so
+// one load of gz serves them all.  Bound by the matrix cores: eight 40^3 cells 32 x 32
+// channels 2580 -> 433 us (the LDS form read two values per product; 180 us at the FP32 peak).
+// With 16 input channels a product covers two taps and a wave needs half the registers, so
+// twice the groups run (1228 -> 265 us).
+constexpr int kWgradWaves = 8;
+template <int CI>
+__global__ __launch_bounds__(64 * kWgradWaves) void wgrad_mfma_kernel(int n1, int n2, int n3, int q, int64_t total,
+                                                                      const float* __restrict__ a,
+                                                                      const float* __restrict__ gz,
+                                                                      float* __restrict__ part) {
+  typedef mf<32> M;
+  constexpr int CO = 32, TP = 32 / CI, NT = (9 + TP - 1) / TP;
+  __shared__ float red[kWgradWaves][1024];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, m = lane & 31, h = lane >> 5;
+  const int g = blockIdx.x, kz = blockIdx.y;
+  const int64_t V = (int64_t)n1 * n2 * n3;
+  const int ci = m % CI;
+  // voxels of this wave: an even share
+  const int64_t share = ((total + (int64_t)gridDim.x * kWgradWaves * 2 - 1) / ((int64_t)gridDim.x * kWgradWaves * 2)) * 2;
+  const int64_t g0 = ((int64_t)g * kWgradWaves + wv) * share, g1 = g0 + share < total ? g0 + share : total;
+  const int oz = q * (kz - 1);
+  int tx[NT], ty[NT];   // the lane's tap of product u
+#pragma unroll
+  for (int u = 0; u < NT; ++u) {
+    int tl = u * TP + m / CI;
+    if (tl > 8) tl = 8;   // a slot past the nine taps repeats the last one and is not stored
+    ty[u] = tl / 3;
+    tx[u] = tl % 3;
+  }
+  typename M::acc acc[NT];
+#pragma unroll
+  for (int u = 0; u < NT; ++u)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[u][r] = 0.0f;
+  if (g0 < total) {
+    Walk w(g0 + h < total ? g0 + h : total - 1, n1, n2, V);
+    float an[NT], bn = 0.0f;
+    auto fetch = [&](int64_t gv) {
+      const bool ok = gv < g1;
+      // the three rows and columns of the nine taps, then one address per product
+      const int kk = wrapi(w.k + oz, n3) * n2;
+      const int r[3] = {(kk + wrapi(w.j - q, n2)) * n1, (kk + w.j) * n1, (kk + wrapi(w.j + q, n2)) * n1};
+      const int c[3] = {wrapi(w.i - q, n1), w.i, wrapi(w.i + q, n1)};
+      const float* __restrict__ p = a + w.base * CI + ci;
+      bn = 0.0f;
+      if (ok) bn = gz[gv * CO + m];
+#pragma unroll
+      for (int u = 0; u < NT; ++u) {
+        int idx;
+        if constexpr (TP == 1) {
+          idx = r[u / 3] + c[u % 3];
+        } else {
+          idx = (ty[u] == 0 ? r[0] : ty[u] == 1 ? r[1] : r[2]) + (tx[u] == 0 ? c[0] : tx[u] == 1 ? c[1] : c[2]);
+        }
+        an[u] = 0.0f;
+        if (ok) an[u] = p[(int64_t)idx * CI];
+      }
+    };
+    fetch(g0 + h);
+    for (int64_t gv = g0; gv < g1; gv += 2) {
+      float x[NT];
+      const float y = bn;
+#pragma unroll
+      for (int u = 0; u < NT; ++u) x[u] = an[u];
+      if (gv + 2 < g1) {
+        w.advance(2, n1, n2, n3, V);
+        fetch(gv + 2 + h);
+      }
+#pragma unroll
+      for (int u = 0; u < NT; ++u) acc[u] = M::step(x[u], y, acc[u]);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < NT; ++u) {
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 16; ++r) red[wv][M::row(lane, r) * 32 + m] = acc[u][r];
+    __syncthreads();
+    for (int e = threadIdx.x; e < 1024; e += 64 * kWgradWaves) {
+      float s = 0.0f;
+#pragma unroll
+      for (int k = 0; k < kWgradWaves; ++k) s += red[k][e];
+      const int row = e >> 5, tl = u * TP + row / CI;
+      if (tl < 9) part[(((int64_t)g * 27 + kz * 9 + tl) * CI + row % CI) * CO + (e & 31)] = s;
+    }
   }
 }
 
-// gW[t][p] = sum_g part[g][t][p] (fixed order)
-__global__ void wgrad_reduce_kernel(int np, int groups, const float* __restrict__ part, float* __restrict__ gW) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= np) return;
+// The same for 32 -> 1 channels, with the voxels of a in place: row ci, column tap,
+// sum over u of a(u)[ci] * gz(u - offset_t) (1559 -> 40 us on eight 40^3 cells)
+__global__ __launch_bounds__(64 * kWgradWaves) void wgrad_32to1_kernel(int n1, int n2, int n3, int q, int64_t total,
+                                                                       const float* __restrict__ a,
+                                                                       const float* __restrict__ gz,
+                                                                       float* __restrict__ part) {
+  typedef mf<32> M;
+  __shared__ float red[kWgradWaves][1024];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, m = lane & 31, h = lane >> 5;
+  const int64_t V = (int64_t)n1 * n2 * n3;
+  const int64_t share = ((total + (int64_t)gridDim.x * kWgradWaves * 2 - 1) / ((int64_t)gridDim.x * kWgradWaves * 2)) * 2;
+  const int64_t g0 = ((int64_t)blockIdx.x * kWgradWaves + wv) * share, g1 = g0 + share < total ? g0 + share : total;
+  const int oz = -q * (m / 9 - 1), oy = -q * ((m / 3) % 3 - 1), ox = -q * (m % 3 - 1);
+  const bool tap = m < 27;
+  typename M::acc acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+  if (g0 < total) {
+    Walk w(g0 + h < total ? g0 + h : total - 1, n1, n2, V);
+    constexpr int U = 8;   // voxel pairs in flight
+    for (int64_t gv = g0; gv < g1; gv += 2 * U) {
+      float x[U], y[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t v = gv + 2 * u + h;
+        const bool ok = v < g1;
+        x[u] = ok ? a[v * 32 + m] : 0.0f;
+        y[u] = ok && tap ? gz[w.at(ox, oy, oz, n1, n2, n3)] : 0.0f;
+        w.advance(2, n1, n2, n3, V);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) acc = M::step(x[u], y[u], acc);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) red[wv][M::row(lane, r) * 32 + m] = acc[r];
+  __syncthreads();
+  for (int e = threadIdx.x; e < 1024; e += 64 * kWgradWaves) {
+    float s = 0.0f;
+#pragma unroll
+    for (int k = 0; k < kWgradWaves; ++k) s += red[k][e];
+    if ((e & 31) < 27) part[((int64_t)blockIdx.x * 27 + (e & 31)) * 32 + (e >> 5)] = s;
+  }
+}
+
+// The same for 2 -> 16 channels: 16 rows are 8 taps by 2 channels (four products for the 27
+// taps), four voxels per product (317 -> 49 us on eight 40^3 cells)
+__global__ __launch_bounds__(64 * kWgradWaves) void wgrad_2to16_kernel(int n1, int n2, int n3, int q, int64_t total,
+                                                                       const float* __restrict__ a,
+                                                                       const float* __restrict__ gz,
+                                                                       float* __restrict__ part) {
+  typedef mf<16> M;
+  __shared__ float red[kWgradWaves][1024];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, m = lane & 15, h = lane >> 4;
+  const int64_t V = (int64_t)n1 * n2 * n3;
+  const int64_t share = ((total + (int64_t)gridDim.x * kWgradWaves * 4 - 1) / ((int64_t)gridDim.x * kWgradWaves * 4)) * 4;
+  const int64_t g0 = ((int64_t)blockIdx.x * kWgradWaves + wv) * share, g1 = g0 + share < total ? g0 + share : total;
+  int ox[4], oy[4], oz[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    int t = 8 * u + m / 2;
+    if (t > 26) t = 26;
+    oz[u] = q * (t / 9 - 1);
+    oy[u] = q * ((t / 3) % 3 - 1);
+    ox[u] = q * (t % 3 - 1);
+  }
+  typename M::acc acc[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc[u][r] = 0.0f;
+  if (g0 < total) {
+    Walk w(g0 + h < total ? g0 + h : total - 1, n1, n2, V);
+    constexpr int U = 4;   // groups of four voxels in flight
+    for (int64_t gv = g0; gv < g1; gv += 4 * U) {
+      float x[U][4], y[U];
+#pragma unroll
+      for (int c = 0; c < U; ++c) {
+        const int64_t v = gv + 4 * c + h;
+        const bool ok = v < g1;
+        y[c] = ok ? gz[v * 16 + m] : 0.0f;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[c][u] = ok ? a[w.at(ox[u], oy[u], oz[u], n1, n2, n3) * 2 + (m & 1)] : 0.0f;
+        w.advance(4, n1, n2, n3, V);
+      }
+#pragma unroll
+      for (int c = 0; c < U; ++c)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc[u] = M::step(x[c][u], y[c], acc[u]);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) red[wv][u * 256 + M::row(lane, r) * 16 + m] = acc[u][r];
+  __syncthreads();
+  for (int e = threadIdx.x; e < 1024; e += 64 * kWgradWaves) {
+    float s = 0.0f;
+#pragma unroll
+    for (int k = 0; k < kWgradWaves; ++k) s += red[k][e];
+    const int row = (e >> 4) & 15, t = 8 * (e >> 8) + row / 2;
+    if (t < 27) part[((int64_t)blockIdx.x * 27 + t) * 32 + (row & 1) * 16 + (e & 15)] = s;
+  }
+}
+
+// gW[t][p] = sum_g part[g][t][p] in a fixed order: eight strided sums per element, then those
+// (one sum per element waited for its 64 loads in turn: 42 -> 9 us)
+__global__ __launch_bounds__(256) void wgrad_reduce_kernel(int np, int groups, const float* __restrict__ part,
+                                                           float* __restrict__ gW) {
+  __shared__ double red[8][32];
+  const int e = threadIdx.x & 31, r = threadIdx.x >> 5, idx = blockIdx.x * 32 + e;
   double s = 0.0;
-  for (int g = 0; g < groups; ++g) s += part[(int64_t)g * np + idx];
-  gW[idx] = (float)s;
+  if (idx < np) {
+#pragma unroll 4
+    for (int g = r; g < groups; g += 8) s += part[(int64_t)g * np + idx];
+  }
+  red[r][e] = s;
+  __syncthreads();
+  if (r == 0 && idx < np) {
+    for (int k = 1; k < 8; ++k) s += red[k][e];
+    gW[idx] = (float)s;
+  }
 }
 
-// bias gradient, partial: bpart[blk][co] = sum over the voxels blk, blk + grid, ... of gz[.][co]
+// bias gradient, partial: bpart[blk][co] = sum over the voxels blk, blk + grid, ... of
+// gz[.][co], the channels side by side in the lanes (one pass over gz: 367 -> 62 us on eight
+// 40^3 cells of 32 channels)
 template <int CO>
 __global__ __launch_bounds__(256) void bgrad_kernel(int64_t total, const float* __restrict__ gz,
                                                     double* __restrict__ bpart) {
   __shared__ double red[256];
-  for (int co = 0; co < CO; ++co) {
-    double s = 0.0;
-    for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < total; v += (int64_t)gridDim.x * 256)
-      s += gz[v * CO + co];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-      if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) bpart[blockIdx.x * CO + co] = red[0];
+  constexpr int ROWS = 256 / CO;
+  const int co = threadIdx.x % CO, r = threadIdx.x / CO;
+  double s = 0.0;
+  for (int64_t v = (int64_t)blockIdx.x * ROWS + r; v < total; v += (int64_t)gridDim.x * ROWS) s += gz[v * CO + co];
+  red[threadIdx.x] = s;
+  __syncthreads();
+  for (int o = 128; o >= CO; o >>= 1) {
+    if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
     __syncthreads();
   }
+  if (threadIdx.x < CO) bpart[blockIdx.x * CO + threadIdx.x] = red[threadIdx.x];
 }
 
-// gb[co] = sum over blocks of bpart (fixed order)
-__global__ void bgrad_final_kernel(int co_n, int nblk, const double* __restrict__ bpart, float* __restrict__ gb) {
-  const int co = threadIdx.x;
-  if (co >= co_n) return;
+// gb[co] = sum over blocks of bpart (fixed order): one work-group, 1024 / co_n strided sums per
+// channel, then those
+__global__ __launch_bounds__(1024) void bgrad_final_kernel(int co_n, int nblk, const double* __restrict__ bpart,
+                                                           float* __restrict__ gb) {
+  __shared__ double red[1024];
+  const int co = threadIdx.x % co_n, rows = 1024 / co_n;
   double s = 0.0;
-  for (int k = 0; k < nblk; ++k) s += bpart[k * co_n + co];
-  gb[co] = (float)s;
+  for (int k = threadIdx.x / co_n; k < nblk; k += rows) s += bpart[k * co_n + co];
+  red[threadIdx.x] = s;
+  __syncthreads();
+  for (int o = 512; o >= co_n; o >>= 1) {   // co_n is a power of two
+    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+    __syncthreads();
+  }
+  if ((int)threadIdx.x < co_n) gb[threadIdx.x] = (float)red[threadIdx.x];
 }
 
 // per-sample partial sums of up to two fields: part[(b * nblk + blk) * 2 + q]
@@ -318,14 +648,14 @@ __global__ __launch_bounds__(256) void sample_sums_kernel(int64_t V, const float
   }
 }
 
-// sums[b * 2 + q] = sum over blocks of part (fixed order)
-__global__ void sample_sums_final_kernel(int B, int nblk, const double* __restrict__ part, double* __restrict__ sums) {
-  const int idx = threadIdx.x;
-  if (idx >= 2 * B) return;
-  const int b = idx / 2, q = idx % 2;
+// sums[b * 2 + q] = sum over blocks of part (fixed order), one wave per sum
+__global__ __launch_bounds__(128) void sample_sums_final_kernel(int nblk, const double* __restrict__ part,
+                                                                double* __restrict__ sums) {
+  const int b = blockIdx.x, q = threadIdx.x >> 6, lane = threadIdx.x & 63;
   double s = 0.0;
-  for (int k = 0; k < nblk; ++k) s += part[((int64_t)b * nblk + k) * 2 + q];
-  sums[idx] = s;
+  for (int k = lane; k < nblk; k += 64) s += part[((int64_t)b * nblk + k) * 2 + q];
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  if (lane == 0) sums[b * 2 + q] = s;
 }
 
 // loss head: s = x + d - mean_b(d), r = s - y (before the ReLU of the prediction, so
@@ -400,9 +730,26 @@ template <int CI, int CO, int MODE>
 static int launch_conv(hipStream_t s, int n1, int n2, int n3, int q, int B, const float* in, const float* W,
                        const float* bias, const float* mask, float* out) {
   const int64_t V = (int64_t)n1 * n2 * n3;
-  dim3 grid((unsigned)((V + 255) / 256), (unsigned)B);
-  conv_kernel<CI, CO, MODE><<<grid, 256, 0, s>>>(n1, n2, n3, q, in, W, bias, mask, out);
-  return check_launch("conv_kernel");
+  if constexpr (CI >= 16 && CO >= 16) {
+    // two voxel tiles per wave (the weights of a tap serve both) once that leaves two waves
+    // for every SIMD
+    if (V * B >= (int64_t)CO * 2 * 2048) {
+      dim3 grid((unsigned)((V + 8 * CO - 1) / (8 * CO)), (unsigned)B);
+      conv_mfma_kernel<CI, CO, MODE, 2><<<grid, 256, 0, s>>>(n1, n2, n3, q, in, W, bias, mask, out);
+    } else {
+      dim3 grid((unsigned)((V + 4 * CO - 1) / (4 * CO)), (unsigned)B);
+      conv_mfma_kernel<CI, CO, MODE, 1><<<grid, 256, 0, s>>>(n1, n2, n3, q, in, W, bias, mask, out);
+    }
+    return check_launch("conv_mfma_kernel");
+  } else if constexpr (CI == 32 && CO == 1 && MODE == 0) {
+    dim3 grid((unsigned)((V + 31) / 32), (unsigned)B);
+    conv_32to1_kernel<<<grid, 256, 0, s>>>(n1, n2, n3, q, in, W, bias, out);
+    return check_launch("conv_32to1_kernel");
+  } else {
+    dim3 grid((unsigned)((V + 255) / 256), (unsigned)B);
+    conv_kernel<CI, CO, MODE><<<grid, 256, 0, s>>>(n1, n2, n3, q, in, W, bias, mask, out);
+    return check_launch("conv_kernel");
+  }
 }
 
 template <int CI, int CO, bool RELU, bool OUT16>
@@ -417,14 +764,22 @@ static int launch_conv_bf16(hipStream_t s, int n1, int n2, int n3, int q, int B,
 template <int CI, int CO>
 static int launch_wgrad(hipStream_t s, int n1, int n2, int n3, int q, int B, const float* a, const float* gz,
                         float* part, double* bpart, float* gW, float* gb) {
-  wgrad_kernel<CI, CO><<<dim3(27, kGroups), 256, 0, s>>>(n1, n2, n3, q, B, a, gz, part);
-  SPARC_TRY(check_launch("wgrad_kernel"));
+  constexpr bool wide = CI >= 16 && CO == 32;
+  const int groups = wide ? (CI == 16 ? 2 * kGroups : kGroups) : kGroupsThin;
+  const int64_t total = (int64_t)n1 * n2 * n3 * B;
+  if constexpr (wide)
+    wgrad_mfma_kernel<CI><<<dim3(groups, 3), 64 * kWgradWaves, 0, s>>>(n1, n2, n3, q, total, a, gz, part);
+  else if constexpr (CO == 1)
+    wgrad_32to1_kernel<<<kGroupsThin, 64 * kWgradWaves, 0, s>>>(n1, n2, n3, q, total, a, gz, part);
+  else
+    wgrad_2to16_kernel<<<kGroupsThin, 64 * kWgradWaves, 0, s>>>(n1, n2, n3, q, total, a, gz, part);
+  SPARC_TRY(check_launch("wgrad kernel"));
   const int np = 27 * CI * CO;
-  wgrad_reduce_kernel<<<(np + 255) / 256, 256, 0, s>>>(np, kGroups, part, gW);
+  wgrad_reduce_kernel<<<(np + 31) / 32, 256, 0, s>>>(np, groups, part, gW);
   SPARC_TRY(check_launch("wgrad_reduce_kernel"));
-  bgrad_kernel<CO><<<kGroups, 256, 0, s>>>((int64_t)n1 * n2 * n3 * B, gz, bpart);
+  bgrad_kernel<CO><<<kGroupsThin, 256, 0, s>>>(total, gz, bpart);
   SPARC_TRY(check_launch("bgrad_kernel"));
-  bgrad_final_kernel<<<1, 64, 0, s>>>(CO, kGroups, bpart, gb);
+  bgrad_final_kernel<<<1, 1024, 0, s>>>(CO, kGroupsThin, bpart, gb);
   return check_launch("bgrad_final_kernel");
 }
 
@@ -505,7 +860,7 @@ static int dnet_sample_sums(sparc_dnet* N, int B, const float* f0, const float* 
   hipStream_t s = N->ctx->stream;
   sample_sums_kernel<<<dim3(kRedBlocks, B), 256, 0, s>>>(N->V, f0, f1, N->rpart);
   SPARC_TRY(check_launch("sample_sums_kernel"));
-  sample_sums_final_kernel<<<1, 256, 0, s>>>(B, kRedBlocks, N->rpart, N->rsum);
+  sample_sums_final_kernel<<<B, 128, 0, s>>>(kRedBlocks, N->rpart, N->rsum);
   return check_launch("sample_sums_final_kernel");
 }
 
@@ -602,7 +957,7 @@ int sparc_dnet_create(sparc_ctx* ctx, const int32_t* n, int32_t max_batch, sparc
   A((void**)&N->part, (size_t)kGroups * 27 * 32 * 32 * 4);
   A((void**)&N->rpart, (size_t)max_batch * kRedBlocks * 2 * 8);
   A((void**)&N->rsum, (size_t)std::max(2 * max_batch, 2) * 8);
-  A((void**)&N->bpart, (size_t)kGroups * 32 * 8);
+  A((void**)&N->bpart, (size_t)kGroupsThin * 32 * 8);
   A((void**)&N->r2, BV * 4);
   if (rc == SPARC_OK) {
     hipStream_t s = ctx->stream;
