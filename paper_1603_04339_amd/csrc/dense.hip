@@ -549,221 +549,171 @@ __global__ __launch_bounds__(1024) void hetrd_kernel(int n, T* __restrict__ A, d
   }
   if (tid == 0) d[n - 1] = re_(A[(n - 1) + (int64_t)(n - 1) * n]);
 }
+// The same reduction with the whole matrix in the registers of one work-group of NWV waves:
+// lane l of every wave holds the rows l + 64 k, k < RK, wave q the columns q + NWV m, m < CM.
+// Per column: its wave writes it to LDS; every wave forms the same reflector from it
+// (register-only DPP sums); each wave's partial products A v go to LDS and every wave adds all
+// of them, so that v and w are in every wave's lanes; the columns' elements of v and w then
+// come from lane reads, and the rank-2 update runs in registers.  Two barriers per column.
+// Bound by that chain of dependent steps; the panel form below reads the trailing block from
+// L2 once per column and exchanges sums through LDS six times.  n = 128: 1.71 ms there
+// and 0.84 ms here complex, 1.2 and 0.30 ms real.  A matrix held in LDS took 85 us for n = 56
+// real, this 76.  With the rows of a product summed over lanes by DPP instead (a 16 x 32
+// thread grid) n = 128 took 0.41 ms real and 1.8 ms complex.
+__device__ __forceinline__ double lane_of(double v, int l) { return readlane_f64(v, l); }
+__device__ __forceinline__ cd lane_of(cd v, int l) { return {readlane_f64(v.re, l), readlane_f64(v.im, l)}; }
 
-// Same reduction with a two-dimensional thread map for memory-level parallelism:
-// lanes run over 64 consecutive rows (coalesced column segments), the 16 waves over
-// interleaved columns; the matrix-vector product is reduced across waves in LDS.
-// LDS: 16 partial vectors + v + w (n <= 1066 real, n <= 533 complex).
-template <typename T>
-__global__ __launch_bounds__(1024) void hetrd2_kernel(int n, T* __restrict__ A, double* __restrict__ d,
-                                                      double* __restrict__ e, T* __restrict__ tau) {
-  extern __shared__ char smem[];
-  T* v = (T*)smem;           // [n]
-  T* w = v + n;              // [n]
-  T* part = w + n;           // [16][n]
-  __shared__ double red[16];
-  __shared__ T s_tau, s_scale;
-  __shared__ double s_beta;
-  const int tid = threadIdx.x, nt = blockDim.x;
-  const int lane = tid & 63, wave = tid >> 6, nwave = nt >> 6;
-  for (int i = 0; i < n - 1; ++i) {
-    const int r0 = i + 1;       // first row/column of the trailing block
-    const int m = n - r0;
-    double xn = 0;
-    for (int r = i + 2 + tid; r < n; r += nt) {
-      T x = A[r + (int64_t)i * n];
-      xn += re_(mul_(conj_(x), x));
+template <typename T, int RK, int CM, int NWV>
+__global__ __launch_bounds__(64 * NWV) void hetrd_reg_kernel(int n, T* __restrict__ A, double* __restrict__ d,
+                                                             double* __restrict__ e, T* __restrict__ tau) {
+  constexpr bool CX = sizeof(T) == 16;
+  __shared__ T col[64 * RK];
+  __shared__ T part[NWV][64 * RK];
+  const int lane = threadIdx.x & 63;
+  const int q = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const T zero_t = mkT<T>(0.0, 0.0), one_t = mkT<T>(1.0, 0.0);
+  T a[RK][CM];
+#pragma unroll
+  for (int k = 0; k < RK; ++k)
+#pragma unroll
+    for (int m = 0; m < CM; ++m) {
+      const int r = lane + 64 * k, c = q + NWV * m;
+      a[k][m] = (r < n && c < n) ? A[r + (int64_t)c * n] : zero_t;
     }
-    xn = block_sum(xn, red);
-    if (tid == 0) {
-      T alpha = A[i + 1 + (int64_t)i * n];
-      double ar = re_(alpha);
-      double ai = 0;
-      if constexpr (sizeof(T) == 16) ai = ((cd&)alpha).im;
-      if (xn == 0.0 && ai == 0.0) {
-        s_tau = mkT<T>(0.0, 0.0);
-        s_beta = ar;
-        s_scale = mkT<T>(0.0, 0.0);
-      } else {
-        double beta = -copysign(sqrt(ar * ar + ai * ai + xn), ar);
-        s_beta = beta;
-        s_tau = mkT<T>((beta - ar) / beta, -ai / beta);
-        double dr = ar - beta, di = ai, den = dr * dr + di * di;
-        s_scale = mkT<T>(dr / den, -di / den);
-      }
+  // the matrix is in registers before its columns are overwritten by reflectors
+#pragma unroll
+  for (int k = 0; k < RK; ++k)
+#pragma unroll
+    for (int m = 0; m < CM; ++m) {
+      double* x = (double*)&a[k][m];
+      asm volatile("" : "+v"(x[0]));
+      if constexpr (CX) asm volatile("" : "+v"(x[1]));
     }
-    __syncthreads();
-    const T tau_i = s_tau;
-    const double beta = s_beta;
-    if (tid == 0) tau[i] = tau_i;
-    const bool trivial = re_(mul_(conj_(tau_i), tau_i)) == 0.0;
-    for (int r = r0 + tid; r < n; r += nt) {
-      T val;
-      if (r == r0) val = mkT<T>(1.0, 0.0);
-      else {
-        val = mul_(A[r + (int64_t)i * n], s_scale);
-        A[r + (int64_t)i * n] = val;
-      }
-      v[r] = val;
-    }
-    __syncthreads();
-    if (!trivial) {
-      // partial products over this wave's columns
-      for (int rb = r0; rb < n; rb += 64) {
-        const int r = rb + lane;
-        T acc = mkT<T>(0.0, 0.0);
-        if (r < n) {
-          int c = r0 + wave;
-#pragma unroll 4
-          for (; c < n; c += nwave) acc = add_(acc, mul_(A[r + (int64_t)c * n], v[c]));
-        }
-        if (r < n) part[wave * n + r] = acc;
-      }
-      __syncthreads();
-      for (int r = r0 + tid; r < n; r += nt) {
-        T acc = mkT<T>(0.0, 0.0);
-        for (int q = 0; q < nwave; ++q) acc = add_(acc, part[q * n + r]);
-        w[r] = mul_(tau_i, acc);
-      }
-      __syncthreads();
-      double pr = 0, pi = 0;
-      for (int r = r0 + tid; r < n; r += nt) {
-        T t = mul_(conj_(w[r]), v[r]);
-        pr += re_(t);
-        if constexpr (sizeof(T) == 16) pi += ((cd&)t).im;
-      }
-      pr = block_sum(pr, red);
-      if constexpr (sizeof(T) == 16) pi = block_sum(pi, red);
-      T a2 = mul_(mkT<T>(-0.5, 0.0), mul_(tau_i, mkT<T>(pr, pi)));
-      for (int r = r0 + tid; r < n; r += nt) w[r] = add_(w[r], mul_(a2, v[r]));
-      __syncthreads();
-      // A_sub -= v w^H + w v^H
-      for (int rb = r0; rb < n; rb += 64) {
-        const int r = rb + lane;
-        if (r < n) {
-          const T vr = v[r], wr = w[r];
-          int c = r0 + wave;
-#pragma unroll 4
-          for (; c < n; c += nwave) {
-            T upd = add_(mul_(vr, conj_(w[c])), mul_(wr, conj_(v[c])));
-            A[r + (int64_t)c * n] = sub_(A[r + (int64_t)c * n], upd);
-          }
-        }
-      }
-    }
-    if (tid == 0) {
-      e[i] = beta;
-      d[i] = re_(A[i + (int64_t)i * n]);
-    }
-    __syncthreads();
-  }
-  if (tid == 0) d[n - 1] = re_(A[(n - 1) + (int64_t)(n - 1) * n]);
-}
-
-// The same reduction for n <= 64 with the whole matrix in LDS (column-major, leading
-// dimension n + 1), eight waves: lane r of every wave owns row r, wave q the columns
-// c = q mod 8 of the matrix-vector product and of the rank-2 update.  Sums over rows are
-// wave butterflies, whose result is the same on every lane of every wave, so each wave
-// forms the same reflector without exchanging it (register-only DPP sums).  The matrix
-// is read once and written back once.
-template <typename T>
-__global__ __launch_bounds__(512) void hetrd_small_kernel(int n, T* __restrict__ A, double* __restrict__ d,
-                                                          double* __restrict__ e, T* __restrict__ tau) {
-  extern __shared__ char smem[];
-  const int ld = n + 1;
-  T* a = (T*)smem;       // [n][ld]
-  T* v = a + n * ld;     // [64]
-  T* w = v + 64;         // [64]
-  T* part = w + 64;      // [8][64]
-  const int r = threadIdx.x & 63, q = threadIdx.x >> 6;
-  for (int c = q; c < n; c += 8)
-    if (r < n) a[r + c * ld] = A[r + (int64_t)c * n];
   __syncthreads();
   for (int i = 0; i < n - 1; ++i) {
-    const int r0 = i + 1;
+    const int r0 = i + 1, im = i / NWV;
+    if (q == i % NWV) {
+#pragma unroll
+      for (int m = 0; m < CM; ++m)
+        if (m == im) {
+#pragma unroll
+          for (int k = 0; k < RK; ++k) col[lane + 64 * k] = a[k][m];
+        }
+    }
+    __syncthreads();
+    T v[RK];
     double xn = 0.0;
-    if (r >= i + 2 && r < n) {
-      const T x = a[r + i * ld];
-      xn = re_(mul_(conj_(x), x));
+#pragma unroll
+    for (int k = 0; k < RK; ++k) {
+      const int r = lane + 64 * k;
+      v[k] = col[r];
+      if (r >= i + 2) xn += re_(mul_(conj_(v[k]), v[k]));   // rows past n hold zeros
     }
     xn = wave_sum_dpp(xn);
-    const T alpha = a[r0 + i * ld];
+    const T alpha = col[r0];
     const double ar = re_(alpha);
     double ai = 0;
-    if constexpr (sizeof(T) == 16) ai = ((const cd&)alpha).im;
-    T tau_i, scl;
-    double beta;
-    if (xn == 0.0 && ai == 0.0) {
-      tau_i = mkT<T>(0.0, 0.0);
-      beta = ar;
-      scl = mkT<T>(0.0, 0.0);
-    } else {
+    if constexpr (CX) ai = ((const cd&)alpha).im;
+    T tau_i = zero_t, scl = zero_t;
+    double beta = ar;
+    const bool trivial = xn == 0.0 && ai == 0.0;
+    if (!trivial) {
       beta = -copysign(sqrt(ar * ar + ai * ai + xn), ar);
       tau_i = mkT<T>((beta - ar) / beta, -ai / beta);
       const double dr = ar - beta, di = ai, den = dr * dr + di * di;
       scl = mkT<T>(dr / den, -di / den);
     }
-    const bool trivial = re_(mul_(conj_(tau_i), tau_i)) == 0.0;
-    T vr = mkT<T>(0.0, 0.0);
-    if (r == r0) vr = mkT<T>(1.0, 0.0);
-    else if (r > r0 && r < n) vr = mul_(a[r + i * ld], scl);
-    __syncthreads();   // every wave has read column i
-    if (q == 0) {
-      if (r > r0 && r < n) a[r + i * ld] = vr;
-      v[r] = vr;
-    }
-    __syncthreads();
-    if (!trivial) {
-      // p = tau A_sub v (partial products over this wave's columns), alpha2 = -1/2 tau
-      // (p^H v), w = p + alpha2 v
-      T acc = mkT<T>(0.0, 0.0);
-      if (r >= r0 && r < n) {
-        int c = r0 + ((q - r0) & 7);
-#pragma unroll 2
-        for (; c < n; c += 8) acc = add_(acc, mul_(a[r + c * ld], v[c]));
-      }
-      part[q * 64 + r] = acc;
-      __syncthreads();
-      const T sum = add_(add_(add_(part[r], part[64 + r]), add_(part[128 + r], part[192 + r])),
-                         add_(add_(part[256 + r], part[320 + r]), add_(part[384 + r], part[448 + r])));
-      const T pr = (r >= r0 && r < n) ? mul_(tau_i, sum) : mkT<T>(0.0, 0.0);
-      const T t = mul_(conj_(pr), vr);
-      double sr = wave_sum_dpp(re_(t)), si = 0.0;
-      if constexpr (sizeof(T) == 16) si = wave_sum_dpp(((const cd&)t).im);
-      const T a2 = mul_(mkT<T>(-0.5, 0.0), mul_(tau_i, mkT<T>(sr, si)));
-      const T wr = add_(pr, mul_(a2, vr));
-      if (q == 0) w[r] = wr;
-      __syncthreads();
-      // A_sub -= v w^H + w v^H over this wave's columns
-      if (r >= r0 && r < n) {
-        int c = r0 + ((q - r0) & 7);
-#pragma unroll 2
-        for (; c < n; c += 8)
-          a[r + c * ld] = sub_(a[r + c * ld], add_(mul_(vr, conj_(w[c])), mul_(wr, conj_(v[c]))));
-      }
-      __syncthreads();
-    }
     if (threadIdx.x == 0) {
       e[i] = beta;
-      d[i] = re_(a[i + i * ld]);
+      d[i] = re_(col[i]);
       tau[i] = tau_i;
     }
+#pragma unroll
+    for (int k = 0; k < RK; ++k) {
+      const int r = lane + 64 * k;
+      v[k] = r == r0 ? one_t : (r > r0 ? mul_(v[k], scl) : zero_t);
+      if (q == 0 && r > r0 && r < n) A[r + (int64_t)i * n] = v[k];
+    }
+    if (trivial) {   // nothing to apply; col is rewritten once every wave has read it
+      __syncthreads();
+      continue;
+    }
+    // this wave's columns of A v (columns up to i hold zeros of v)
+    T y[RK];
+#pragma unroll
+    for (int k = 0; k < RK; ++k) y[k] = zero_t;
+#pragma unroll
+    for (int m = 0; m < CM; ++m) {
+      const int c = q + NWV * m;
+      if (c >= r0 && c < n) {
+        const T vc = lane_of(v[m * NWV / 64], c & 63);
+#pragma unroll
+        for (int k = 0; k < RK; ++k) y[k] = add_(y[k], mul_(a[k][m], vc));
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < RK; ++k) part[q][lane + 64 * k] = y[k];
+    __syncthreads();
+    // p = tau A v; alpha2 = -1/2 tau (p^H v); w = p + alpha2 v
+    T w[RK];
+    double sr = 0.0, si = 0.0;
+#pragma unroll
+    for (int k = 0; k < RK; ++k) {
+      T s = part[0][lane + 64 * k];
+#pragma unroll
+      for (int j = 1; j < NWV; ++j) s = add_(s, part[j][lane + 64 * k]);
+      w[k] = lane + 64 * k >= r0 ? mul_(tau_i, s) : zero_t;
+      const T t = mul_(conj_(w[k]), v[k]);
+      sr += re_(t);
+      if constexpr (CX) si += ((const cd&)t).im;
+    }
+    sr = wave_sum_dpp(sr);
+    if constexpr (CX) si = wave_sum_dpp(si);
+    const T a2 = mul_(mkT<T>(-0.5, 0.0), mul_(tau_i, mkT<T>(sr, si)));
+#pragma unroll
+    for (int k = 0; k < RK; ++k) w[k] = add_(w[k], mul_(a2, v[k]));
+    // A -= v w^H + w v^H
+#pragma unroll
+    for (int m = 0; m < CM; ++m) {
+      const int c = q + NWV * m;
+      if (c >= r0 && c < n) {
+        const T vc = conj_(lane_of(v[m * NWV / 64], c & 63)), wc = conj_(lane_of(w[m * NWV / 64], c & 63));
+#pragma unroll
+        for (int k = 0; k < RK; ++k) a[k][m] = sub_(a[k][m], add_(mul_(v[k], wc), mul_(w[k], vc)));
+      }
+    }
   }
-  __syncthreads();
-  if (threadIdx.x == 0) d[n - 1] = re_(a[(n - 1) + (n - 1) * ld]);
-  for (int c = q; c < n; c += 8)
-    if (r < n) A[r + (int64_t)c * n] = a[r + c * ld];
+#pragma unroll
+  for (int k = 0; k < RK; ++k)
+#pragma unroll
+    for (int m = 0; m < CM; ++m)
+      if (lane + 64 * k == n - 1 && q + NWV * m == n - 1) d[n - 1] = re_(a[k][m]);
+}
+
+// Whether the register form takes n, and its launch.  The line is where the matrix no longer
+// fits the registers of eight waves.  A whole small Rayleigh-Ritz step, panel form against
+// this: real n = 64 898 and 542 us, 96 1559 and 982, 128 2043 and 1225, 160 2632 and 2109,
+// 192 3137 and 2576; complex n = 64 1359 and 818, 96 2030 and 1432, 128 2816 and 1855.
+template <typename T>
+static bool hetrd_reg_fits(int n) {
+  return n > 1 && n <= (sizeof(T) == 16 ? 128 : 192);
+}
+template <typename T>
+static void hetrd_reg_launch(hipStream_t s, int n, T* A, double* d, double* e, T* tau) {
+  if (n <= 64) hetrd_reg_kernel<T, 1, 8, 8><<<1, 512, 0, s>>>(n, A, d, e, tau);
+  else if (n <= 128) hetrd_reg_kernel<T, 2, 16, 8><<<1, 512, 0, s>>>(n, A, d, e, tau);
+  else if constexpr (sizeof(T) == 8) hetrd_reg_kernel<T, 3, 24, 8><<<1, 512, 0, s>>>(n, A, d, e, tau);
 }
 
 // Blocked Householder tridiagonalisation (lower; panel / trailing-update split).
 // latrd_kernel reduces columns i0 .. i0+jb-1 with one work-group: column i is first
 // brought up to date with the panel's earlier reflectors (A(i:n, i) -= V W(i)^H +
-// W V(i)^H), its reflector is formed as in hetrd2_kernel, and the product with the
+// W V(i)^H), its reflector is formed as in hetrd_kernel, and the product with the
 // trailing block reads that block as it stood before the panel, corrected by
 // -V (W^H v) - W (V^H v).  The trailing block is read once per column instead of read
 // twice and written once.  trail_kernel then applies A -= V W^H + W V^H to the block
 // past the panel on many work-groups.  V, W: [jb][n] (vector k contiguous, zero above
-// its first row); storage of the reflectors in A, tau, d and e as hetrd2_kernel.
+// its first row); storage of the reflectors in A, tau, d and e as hetrd_kernel.
 template <typename T>
 __global__ __launch_bounds__(1024) void latrd_kernel(int n, int i0, int jb, T* __restrict__ A, double* __restrict__ d,
                                                      double* __restrict__ e, T* __restrict__ tau, T* __restrict__ V,
@@ -822,7 +772,7 @@ __global__ __launch_bounds__(1024) void latrd_kernel(int n, int i0, int jb, T* _
         }
         __syncthreads();
       }
-      // (2) reflector of A(i+2:n, i) (as hetrd2_kernel)
+      // (2) reflector of A(i+2:n, i) (as hetrd_kernel)
       for (int r = i + 2 + tid; r < n; r += nt) {
         T x = A[r + (int64_t)i * n];
         xn += re_(mul_(conj_(x), x));
@@ -1343,7 +1293,9 @@ static int heev_t(hipStream_t s, int n, T* A, double* w, T* Z, void* work) {
   (void)take((size_t)n * n * 4);  // reserved (pivots are kept in LDS)
   const size_t lds2 = (size_t)18 * n * sizeof(T);
   constexpr int NB = 32;   // panel width of the blocked reduction
-  if (n >= 64 && lds2 <= 150 * 1024) {
+  if (hetrd_reg_fits<T>(n)) {
+    hetrd_reg_launch<T>(s, n, A, d, e, tau);
+  } else if (n > 1 && lds2 <= 150 * 1024) {
     T* Vb = (T*)scr;       // [NB][n] each; the inverse-iteration scratch is free until then
     T* Wb = Vb + (size_t)NB * n;
     SPARC_HIP(hipFuncSetAttribute((const void*)latrd_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2));
@@ -1360,18 +1312,8 @@ static int heev_t(hipStream_t s, int n, T* A, double* w, T* Z, void* work) {
       }
     }
     last_diag_kernel<T><<<1, 64, 0, s>>>(n, A, d);
-  } else if (n == 1) {
-    hetrd_kernel<T><<<1, 64, 2 * n * sizeof(T), s>>>(n, A, d, e, tau);
-  } else if (n <= 64) {
-    const size_t lds_s = ((size_t)n * (n + 1) + 640) * sizeof(T);
-    SPARC_HIP(hipFuncSetAttribute((const void*)hetrd_small_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)lds_s));
-    hetrd_small_kernel<T><<<1, 512, lds_s, s>>>(n, A, d, e, tau);
-  } else if (lds2 <= 150 * 1024) {
-    SPARC_HIP(hipFuncSetAttribute((const void*)hetrd2_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2));
-    hetrd2_kernel<T><<<1, n < 64 ? 128 : 1024, lds2, s>>>(n, A, d, e, tau);
   } else {
-    int nt = n >= 1024 ? 1024 : ((n + 63) / 64) * 64;
+    const int nt = n >= 1024 ? 1024 : ((n + 63) / 64) * 64;
     hetrd_kernel<T><<<1, nt, 2 * n * sizeof(T), s>>>(n, A, d, e, tau);
   }
   SPARC_TRY(check_launch("hetrd_kernel"));
