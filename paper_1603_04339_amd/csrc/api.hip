@@ -307,20 +307,27 @@ static int sub_vec(sparc_dtype dt, hipStream_t s, void* w, const void* t, int64_
 
 // Chebyshev filter of degree m (three-term recurrence, one stencil step per degree):
 // each step projects its input onto the projectors, then the stencil step applies the
-// local and (inside the step, or with the scatter kernel after it) non-local terms.
+// local and (inside the step, or with the scatter kernel after it) non-local terms; in the
+// update form the scatter of a step makes the projections for the next one.
 int filter_impl(sparc_ham* H, void* X, int64_t ldx, int32_t n_s, int32_t degree, double lcut, double lmax,
                 void* Wb, void* alpha) {
   const double c = 0.5 * (lmax + lcut), e = 0.5 * (lmax - lcut);
   const int64_t N = H->n_d;
+  const bool upd = nl_update_applies(H) && nl_update_pairs(H, n_s) >= 2 * (int64_t)H->ctx->n_cu;
   SPARC_TRY(nl_project(H, X, ldx, n_s, alpha));
-  SPARC_TRY(ham_step(H, X, ldx, nullptr, 0, Wb, N, n_s, 1.0 / e, -c / e, 0.0, alpha));
+  SPARC_TRY(ham_step(H, X, ldx, nullptr, 0, Wb, N, n_s, 1.0 / e, -c / e, 0.0, alpha,
+                     upd && degree > 1 ? STEP_NO_NONLOCAL : 0));
+  if (upd && degree > 1) SPARC_TRY(nl_update(H, alpha, n_s, 1.0 / e, Wb, N));
   void* prev = X;
   int64_t ldp = ldx;
   void* cur = Wb;
   int64_t ldc = N;
   for (int j = 1; j < degree; ++j) {
-    SPARC_TRY(nl_project(H, cur, ldc, n_s, alpha));
-    SPARC_TRY(ham_step(H, cur, ldc, prev, ldp, prev, ldp, n_s, 2.0 / e, -2.0 * c / e, -1.0, alpha));
+    const bool more = upd && j + 1 < degree;
+    if (!upd) SPARC_TRY(nl_project(H, cur, ldc, n_s, alpha));
+    SPARC_TRY(ham_step(H, cur, ldc, prev, ldp, prev, ldp, n_s, 2.0 / e, -2.0 * c / e, -1.0, alpha,
+                       more ? STEP_NO_NONLOCAL : 0));
+    if (more) SPARC_TRY(nl_update(H, alpha, n_s, 2.0 / e, prev, ldp));
     std::swap(prev, cur);
     std::swap(ldp, ldc);
   }

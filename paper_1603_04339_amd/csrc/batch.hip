@@ -32,6 +32,7 @@ struct sparc_filter_plan {
   std::vector<sparc_ham*> H;
   std::vector<void*> X, W, alpha;
   std::vector<char> fused;        // the problem applies its projectors inside the step
+  bool update;                    // a step's scatter makes the projections of the next
   std::vector<int64_t> ldx;
   std::vector<int> n_s, deg;
   // per step: participating problems, their table and work-group offsets
@@ -65,6 +66,11 @@ struct sparc_filter_plan {
 
 namespace sparc {
 
+// orbitals per thread of step j's scatter launch
+static int scatter_nb(const sparc_filter_plan* P, int j) {
+  return P->update && j + 1 < P->max_deg ? kSharedNB : kScatterNB;
+}
+
 // the step sequence of all problems (enqueued directly, or recorded into the graph)
 static int plan_enqueue(sparc_filter_plan* P) {
   const size_t eb = elem_bytes(P->dt);
@@ -72,8 +78,9 @@ static int plan_enqueue(sparc_filter_plan* P) {
     const auto& mem = P->members[j];
     // projections of the step input (all problems, one launch)
     const size_t t0 = (size_t)j * P->n_prob, o0 = (size_t)j * (P->n_prob + 1);
-    SPARC_TRY(nl_gather_batched(P->ctx, P->dt, P->maxp, P->dev_gather + t0, P->dev_goff + o0, P->n_gather[j],
-                                P->gather_wg[j]));
+    if (j == 0 || !P->update)
+      SPARC_TRY(nl_gather_batched(P->ctx, P->dt, P->maxp, P->dev_gather + t0, P->dev_goff + o0, P->n_gather[j],
+                                  P->gather_wg[j]));
     if (!P->row.empty()) {
       // one launch per chunk width (the step's problems are in that order)
       for (size_t a = 0, b; a < mem.size(); a = b) {
@@ -87,9 +94,14 @@ static int plan_enqueue(sparc_filter_plan* P) {
       SPARC_TRY(step_table_launch(P->ctx, P->dt, P->n_o, P->tile, P->dev_tables + P->table_off[j],
                                   P->dev_wg + P->wg_off[j], (int)mem.size(), P->total_wg[j], P->dir, P->nl_lds[j]));
     }
-    // projector scatters of the problems that do not apply them inside the step (one launch)
-    SPARC_TRY(nl_scatter_batched(P->ctx, P->dt, P->dev_scatter + t0, P->dev_soff + o0, P->n_scatter[j],
-                                 P->scatter_wg[j], P->dev_a + (size_t)j * P->n_prob));
+    // projector scatters of the problems that do not apply them inside the step (one launch);
+    // in the update form, of the shared nodes alone where a step follows
+    SPARC_TRY(nl_scatter_batched(P->ctx, P->dt, scatter_nb(P, j), P->dev_scatter + t0, P->dev_soff + o0,
+                                 P->n_scatter[j], P->scatter_wg[j], P->dev_a + (size_t)j * P->n_prob));
+    if (P->update && j + 1 < P->max_deg)
+      SPARC_TRY(nl_update_batched(P->ctx, P->dt, P->maxp, P->dev_gather + t0 + P->n_prob,
+                                  P->dev_goff + o0 + P->n_prob + 1, P->n_gather[j + 1], P->gather_wg[j + 1],
+                                  P->dev_a + (size_t)j * P->n_prob));
   }
   // Y_m of an odd degree sits in the work block
   for (int p = 0; p < P->n_prob; ++p)
@@ -135,9 +147,12 @@ static int plan_tables(sparc_filter_plan* P, const double* lcut, const double* l
       // projections of Y_j and (separate form) the scatter into Y_{j+1}
       NlBatchArgs nb;
       int gw = 0, sw = 0;
-      nl_batch_args(P->H[p], s.x, s.ldx, s.out, s.ldo, s.n_s, P->alpha[p], p, &nb, &gw, &sw);
+      nl_batch_args(P->H[p], s.x, s.ldx, s.out, s.ldo, s.n_s, P->alpha[p], p, scatter_nb(P, j), &nb, &gw, &sw);
+      NlBatchArgs gb = nb;
+      if (P->update && j > 0) gw = nl_update_args(P->H[p], (void*)s.x, s.ldx, s.n_s, P->alpha[p], p, &gb);
+      if (P->update && j + 1 < P->deg[p] && sw > 0) sw = nl_shared_args(P->H[p], scatter_nb(P, j), &nb);
       if (gw > 0) {
-        P->host_gather[(size_t)j * P->n_prob + P->n_gather[j]] = nb;
+        P->host_gather[(size_t)j * P->n_prob + P->n_gather[j]] = gb;
         P->host_goff[(size_t)j * (P->n_prob + 1) + P->n_gather[j]] = (int)P->gather_wg[j];
         P->gather_wg[j] += gw;
         P->n_gather[j]++;
@@ -363,6 +378,16 @@ int sparc_filter_plan_create(sparc_ctx* ctx, int32_t n_prob, sparc_ham* const* H
     if (rc != SPARC_OK) { delete P; return rc; }
   }
   for (int p = 0; p < n_prob; ++p) P->fused.push_back(P->row.empty() && nl_step_fused(H[p], P->tile) ? 1 : 0);
+  // the update form for the plan as a whole: all problems with projectors allow it and
+  // together they are enough for it
+  int64_t pairs = 0;
+  P->update = true;
+  for (int p = 0; p < n_prob; ++p) {
+    if (P->H[p]->n_proj == 0 || P->H[p]->n_nlpts == 0) continue;
+    P->update = P->update && nl_update_applies(P->H[p]);
+    pairs += nl_update_pairs(P->H[p], n_s[p]);
+  }
+  P->update = P->update && pairs >= 2 * (int64_t)ctx->n_cu;
   P->use_graph = use_graph != 0;
   P->cap_stream = nullptr;
   P->graph = nullptr;

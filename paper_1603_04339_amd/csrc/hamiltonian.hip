@@ -83,6 +83,37 @@ __global__ __launch_bounds__(256) void nl_scatter_batched_kernel(const NlBatchAr
                          (typename elem<E>::real)a_dev[P.slot], (E*)P.y, P.ldy);
 }
 
+// the projections of one work-group's sums: wave butterflies, then across the 4 waves
+// through LDS
+template <typename E, int MAXP, int NB>
+__device__ __forceinline__ void nl_store_projections(const E (&acc)[MAXP][NB], int pb, int np, int nb0, int n_s,
+                                                     double dV, E* __restrict__ alpha, int lda) {
+  typedef typename elem<E>::real R;
+  constexpr int NV = elem<E>::is_cplx ? 2 : 1;
+  __shared__ R red[4][MAXP * NB * NV];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+  for (int p = 0; p < MAXP; ++p)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const R* comp = (const R*)&acc[p][j];
+#pragma unroll
+      for (int c = 0; c < NV; ++c) {
+        R s = wave_sum(comp[c]);
+        if (lane == 0) red[wv][(p * NB + j) * NV + c] = s;
+      }
+    }
+  __syncthreads();
+  for (int i = threadIdx.x; i < MAXP * NB * NV; i += blockDim.x) {
+    int pj = i / NV, c = i % NV;
+    int p = pj / NB, j = pj % NB;
+    if (p < np && nb0 + j < n_s) {
+      R s = red[0][i] + red[1][i] + red[2][i] + red[3][i];
+      ((R*)&alpha[(int64_t)(pb + p) * lda + nb0 + j])[c] = (R)(dV * (double)s);
+    }
+  }
+}
+
 // Non-local gather: alpha[p][n] = dV * sum_{t in supp(atom)} conj(chi~_p(t)) x(g_t, n)
 // One work-group per (atom, block of NB orbitals).
 template <typename E, int MAXP, int NB>
@@ -92,8 +123,6 @@ __device__ __forceinline__ void nl_gather_body(int a, int nb0, const E* __restri
                                                const int32_t* __restrict__ atom_pbeg,
                                                const int64_t* __restrict__ proj_voff, const E* __restrict__ pval,
                                                double dV, E* __restrict__ alpha, int lda) {
-  typedef typename elem<E>::real R;
-  constexpr int NV = elem<E>::is_cplx ? 2 : 1;
   const int t0 = sup_ptr[a], t1 = sup_ptr[a + 1];
   const int pb = atom_pbeg[a], np = atom_pbeg[a + 1] - pb;
   E acc[MAXP][NB];
@@ -119,29 +148,7 @@ __device__ __forceinline__ void nl_gather_body(int a, int nb0, const E* __restri
       }
     }
   }
-  // block reduction: wave butterflies, then across the 4 waves through LDS
-  __shared__ R red[4][MAXP * NB * NV];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-  for (int p = 0; p < MAXP; ++p)
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const R* comp = (const R*)&acc[p][j];
-#pragma unroll
-      for (int c = 0; c < NV; ++c) {
-        R s = wave_sum(comp[c]);
-        if (lane == 0) red[wv][(p * NB + j) * NV + c] = s;
-      }
-    }
-  __syncthreads();
-  for (int i = threadIdx.x; i < MAXP * NB * NV; i += blockDim.x) {
-    int pj = i / NV, c = i % NV;
-    int p = pj / NB, j = pj % NB;
-    if (p < np && nb0 + j < n_s) {
-      R s = red[0][i] + red[1][i] + red[2][i] + red[3][i];
-      ((R*)&alpha[(int64_t)(pb + p) * lda + nb0 + j])[c] = (R)(dV * (double)s);
-    }
-  }
+  nl_store_projections<E, MAXP, NB>(acc, pb, np, nb0, n_s, dV, alpha, lda);
 }
 
 template <typename E, int MAXP, int NB>
@@ -173,6 +180,125 @@ __global__ __launch_bounds__(256) void nl_gather_batched_kernel(const NlBatchArg
   const int local = b - off[lo];
   nl_gather_body<E, MAXP, NB>(local % P.n_atoms, (local / P.n_atoms) * NB, (const E*)P.x, P.ldx, P.n_s, P.sup_ptr,
                               P.sup_idx, P.atom_pbeg, P.proj_voff, (const E*)P.pval, P.dV, (E*)P.alpha, P.lda);
+}
+
+__device__ __forceinline__ double uniform_real(double v) { return readlane_f64(v, 0); }
+__device__ __forceinline__ float uniform_real(float v) {
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+
+// Scatter of one step and gather of the next in one pass over an atom's support:
+//   y(g, n) += a * sum_p gamma_p chi~_p(g) alpha[p][n],  then alpha[p][n] = dV * sum_g conj(chi~_p(g)) y(g, n).
+// Nodes in several supports (marked ~g) need the other atoms' terms too: the scatter kernel
+// has added all of theirs before, over the list of shared nodes alone, and here they are only
+// read.  An atom's coefficients are read and replaced by its own work-group.  Bound by memory, by
+// the 128-byte lines of the supports: apart, the two kernels read them twice.  96^3, 64 atoms, 512
+// states, FP64: scatter 621 and gather 375 us, here shared scatter 101 and update 662 (8 orbitals
+// per thread 714, 4 with non-temporal loads slower still); 24 FP64 filter steps 77.4 -> 74.2 ms.
+template <typename E, int MAXP, int NB>
+__device__ __forceinline__ void nl_update_body(int a, int nb0, E* __restrict__ y, int64_t ldy, int n_s,
+                                               typename elem<E>::real scale, const int32_t* __restrict__ sup_ptr,
+                                               const int32_t* __restrict__ mark, const int32_t* __restrict__ atom_pbeg,
+                                               const int64_t* __restrict__ proj_voff, const E* __restrict__ pval,
+                                               const typename elem<E>::real* __restrict__ gamma, double dV, E* alpha,
+                                               int lda) {
+  typedef typename elem<E>::real R;
+  constexpr int NV = elem<E>::is_cplx ? 2 : 1;
+  const int t0 = sup_ptr[a], t1 = sup_ptr[a + 1];
+  const int pb = atom_pbeg[a], np = atom_pbeg[a + 1] - pb;
+  E acc[MAXP][NB], ga[MAXP][NB];
+  int64_t voff[MAXP];
+#pragma unroll
+  for (int p = 0; p < MAXP; ++p) {
+    voff[p] = (p < np) ? proj_voff[pb + p] : 0;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      acc[p][j] = ga[p][j] = zero<E>();
+      if (p < np && nb0 + j < n_s) {
+        const E v = alpha[(int64_t)(pb + p) * lda + nb0 + j];
+        const R g = gamma[pb + p];
+#pragma unroll
+        for (int c = 0; c < NV; ++c) ((R*)&ga[p][j])[c] = uniform_real(g * ((const R*)&v)[c]);
+      }
+    }
+  }
+  int t = t0 + (int)threadIdx.x;
+  int32_t m = 0;
+  E chi[MAXP], yv[NB];
+  auto load = [&](int tt, int32_t& mm, E (&cc)[MAXP], E (&yy)[NB]) {
+    mm = mark[tt];
+    const int64_t g = mm < 0 ? ~mm : mm;
+#pragma unroll
+    for (int p = 0; p < MAXP; ++p) cc[p] = (p < np) ? pval[voff[p] + (tt - t0)] : zero<E>();
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+      if (nb0 + j < n_s) yy[j] = y[g + (int64_t)(nb0 + j) * ldy];
+  };
+  if (t < t1) load(t, m, chi, yv);
+  while (t < t1) {
+    // the next node's loads are in flight while this one is worked on (an atom's support
+    // holds a node once)
+    const int tn = t + 256;
+    int32_t mn = 0;
+    E chin[MAXP], yn[NB];
+    if (tn < t1) load(tn, mn, chin, yn);
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      if (nb0 + j < n_s) {
+        if (m >= 0) {
+          E s = zero<E>();
+#pragma unroll
+          for (int p = 0; p < MAXP; ++p) s = fmae(s, chi[p], ga[p][j]);
+          yv[j] = fmar(yv[j], scale, s);
+          y[m + (int64_t)(nb0 + j) * ldy] = yv[j];
+        }
+#pragma unroll
+        for (int p = 0; p < MAXP; ++p) acc[p][j] = fmac(acc[p][j], chi[p], yv[j]);
+      }
+    }
+    t = tn;
+    m = mn;
+#pragma unroll
+    for (int p = 0; p < MAXP; ++p) chi[p] = chin[p];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) yv[j] = yn[j];
+  }
+  nl_store_projections<E, MAXP, NB>(acc, pb, np, nb0, n_s, dV, alpha, lda);
+}
+
+template <typename E, int MAXP, int NB>
+__global__ __launch_bounds__(256) void nl_update_kernel(E* __restrict__ y, int64_t ldy, int n_s,
+                                                        typename elem<E>::real scale,
+                                                        const int32_t* __restrict__ sup_ptr,
+                                                        const int32_t* __restrict__ mark,
+                                                        const int32_t* __restrict__ atom_pbeg,
+                                                        const int64_t* __restrict__ proj_voff,
+                                                        const E* __restrict__ pval,
+                                                        const typename elem<E>::real* __restrict__ gamma, double dV,
+                                                        E* alpha, int lda) {
+  nl_update_body<E, MAXP, NB>(blockIdx.x, blockIdx.y * NB, y, ldy, n_s, scale, sup_ptr, mark, atom_pbeg, proj_voff,
+                              pval, gamma, dV, alpha, lda);
+}
+
+// Several problems in one launch, work-groups as in nl_gather_batched_kernel, the scale of a
+// problem's finished step from the device step table
+template <typename E, int MAXP, int NB>
+__global__ __launch_bounds__(256) void nl_update_batched_kernel(const NlBatchArgs* __restrict__ probs,
+                                                                const int* __restrict__ off, int n_probs,
+                                                                const double* __restrict__ a_dev) {
+  typedef typename elem<E>::real R;
+  const int b = blockIdx.x;
+  int lo = 0, hi = n_probs - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) / 2;
+    if (off[mid] <= b) lo = mid;
+    else hi = mid - 1;
+  }
+  const NlBatchArgs& P = probs[lo];
+  const int local = b - off[lo];
+  nl_update_body<E, MAXP, NB>(local % P.n_atoms, (local / P.n_atoms) * NB, (E*)P.y, P.ldy, P.n_s, (R)a_dev[P.slot],
+                              P.sup_ptr, P.pts, P.atom_pbeg, P.proj_voff, (const E*)P.pval, (const R*)P.ent_coef,
+                              P.dV, (E*)P.alpha, P.lda);
 }
 
 // projections are stored [projector][orbital] with the orbital count padded to a multiple of 16
@@ -369,11 +495,11 @@ static bool nl_fill(sparc_ham* H, StepArgs<E>& A, int t, double a, const void* a
 }
 
 template <typename E>
+static constexpr int update_nb() { return elem<E>::is_cplx ? 2 : 4; }
+template <typename E>
 static constexpr int gather_nb() { return elem<E>::is_cplx ? 4 : 8; }
-constexpr int kScatterNB = 16;
-
 void nl_batch_args(const sparc_ham* H, const void* x, int64_t ldx, void* y, int64_t ldy, int n_s, void* alpha,
-                   int slot, NlBatchArgs* o, int* gather_wg, int* scatter_wg) {
+                   int slot, int snb, NlBatchArgs* o, int* gather_wg, int* scatter_wg) {
   o->x = x;
   o->ldx = ldx;
   o->y = y;
@@ -397,7 +523,25 @@ void nl_batch_args(const sparc_ham* H, const void* x, int64_t ldx, void* y, int6
   const int gnb = dtype_complex(H->dtype) ? 4 : 8;
   const bool any = H->n_proj > 0 && H->n_nlpts > 0;
   *gather_wg = any ? H->n_atoms_nl * ((n_s + gnb - 1) / gnb) : 0;
-  *scatter_wg = any ? (int)((H->n_nlpts + 255) / 256) * ((n_s + kScatterNB - 1) / kScatterNB) : 0;
+  *scatter_wg = any ? (int)((H->n_nlpts + 255) / 256) * ((n_s + snb - 1) / snb) : 0;
+}
+
+int nl_update_args(const sparc_ham* H, void* y, int64_t ldy, int n_s, void* alpha, int slot, NlBatchArgs* o) {
+  int gw, sw;
+  nl_batch_args(H, y, ldy, y, ldy, n_s, alpha, slot, kScatterNB, o, &gw, &sw);
+  o->pts = H->sup_mark;
+  o->ent_coef = H->gamma_d;
+  const int nb = dtype_complex(H->dtype) ? update_nb<cd>() : update_nb<double>();
+  return gw > 0 ? H->n_atoms_nl * ((n_s + nb - 1) / nb) : 0;
+}
+
+int nl_shared_args(const sparc_ham* H, int nb, NlBatchArgs* o) {
+  o->n_pts = (int)H->n_shared;
+  o->pts = H->sh_pts;
+  o->ptr = H->sh_ptr;
+  o->ent_proj = H->sh_proj;
+  o->ent_coef = H->sh_coef;
+  return (int)((H->n_shared + 255) / 256) * ((o->n_s + nb - 1) / nb);
 }
 
 template <typename E>
@@ -424,23 +568,51 @@ int nl_gather_batched(sparc_ctx* ctx, sparc_dtype dt, int maxp, const NlBatchArg
 }
 
 template <typename E>
-static int scatter_batched_t(sparc_ctx* ctx, const NlBatchArgs* tab, const int* off, int n, int64_t total,
+static int update_batched_t(sparc_ctx* ctx, int maxp, const NlBatchArgs* tab, const int* off, int n, int64_t total,
+                            const double* a_dev) {
+  if (total <= 0) return SPARC_OK;
+  if (total > INT32_MAX) return fail(SPARC_ESHAPE, "batched projector update: too many work-groups");
+  int t = timer_begin(ctx, "nl_update");
+  if (maxp <= 1)
+    nl_update_batched_kernel<E, 1, update_nb<E>()><<<(unsigned)total, 256, 0, ctx->stream>>>(tab, off, n, a_dev);
+  else
+    nl_update_batched_kernel<E, 4, update_nb<E>()><<<(unsigned)total, 256, 0, ctx->stream>>>(tab, off, n, a_dev);
+  timer_end(ctx, t);
+  return check_launch("nl_update_batched_kernel");
+}
+
+int nl_update_batched(sparc_ctx* ctx, sparc_dtype dt, int maxp, const NlBatchArgs* tab, const int* off, int n,
+                      int64_t total, const double* a_dev) {
+  switch (dt) {
+    case SPARC_R64: return update_batched_t<double>(ctx, maxp, tab, off, n, total, a_dev);
+    case SPARC_R32: return update_batched_t<float>(ctx, maxp, tab, off, n, total, a_dev);
+    case SPARC_C128: return update_batched_t<cd>(ctx, maxp, tab, off, n, total, a_dev);
+    case SPARC_C64: return update_batched_t<cf>(ctx, maxp, tab, off, n, total, a_dev);
+  }
+  return fail(SPARC_EINVAL, "batched projector update: bad dtype");
+}
+
+template <typename E>
+static int scatter_batched_t(sparc_ctx* ctx, int nb, const NlBatchArgs* tab, const int* off, int n, int64_t total,
                              const double* a_dev) {
   if (total <= 0) return SPARC_OK;
   if (total > INT32_MAX) return fail(SPARC_ESHAPE, "batched scatter: too many work-groups");
   int t = timer_begin(ctx, "nl_scatter");
-  nl_scatter_batched_kernel<E, kScatterNB><<<(unsigned)total, 256, 0, ctx->stream>>>(tab, off, n, a_dev);
+  if (nb == kScatterNB)
+    nl_scatter_batched_kernel<E, kScatterNB><<<(unsigned)total, 256, 0, ctx->stream>>>(tab, off, n, a_dev);
+  else
+    nl_scatter_batched_kernel<E, kSharedNB><<<(unsigned)total, 256, 0, ctx->stream>>>(tab, off, n, a_dev);
   timer_end(ctx, t);
   return check_launch("nl_scatter_batched_kernel");
 }
 
-int nl_scatter_batched(sparc_ctx* ctx, sparc_dtype dt, const NlBatchArgs* tab, const int* off, int n, int64_t total,
-                       const double* a_dev) {
+int nl_scatter_batched(sparc_ctx* ctx, sparc_dtype dt, int nb, const NlBatchArgs* tab, const int* off, int n,
+                       int64_t total, const double* a_dev) {
   switch (dt) {
-    case SPARC_R64: return scatter_batched_t<double>(ctx, tab, off, n, total, a_dev);
-    case SPARC_R32: return scatter_batched_t<float>(ctx, tab, off, n, total, a_dev);
-    case SPARC_C128: return scatter_batched_t<cd>(ctx, tab, off, n, total, a_dev);
-    case SPARC_C64: return scatter_batched_t<cf>(ctx, tab, off, n, total, a_dev);
+    case SPARC_R64: return scatter_batched_t<double>(ctx, nb, tab, off, n, total, a_dev);
+    case SPARC_R32: return scatter_batched_t<float>(ctx, nb, tab, off, n, total, a_dev);
+    case SPARC_C128: return scatter_batched_t<cd>(ctx, nb, tab, off, n, total, a_dev);
+    case SPARC_C64: return scatter_batched_t<cf>(ctx, nb, tab, off, n, total, a_dev);
   }
   return fail(SPARC_EINVAL, "batched scatter: bad dtype");
 }
@@ -577,6 +749,57 @@ int nl_scatter(sparc_ham* H, const void* alpha, int32_t n_s, double a, const dou
     case SPARC_C64: return nl_scatter_t<cf>(H, alpha, n_s, a, a_dev, out, ldo);
   }
   return fail(SPARC_EINVAL, "nl_scatter: bad dtype");
+}
+
+// Scatter and the next step's gather as one pass (nl_update_kernel) after the scatter over the
+// shared nodes.  The form moves no more bytes however many nodes are shared.  It is taken where
+// (atom, 4 orbitals) pairs give every CU two work-groups; below that the calls are a few
+// microseconds each and its longer chain (load, update, store, sum) shows.  A degree-20 filter,
+// kernels apart against this: 48^3, 16 atoms, FP64, 64 states 1.06 and 1.09 ms, 128 states 1.78
+// and 1.72; complex 64 states 2.05 and 2.08, 128 states 4.04 and 3.92; 32^3, 8 atoms, 64 states
+// 0.47 and 0.50; 40^3 with 64 overlapping atoms, 128 states 2.38 and 2.29.
+bool nl_update_applies(const sparc_ham* H) {
+  return H->n_proj > 0 && H->n_nlpts > 0 && !H->nl_fused && H->max_proj_per_atom <= 4;
+}
+int64_t nl_update_pairs(const sparc_ham* H, int32_t n_s) { return (int64_t)H->n_atoms_nl * ((n_s + 3) / 4); }
+
+template <typename E, int MAXP, int NB>
+static void nl_update_launch(sparc_ham* H, void* alpha, int32_t n_s, double a, void* out, int64_t ldo) {
+  typedef typename elem<E>::real R;
+  dim3 grid(H->n_atoms_nl, (n_s + NB - 1) / NB);
+  nl_update_kernel<E, MAXP, NB><<<grid, 256, 0, H->ctx->stream>>>(
+      (E*)out, ldo, n_s, (R)a, H->sup_ptr, H->sup_mark, H->atom_pbeg, H->proj_voff, (const E*)H->pval,
+      (const R*)H->gamma_d, H->dV, (E*)alpha, alpha_ld(n_s));
+}
+
+template <typename E>
+static int nl_update_t(sparc_ham* H, void* alpha, int32_t n_s, double a, void* out, int64_t ldo) {
+  typedef typename elem<E>::real R;
+  if (H->n_shared > 0) {
+    int t = timer_begin(H->ctx, "nl_scatter");
+    dim3 grid((unsigned)((n_s + kSharedNB - 1) / kSharedNB), (unsigned)((H->n_shared + 255) / 256));
+    nl_scatter_kernel<E, kSharedNB><<<grid, 256, 0, H->ctx->stream>>>(
+        (int)H->n_shared, H->sh_pts, H->sh_ptr, H->sh_proj, (const E*)H->sh_coef, (const E*)alpha, alpha_ld(n_s), n_s,
+        (R)a, nullptr, (E*)out, ldo);
+    timer_end(H->ctx, t);
+    SPARC_TRY(check_launch("nl_scatter_kernel"));
+  }
+  int t = timer_begin(H->ctx, "nl_update");
+  if (H->max_proj_per_atom <= 1) nl_update_launch<E, 1, update_nb<E>()>(H, alpha, n_s, a, out, ldo);
+  else nl_update_launch<E, 4, update_nb<E>()>(H, alpha, n_s, a, out, ldo);
+  timer_end(H->ctx, t);
+  return check_launch("nl_update_kernel");
+}
+
+int nl_update(sparc_ham* H, void* alpha, int32_t n_s, double a, void* out, int64_t ldo) {
+  if ((H->n_shared + 255) / 256 > 65535) return fail(SPARC_ESHAPE, "nl_update: too many projector nodes");
+  switch (H->dtype) {
+    case SPARC_R64: return nl_update_t<double>(H, alpha, n_s, a, out, ldo);
+    case SPARC_R32: return nl_update_t<float>(H, alpha, n_s, a, out, ldo);
+    case SPARC_C128: return nl_update_t<cd>(H, alpha, n_s, a, out, ldo);
+    case SPARC_C64: return nl_update_t<cf>(H, alpha, n_s, a, out, ldo);
+  }
+  return fail(SPARC_EINVAL, "nl_update: bad dtype");
 }
 
 // ------------------------------------------------------------ small launches

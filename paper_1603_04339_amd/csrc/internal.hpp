@@ -147,6 +147,12 @@ struct sparc_ham {
   double gtap[3][8];    // FD gradient weights w~_p / h_s per direction, p = 1..n_o
   bool nl_fused;        // the stencil step applies the projectors (tables built)
   NlTileTable nlt[kNlTileShapes];
+  int32_t* sup_mark;    // [n_sup] sup_idx, as ~g for nodes in several supports
+  int64_t n_shared;     // nodes in several supports
+  int32_t* sh_pts;      // their nodes, CSR, projectors and coefficients, as nl_pts .. ent_coef
+  int32_t* sh_ptr;
+  int32_t* sh_proj;
+  void* sh_coef;
 };
 
 namespace sparc {
@@ -191,6 +197,11 @@ int check_block(const sparc_ham* H, const void* X, int64_t ldx, int32_t n_s, con
 int noalloc_scratch_init(int device);
 //   out += a * V_nl-scatter(alpha); a from a device scalar when a_dev != nullptr
 int nl_scatter(sparc_ham* H, const void* alpha, int32_t n_s, double a, const double* a_dev, void* out, int64_t ldo);
+//   out += a * V_nl-scatter(alpha), then alpha = the projections of out; whether the form
+//   applies, and the (atom, 4 orbitals) pairs that decide whether it pays
+bool nl_update_applies(const sparc_ham* H);
+int64_t nl_update_pairs(const sparc_ham* H, int32_t n_s);
+int nl_update(sparc_ham* H, void* alpha, int32_t n_s, double a, void* out, int64_t ldo);
 int heuristic_tile(int n1, int n2, size_t elem_size);
 // Conjugate gradients on A = a (-1/2 Lap_h) + b (FP64, one orbital) in two launches per
 // iteration, for grids whose stencil step runs in point form (cg_point_form).  In the
@@ -234,15 +245,23 @@ struct NlBatchArgs {
   const void* pval;
   double dV;
   void* alpha;
-  const int32_t *pts, *ptr, *ent_proj;
-  const void* ent_coef;
+  const int32_t *pts, *ptr, *ent_proj;   // update launch: pts = sup_mark
+  const void* ent_coef;                  // update launch: gamma per projector
 };
+constexpr int kScatterNB = 16;  // orbitals per thread of a batched scatter, and over shared nodes
+constexpr int kSharedNB = 4;
 //   argument block of one problem; *gather_wg / *scatter_wg: its work-groups in each launch
 void nl_batch_args(const sparc_ham* H, const void* x, int64_t ldx, void* y, int64_t ldy, int n_s, void* alpha,
-                   int slot, NlBatchArgs* out, int* gather_wg, int* scatter_wg);
+                   int slot, int snb, NlBatchArgs* out, int* gather_wg, int* scatter_wg);
+//   the block of an update launch over y (returns its work-groups), and the scatter block o
+//   cut down to the shared nodes (returns its work-groups)
+int nl_update_args(const sparc_ham* H, void* y, int64_t ldy, int n_s, void* alpha, int slot, NlBatchArgs* o);
+int nl_shared_args(const sparc_ham* H, int nb, NlBatchArgs* o);
+int nl_update_batched(sparc_ctx* ctx, sparc_dtype dt, int maxp, const NlBatchArgs* dev_tab, const int* dev_off,
+                      int n, int64_t total, const double* a_dev);
 int nl_gather_batched(sparc_ctx* ctx, sparc_dtype dt, int maxp, const NlBatchArgs* dev_tab, const int* dev_off,
                       int n, int64_t total);
-int nl_scatter_batched(sparc_ctx* ctx, sparc_dtype dt, const NlBatchArgs* dev_tab, const int* dev_off, int n,
+int nl_scatter_batched(sparc_ctx* ctx, sparc_dtype dt, int nb, const NlBatchArgs* dev_tab, const int* dev_off, int n,
                        int64_t total, const double* a_dev);
 // non-local scatter inside the stencil step (hamiltonian.hip): per tile shape tables
 // from the node-major entries (nodes ascending, entries of node i in [ptr[i], ptr[i+1]),

@@ -498,15 +498,37 @@ int sparc_ham_create(sparc_ctx* ctx, const sparc_grid* grid, const sparc_atoms* 
           cim[e] = T.vim[vi];
         }
   }
+  // nodes in the supports of several atoms, and their entries
+  std::vector<int32_t> sup_mark(T.sup_idx), sh_pts, sh_ptr, sh_proj;
+  std::vector<double> shre, shim;
+  {
+    std::vector<char> times(nd, 0);
+    for (int32_t g : T.sup_idx) times[g] = (char)std::min(2, times[g] + 1);
+    for (int32_t& g : sup_mark)
+      if (times[g] > 1) g = ~g;
+    for (size_t i = 0; i < nl_pts.size(); ++i) {
+      if (times[nl_pts[i]] < 2) continue;
+      sh_pts.push_back(nl_pts[i]);
+      sh_ptr.push_back((int32_t)sh_proj.size());
+      for (int32_t e = nl_ptr[i]; e < nl_ptr[i + 1]; ++e) {
+        sh_proj.push_back(ent_proj[e]);
+        shre.push_back(ere[e]);
+        shim.push_back(eim[e]);
+      }
+    }
+    sh_ptr.push_back((int32_t)sh_proj.size());
+    H->n_shared = (int64_t)sh_pts.size();
+  }
   // the projector scatter inside the stencil step, on request (SPARC_NL_FUSED=1): the
   // separate projection and scatter kernels are the default, as fast or faster on the
   // measured cells (FP64 within 2 %, FP32 and complex slower fused)
   const char* fenv = getenv("SPARC_NL_FUSED");
   const bool fuse = fenv && fenv[0] == '1';
   H->nl_fused = H->n_proj > 0 && H->max_proj_per_atom <= 4 && fuse;
-  std::vector<char> pv, ec, gm;
+  std::vector<char> pv, ec, gm, sc;
   pack(dtype, T.vre, T.vim, pv);
   pack(dtype, ere, eim, ec);
+  pack(dtype, shre, shim, sc);
   std::vector<double> zeros(T.gamma.size(), 0.0);
   pack(dtype_single(dtype) ? SPARC_R32 : SPARC_R64, T.gamma, zeros, gm);
   if ((rc = upload(T.sup_ptr, &H->sup_ptr)) || (rc = upload(T.sup_idx, &H->sup_idx)) ||
@@ -514,7 +536,9 @@ int sparc_ham_create(sparc_ctx* ctx, const sparc_grid* grid, const sparc_atoms* 
       (rc = upload(T.atom_pbeg, &H->atom_pbeg)) || (rc = upload(T.proj_voff, &H->proj_voff)) ||
       (rc = upload(pv, (char**)&H->pval)) || (rc = upload(gm, (char**)&H->gamma_d)) ||
       (rc = upload(nl_pts, &H->nl_pts)) || (rc = upload(nl_ptr, &H->nl_ptr)) || (rc = upload(ent_proj, &H->ent_proj)) ||
-      (rc = upload(ec, (char**)&H->ent_coef))) {
+      (rc = upload(ec, (char**)&H->ent_coef)) || (rc = upload(sup_mark, &H->sup_mark)) ||
+      (rc = upload(sh_pts, &H->sh_pts)) || (rc = upload(sh_ptr, &H->sh_ptr)) ||
+      (rc = upload(sh_proj, &H->sh_proj)) || (rc = upload(sc, (char**)&H->sh_coef))) {
     sparc_ham_destroy(H);
     return rc;
   }
@@ -535,7 +559,7 @@ void sparc_ham_destroy(sparc_ham* H) {
   if (!H) return;
   void* ptrs[] = {H->vloc, H->veff, H->veff32, H->sup_ptr, H->sup_idx, H->atom_pbeg, H->proj_voff,
                   H->pval, H->gamma_d, H->nl_pts, H->nl_ptr, H->ent_proj, H->ent_coef,
-                  H->atom_R, H->atom_D, H->atom_W, H->force_part, H->nl_atom, H->zplane};
+                  H->sup_mark, H->sh_pts, H->sh_ptr, H->sh_proj, H->sh_coef, H->atom_R, H->atom_D, H->atom_W, H->force_part, H->nl_atom, H->zplane};
   for (void* p : ptrs)
     if (p) hipFree(p);
   nl_tables_free(H);
