@@ -1147,9 +1147,14 @@ static int ham_step_t(sparc_ham* H, const void* x, int64_t ldx, const void* z, i
   const void* al = nonlocal ? alpha : nullptr;
   if (row_form(H)) {
     // too few work-groups for a quarter of the CUs (one orbital of a small grid: a step takes
-    // 7 us in either form) leave the point form below
+    // 7 us in either form) leave the point form below.  FP32 rows of 41 to 47 odd nodes, moved
+    // in chunks of one float, stay tiled on a full chip where 48 x 8 tiles cover the plane with
+    // less than an eighth to spare (43 x 47 x 41, 82 orbitals: tiled 32, rows 34 us; 47 x 44^2,
+    // 200: 73 and 88; 43 x 44^2, a seventh to spare: 34 and 29; with 30 orbitals 22 and 17)
     const RowPlan& p = row_single_plan(H, n_s);
-    if (p.cfg.vx && p.wg(n_s) >= H->ctx->n_cu / 4) {
+    const bool tile48 = p.cfg.vx * sizeof(R) == 4 && A.n1 > 40 && A.n1 < 48 && A.n2 <= 64 &&
+                        8 * A.n1 * A.n2 > 7 * 48 * ((A.n2 + 7) / 8 * 8) && (double)H->n_d * n_s > 5e6;
+    if (p.cfg.vx && !tile48 && p.wg(n_s) >= H->ctx->n_cu / 4) {
       row_fill(A, p, n_s);
       SPARC_TRY(hrow_single<E>(H->ctx, A, p.cfg, p.wg(n_s)));
       if (nonlocal) SPARC_TRY(nl_scatter(H, alpha, n_s, a, nullptr, out, ldo));

@@ -127,7 +127,10 @@ struct RowPlan {
 // steps, a step taking the longer of its latency, 1.3 us + 0.3 ns per 16 bytes of the tile,
 // and the CU's rate, k times (1.9 ns per 16 bytes of the tile, 2.7 in chunks narrower than
 // that, + 0.43 ns per 16 bytes of its y halo; complex double, whose x taps read a chunk each,
-// 2.4 and 1.1); more than four waves that do not fill the four SIMDs evenly cost 12 %.  Fitted
+// 2.4 and 1.1); more than four waves that do not fill the four SIMDs evenly cost 12 %.  Chunks
+// of one float hold half the registers of the others, so four waves fit a SIMD instead of
+// three, and a step's latency is 1.7 us (55 blocks with rows of 21 to 91 nodes: the choice costs
+// 0.6 % on average, with the other chunks' numbers 10 %).  Fitted
 // to 1200 timed (tile, chunk) pairs of 41 blocks, 24^3 x 1 to 96^3 x 192 in all four types,
 // over which the choice costs 3 % on average against the fastest pair (80^3 x 60 complex64 at
 // worst, 233 against 174 us; tiled form 241).
@@ -140,7 +143,7 @@ inline RowPlan row_plan(int n1, int n2, int n3, int cp, int rb, int vx, int vy, 
   const int hc = (kRowNO * cp + vx - 1) / vx;
   const int px = txt + 2 * hc;
   const size_t cb = (size_t)vx * rb;
-  const bool c128 = cp == 2 && rb == 8;
+  const bool c128 = cp == 2 && rb == 8, single = cb == 4;
   const double rate = c128 ? 2.4e-3 : (cb < 16 ? 2.7e-3 : 1.9e-3), halo_rate = c128 ? 1.1e-3 : 0.43e-3;
   double best_cost = 1e300;
   int last = 0;
@@ -155,7 +158,7 @@ inline RowPlan row_plan(int n1, int n2, int n3, int cp, int rb, int vx, int vy, 
     if (hm > 2) break;   // lower tiles need more
     const size_t lds = (size_t)(2 * (ty + 2 * kRowNO) * px + 1) * cb;
     if (lds > kRowLds) continue;
-    const int64_t occ = std::max(1, std::min<int>(12 / (nt / 64), (int)(kRowLds / lds)));
+    const int64_t occ = std::max(1, std::min<int>((single ? 16 : 12) / (nt / 64), (int)(kRowLds / lds)));
     const double chunks = (double)nt * vy * (double)cb / 16.0, halo = 2.0 * kRowNO * txt * (double)cb / 16.0;
     const double uneven = nt > 256 && nt % 256 ? 1.12 : 1.0;
     for (int nz = 1; nz == 1 || n3 / nz >= 3; ++nz) {
@@ -163,7 +166,7 @@ inline RowPlan row_plan(int n1, int n2, int n3, int cp, int rb, int vx, int vy, 
       const int64_t wg = (int64_t)tl * nzr * n_s;
       const int64_t k = std::max<int64_t>(1, std::min<int64_t>(occ, (wg + n_cu - 1) / n_cu));
       const double r = (double)wg / ((double)n_cu * k);
-      const double step = uneven * std::max(1.3 + 0.3e-3 * chunks, k * (rate * chunks + halo_rate * halo));
+      const double step = uneven * std::max((single ? 1.7 : 1.3) + 0.3e-3 * chunks, k * (rate * chunks + halo_rate * halo));
       const double rounds = shared ? std::max(1.0, r) + 0.7 : (r < 6 ? std::ceil(r) : r + 0.5);
       const double dur = (zc + 1) * step, cost = 2.0 + rounds * dur;
       if (cost < best_cost * 0.999) {
