@@ -477,7 +477,10 @@ int rayleigh_ritz_batched(sparc_ctx* ctx, int32_t n_prob, sparc_ham* const* H, v
                           size_t work_bytes) {
   if (!ctx || !H || !X || !ldx || !n_s || !ritz_dev) return fail(SPARC_EINVAL, "rayleigh_ritz_batched: null argument");
   if (n_prob < 1) return fail(SPARC_EINVAL, "rayleigh_ritz_batched: n_prob < 1");
+  std::vector<char> done(n_prob, 0);
+  SPARC_TRY(rr_concurrent(ctx, n_prob, H, X, ldx, n_s, mode, ritz_dev, work, work_bytes, done));
   for (int p = 0; p < n_prob; ++p) {
+    if (done[p]) continue;
     if (!H[p] || H[p]->ctx != ctx) return fail(SPARC_EINVAL, "rayleigh_ritz_batched: problem %d has no/another context", p);
     int32_t info = 0;
     SPARC_TRY(rayleigh_ritz(H[p], X[p], ldx[p], n_s[p], mode, ritz_dev[p], work, work_bytes, &info));

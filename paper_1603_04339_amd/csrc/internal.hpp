@@ -4,6 +4,7 @@
 
 #include <cstdint>
 #include <cstdio>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -72,6 +73,12 @@ struct sparc_ctx {
   };
   std::vector<TimeRec> recs;
   std::vector<hipEvent_t> pool;
+  // streams beside `stream` for the small dense kernels of batched Rayleigh-Ritz (made on
+  // first use), and an event per problem; the lock's holder uses them, another thread of the
+  // same context works on `stream` alone meanwhile
+  std::mutex side_lock;
+  std::vector<hipStream_t> side;
+  std::vector<hipEvent_t> side_ev;
 };
 
 // bit s set: zero Dirichlet conditions along direction s
@@ -202,6 +209,11 @@ int nl_scatter(sparc_ham* H, const void* alpha, int32_t n_s, double a, const dou
 bool nl_update_applies(const sparc_ham* H);
 int64_t nl_update_pairs(const sparc_ham* H, int32_t n_s);
 int nl_update(sparc_ham* H, void* alpha, int32_t n_s, double a, void* out, int64_t ldo);
+// Rayleigh-Ritz of several problems with their dense parts on the context's side streams
+// (api.hip): the problems taken on are marked in done, the others are left untouched
+int rr_concurrent(sparc_ctx* ctx, int32_t n_prob, sparc_ham* const* H, void* const* X, const int64_t* ldx,
+                  const int32_t* n_s, sparc_gemm_mode mode, double* const* ritz, void* work, size_t work_bytes,
+                  std::vector<char>& done);
 int heuristic_tile(int n1, int n2, size_t elem_size);
 // Conjugate gradients on A = a (-1/2 Lap_h) + b (FP64, one orbital) in two launches per
 // iteration, for grids whose stencil step runs in point form (cg_point_form).  In the

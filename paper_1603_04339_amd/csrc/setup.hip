@@ -319,6 +319,11 @@ void sparc_ctx_destroy(sparc_ctx* ctx) {
   hipStreamSynchronize(ctx->stream);
   drop_records(ctx);
   for (hipEvent_t e : ctx->pool) hipEventDestroy(e);
+  for (hipStream_t t : ctx->side) {
+    hipStreamSynchronize(t);
+    hipStreamDestroy(t);
+  }
+  for (hipEvent_t e : ctx->side_ev) hipEventDestroy(e);
   if (ctx->scalars) hipFree(ctx->scalars);
   delete ctx;
 }
