@@ -376,10 +376,11 @@ struct Poisson {
   int last_iters = 0;  // iterations of the previous solve: the next one is checked from 3/4 of it
 
   double shift = 0.0;  // k^2 of the Helmholtz form (-Lap_h + k^2); 0: Poisson
-  // two-launch iterations (cg_iterate) on grids whose stencil step runs in point form:
-  // w = A r and s = A p, the scalar ring and its partial sums
+  // one-launch iterations (cg_iterate) on grids whose stencil step runs in point form:
+  // w = A r and s = A p, the scalar ring and its partial sums, and the second copies
   bool fused = false;
   double *w = nullptr, *sv = nullptr, *cs = nullptr, *cpart = nullptr;
+  double *rn = nullptr, *wn = nullptr, *sn = nullptr;
 
   int apply(const double* x, double* y) {
     // -Lap_h x + shift x = 2 * (-1/2 Lap_h x) + shift x: stencil only
@@ -447,10 +448,10 @@ struct Poisson {
     return check_launch("poisson");
   }
 
-  // The same iteration in two launches per step (cg_iterate): r = b - A v, w = A r and
+  // The same iteration in one launch per step (cg_iterate): r = b - A v, w = A r and
   // their dot products start it; p and s start at zero.
   int cg_fused(hipStream_t s, double* v, double tol, int max_it, bool zero_mean) {
-    CgIter C{r, w, sv, p, v, cs, cpart, cg_blocks(H), 0};
+    CgIter C{r, w, sv, p, v, cs, cpart, cg_blocks(H), 0, rn, wn, sn, cpart + 2 * kCgBlocks};
     SPARC_TRY(reduce(s, n, b, b, RED_DOT, part, sc + 4));
     SPARC_TRY(apply(v, r));
     residual_kernel<<<GRID1(n)>>>(n, b, r);
@@ -467,7 +468,6 @@ struct Poisson {
     if (rr <= tol * tol * bb) return finish(s, v, -1, max_it, zero_mean);
     int it = 0;
     for (; it < max_it; ++it) {
-      C.it = it;
       SPARC_TRY(cg_iterate(H, 2.0, shift, C));
       if (it % 8 == 7 && it >= (3 * last_iters) / 4 - 8) {
         SPARC_TRY(cg_residual_norm(H, C));
@@ -668,7 +668,10 @@ extern "C" int sparc_scf_run(sparc_ctx* ctx, const sparc_grid* grid, const sparc
     SPARC_TRY(B.alloc(&PS.w, n));
     SPARC_TRY(B.alloc(&PS.sv, n));
     SPARC_TRY(B.alloc(&PS.cs, 12));
-    SPARC_TRY(B.alloc(&PS.cpart, 2 * kCgBlocks));
+    SPARC_TRY(B.alloc(&PS.cpart, 4 * kCgBlocks));
+    SPARC_TRY(B.alloc(&PS.rn, n));
+    SPARC_TRY(B.alloc(&PS.wn, n));
+    SPARC_TRY(B.alloc(&PS.sn, n));
   }
   const double ptol = P->poisson_tol > 0 ? P->poisson_tol : 1e-10;
   // phi (or V_H) of the current input density, warm-started from the previous one; the
