@@ -19,15 +19,17 @@
 //             Orbitals with zero occupation are skipped.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "devmath.hpp"
 
 namespace sparc {
 
 // ---------------------------------------------------------------- block reduction
-// sum of three per-thread values over a 256-thread work-group (fixed order)
+// sum of three per-thread values over a work-group of NW waves (fixed order)
+template <int NW>
 __device__ __forceinline__ void block_sum3(double v[3], double* out) {
-  __shared__ double red[3][4];
+  __shared__ double red[3][NW];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
@@ -37,7 +39,10 @@ __device__ __forceinline__ void block_sum3(double v[3], double* out) {
   __syncthreads();
   if (threadIdx.x < 3) {
     const int d = threadIdx.x;
-    out[d] = ((red[d][0] + red[d][1]) + red[d][2]) + red[d][3];
+    double s = red[d][0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) s += red[d][w];
+    out[d] = s;
   }
 }
 
@@ -47,6 +52,10 @@ __device__ __forceinline__ int64_t floordiv_l(int64_t a, int64_t b) {
 }
 
 // ---------------------------------------------------------------- local component
+// Bound by issue: a node costs an exp and its index arithmetic, which runs in 32 bits from the
+// box's first node (box coordinates advance by the work-group's size, their images are taken
+// modulo the grid).  64^3, 32 atoms: 27 us, with 64-bit divisions for every node and 8
+// chunks an atom 131.
 __global__ __launch_bounds__(256) void force_local_kernel(int n1, int n2, int n3, double h1, double h2, double h3,
                                                           int dmask, const double* __restrict__ R,
                                                           const double* __restrict__ D,
@@ -68,20 +77,39 @@ __global__ __launch_bounds__(256) void force_local_kernel(int n1, int n2, int n3
   // this chunk's z planes
   const int64_t zc = (nz + gridDim.y - 1) / gridDim.y;
   const int64_t kb = k0 + chunk * zc, ke = std::min(k1 + 1, kb + zc);
-  const int64_t total = (ke > kb) ? nx * ny * (ke - kb) : 0;
   double f[3] = {0.0, 0.0, 0.0};
-  for (int64_t q = threadIdx.x; q < total; q += blockDim.x) {
-    const int64_t i = i0 + q % nx, j = j0 + (q / nx) % ny, k = kb + q / (nx * ny);
-    const double dx = i * h1 - Rx, dy = j * h2 - Ry, dz = k * h3 - Rz;
-    const double r2 = dx * dx + dy * dy + dz * dz;
-    if (r2 > rc * rc) continue;
-    const int64_t gi = i - floordiv_l(i, n1) * n1, gj = j - floordiv_l(j, n2) * n2, gk = k - floordiv_l(k, n3) * n3;
-    const double s = rho[gi + n1 * (gj + (int64_t)n2 * gk)] * amp * exp(-r2 * inv2w2);
-    f[0] = fma(s, dx, f[0]);
-    f[1] = fma(s, dy, f[1]);
-    f[2] = fma(s, dz, f[2]);
+  if (ke > kb && nx > 0 && ny > 0) {
+    const unsigned ux = (unsigned)nx, uy = (unsigned)ny, planes = (unsigned)(ke - kb);
+    // images of the box's first node
+    const unsigned gi0 = (unsigned)(i0 - floordiv_l(i0, n1) * n1), gj0 = (unsigned)(j0 - floordiv_l(j0, n2) * n2),
+                   gk0 = (unsigned)(kb - floordiv_l(kb, n3) * n3);
+    // node threadIdx.x of the box, and the step to the thread's next one
+    unsigned i = threadIdx.x % ux, j = threadIdx.x / ux % uy, k = threadIdx.x / ux / uy;
+    const unsigned di = 256u % ux, dj = 256u / ux % uy, dk = 256u / ux / uy;
+    while (k < planes) {
+      const double dx = (i0 + i) * h1 - Rx, dy = (j0 + j) * h2 - Ry, dz = (kb + k) * h3 - Rz;
+      const double r2 = dx * dx + dy * dy + dz * dz;
+      if (r2 <= rc * rc) {
+        const unsigned gi = (gi0 + i) % (unsigned)n1, gj = (gj0 + j) % (unsigned)n2, gk = (gk0 + k) % (unsigned)n3;
+        const double s = rho[gi + n1 * (gj + (int64_t)n2 * gk)] * amp * exp(-r2 * inv2w2);
+        f[0] = fma(s, dx, f[0]);
+        f[1] = fma(s, dy, f[1]);
+        f[2] = fma(s, dz, f[2]);
+      }
+      i += di;
+      j += dj;
+      k += dk;
+      if (i >= ux) {
+        i -= ux;
+        ++j;
+      }
+      if (j >= uy) {
+        j -= uy;
+        ++k;
+      }
+    }
   }
-  block_sum3(f, part + ((int64_t)J * gridDim.y + chunk) * 3);
+  block_sum3<4>(f, part + ((int64_t)J * gridDim.y + chunk) * 3);
 }
 
 __global__ void force_local_reduce(int n_atoms, int n_chunks, double dV, const double* __restrict__ part,
@@ -123,8 +151,14 @@ __device__ __forceinline__ float cj(float a) { return a; }
 __device__ __forceinline__ cd cj(cd a) { return {a.re, -a.im}; }
 __device__ __forceinline__ cf cj(cf a) { return {a.re, -a.im}; }
 
-template <typename E, int MAXP, int NB>
-__global__ __launch_bounds__(256) void force_nl_kernel(const E* __restrict__ x, int64_t ldx, int n_s,
+constexpr int kForceThreads = 512;
+
+// NO > 0: the stencil half-width, on grids without Dirichlet faces and with at least NO nodes
+// per direction: the taps' offsets and images are made once per node, and all taps of an
+// orbital are in flight together.  NO = 0: any.  Bound by the cache's rate for scattered
+// doubles.  64^3, 32 atoms, 128 states: 98 us, in the general form 304.
+template <typename E, int MAXP, int NB, int NO>
+__global__ __launch_bounds__(kForceThreads) void force_nl_kernel(const E* __restrict__ x, int64_t ldx, int n_s,
                                                        const int32_t* __restrict__ sup_ptr,
                                                        const int32_t* __restrict__ sup_idx,
                                                        const int32_t* __restrict__ atom_pbeg,
@@ -145,6 +179,16 @@ __global__ __launch_bounds__(256) void force_nl_kernel(const E* __restrict__ x, 
   // occupations and projections of this block (uniform over the work-group)
   double on[NB];
   bool any = false;
+  E rot_p[3], rot_m[3];   // e^{+-i k_s L_s} (NO > 0)
+  if constexpr (NO > 0 && elem<E>::is_cplx) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      double s, c;
+      sincos(G.kl[d], &s, &c);
+      rot_p[d] = {(R)c, (R)s};
+      rot_m[d] = {(R)c, (R)-s};
+    }
+  }
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
     on[j] = (nb0 + j < n_s) ? occ[nb0 + j] : 0.0;
@@ -184,23 +228,56 @@ __global__ __launch_bounds__(256) void force_nl_kernel(const E* __restrict__ x, 
         const int pos = (d == 0) ? i : (d == 1) ? jy : k;
         const int nn = (d == 0) ? n1 : (d == 1) ? n2 : n3;
         const int64_t stride = (d == 0) ? 1 : (d == 1) ? n1 : plane;
-        const int64_t base = g - (int64_t)pos * stride;
-        for (int p = 1; p <= G.no; ++p) {
-          const int ip = pos + p, im = pos - p;
-          const int wp = floordiv_i(ip, nn), wm = floordiv_i(im, nn);
-          const int64_t op = base + (int64_t)(ip - wp * nn) * stride, om = base + (int64_t)(im - wm * nn) * stride;
-          const R wt = (R)G.w[d][p - 1];
-          // zero Dirichlet conditions: values past the face are zero
-          const bool zp = ((G.dmask >> d) & 1) && wp != 0, zm = ((G.dmask >> d) & 1) && wm != 0;
+        if constexpr (NO > 0) {
+          int op[NO], om[NO];
+          bool wp[NO], wm[NO];
+#pragma unroll
+          for (int p = 1; p <= NO; ++p) {
+            wp[p - 1] = pos + p >= nn;
+            wm[p - 1] = pos - p < 0;
+            op[p - 1] = (int)(g + (p - (wp[p - 1] ? nn : 0)) * stride);
+            om[p - 1] = (int)(g + ((wm[p - 1] ? nn : 0) - p) * stride);
+          }
 #pragma unroll
           for (int j = 0; j < NB; ++j) {
             if (on[j] != 0.0) {
               const E* xn = x + (int64_t)(nb0 + j) * ldx;
-              E vp = bloch_load(xn, op, wp, G.kl[d]);
-              E vm = bloch_load(xn, om, wm, G.kl[d]);
-              if (zp) vp = zero<E>();
-              if (zm) vm = zero<E>();
-              gs[j] = fmar(gs[j], wt, vp - vm);
+              E vp[NO], vm[NO];
+#pragma unroll
+              for (int p = 0; p < NO; ++p) {
+                vp[p] = xn[op[p]];
+                vm[p] = xn[om[p]];
+              }
+#pragma unroll
+              for (int p = 0; p < NO; ++p) {
+                if constexpr (elem<E>::is_cplx) {
+                  const E rp = rot(vp[p], rot_p[d].re, rot_p[d].im), rm = rot(vm[p], rot_m[d].re, rot_m[d].im);
+                  vp[p] = wp[p] ? rp : vp[p];
+                  vm[p] = wm[p] ? rm : vm[p];
+                }
+                gs[j] = fmar(gs[j], (R)G.w[d][p], vp[p] - vm[p]);
+              }
+            }
+          }
+        } else {
+          const int64_t base = g - (int64_t)pos * stride;
+          for (int p = 1; p <= G.no; ++p) {
+            const int ip = pos + p, im = pos - p;
+            const int wp = floordiv_i(ip, nn), wm = floordiv_i(im, nn);
+            const int64_t op = base + (int64_t)(ip - wp * nn) * stride, om = base + (int64_t)(im - wm * nn) * stride;
+            const R wt = (R)G.w[d][p - 1];
+            // zero Dirichlet conditions: values past the face are zero
+            const bool zp = ((G.dmask >> d) & 1) && wp != 0, zm = ((G.dmask >> d) & 1) && wm != 0;
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+              if (on[j] != 0.0) {
+                const E* xn = x + (int64_t)(nb0 + j) * ldx;
+                E vp = bloch_load(xn, op, wp, G.kl[d]);
+                E vm = bloch_load(xn, om, wm, G.kl[d]);
+                if (zp) vp = zero<E>();
+                if (zm) vm = zero<E>();
+                gs[j] = fmar(gs[j], wt, vp - vm);
+              }
             }
           }
         }
@@ -210,7 +287,7 @@ __global__ __launch_bounds__(256) void force_nl_kernel(const E* __restrict__ x, 
       }
     }
   }
-  block_sum3(f, part + ((int64_t)a * gridDim.y + blockIdx.y) * 3);
+  block_sum3<kForceThreads / 64>(f, part + ((int64_t)a * gridDim.y + blockIdx.y) * 3);
 }
 
 __global__ void force_nl_reduce(int n_atoms_nl, int n_blk, const double* __restrict__ part,
@@ -249,18 +326,23 @@ static int force_nl_t(sparc_ham* H, const void* X, int64_t ldx, int32_t n_s, con
   if (nblk > 65535) return fail(SPARC_ESHAPE, "sparc_forces_nonlocal: n_s=%d too large", n_s);
   dim3 grid(H->n_atoms_nl, nblk);
   typedef typename elem<E>::real R;
-  if (H->max_proj_per_atom <= 1)
-    force_nl_kernel<E, 1, kForceNB><<<grid, 256, 0, st>>>((const E*)X, ldx, n_s, H->sup_ptr, H->sup_idx,
-                                                          H->atom_pbeg, H->proj_voff, (const E*)H->pval,
-                                                          (const R*)H->gamma_d, (const E*)alpha, alpha_ld(n_s), occ,
-                                                          G, part);
-  else if (H->max_proj_per_atom <= 4)
-    force_nl_kernel<E, 4, kForceNB><<<grid, 256, 0, st>>>((const E*)X, ldx, n_s, H->sup_ptr, H->sup_idx,
-                                                          H->atom_pbeg, H->proj_voff, (const E*)H->pval,
-                                                          (const R*)H->gamma_d, (const E*)alpha, alpha_ld(n_s), occ,
-                                                          G, part);
-  else
+  auto launch = [&](auto maxp, auto no) {
+    force_nl_kernel<E, decltype(maxp)::value, kForceNB, decltype(no)::value><<<grid, kForceThreads, 0, st>>>(
+        (const E*)X, ldx, n_s, H->sup_ptr, H->sup_idx, H->atom_pbeg, H->proj_voff, (const E*)H->pval,
+        (const R*)H->gamma_d, (const E*)alpha, alpha_ld(n_s), occ, G, part);
+  };
+  typedef std::integral_constant<int, 0> general;
+  typedef std::integral_constant<int, 6> sixth;
+  const bool six = G.no == 6 && G.dmask == 0 && std::min(G.n1, std::min(G.n2, G.n3)) >= 6;
+  if (H->max_proj_per_atom <= 1) {
+    if (six) launch(std::integral_constant<int, 1>(), sixth());
+    else launch(std::integral_constant<int, 1>(), general());
+  } else if (H->max_proj_per_atom <= 4) {
+    if (six) launch(std::integral_constant<int, 4>(), sixth());
+    else launch(std::integral_constant<int, 4>(), general());
+  } else {
     return fail(SPARC_EINVAL, "sparc_forces_nonlocal: more than 4 projector functions on one atom");
+  }
   SPARC_TRY(check_launch("force_nl_kernel"));
   const int nq = 3 * H->n_atoms_nl;
   force_nl_reduce<<<(nq + 255) / 256, 256, 0, st>>>(H->n_atoms_nl, nblk, part, H->nl_atom, F);

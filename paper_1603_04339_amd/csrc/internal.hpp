@@ -85,7 +85,7 @@ struct sparc_ctx {
 inline int dirichlet_mask(const sparc_grid& g) { return (g.bc[0] == 1 ? 1 : 0) | (g.bc[1] == 1 ? 2 : 0) | (g.bc[2] == 1 ? 4 : 0); }
 
 // z-chunks of the local-force box per atom (partial sums reduced in a fixed order)
-constexpr int kForceChunks = 8;
+constexpr int kForceChunks = 32;
 
 // Tables of the non-local scatter applied inside the stencil step: the step adds
 // V_nl x to its output at the nodes with projector support, from entry lists per
