@@ -1157,6 +1157,28 @@ static bool row_form(const sparc_ham* H) {
 
 static int real_bytes(const sparc_ham* H) { return dtype_single(H->dtype) ? 4 : 8; }
 
+// Where the tiled form is faster than plan p for n_s orbitals on a full chip.  FP32 rows of 41
+// to 47 nodes, moved in chunks of one or two floats, where 48 x 8 tiles cover the plane with
+// less than an eighth (a tenth) to spare (43 x 47 x 41, 82 orbitals: tiled 32, rows 34 us; 47 x
+// 44^2, 200: 73 and 88; 43 x 44^2, a seventh to spare: 34 and 29; with 30 orbitals 22 and 17;
+// 46^2 x 45, 150, two floats: 8 % apart, 46 x 44^2, an eighth to spare, 5 % the other way).
+// Complex double rows of 57 to 64 nodes that no tile of full lanes fits, where 64 x 8 tiles
+// spare at most a quarter (58 x 53^2, 178 orbitals: tiled 492, rows 611 us; 60 x 56^2 523 and
+// 650; 54 x 53^2, whose rows leave a higher tile, 479 and 366; 64 x 60^2, full lanes, 623 and
+// 595).
+static bool row_tiled_better(const sparc_ham* H, const RowPlan& p, int64_t n_s) {
+  const sparc_grid& g = H->grid;
+  const int64_t n1 = g.n[0], n2 = g.n[1], rows8 = (n2 + 7) / 8 * 8;
+  if ((double)H->n_d * (double)n_s <= 5e6) return false;
+  if (H->dtype == SPARC_R32 && p.cfg.vx < 4) {
+    const int64_t part = p.cfg.vx == 1 ? 8 : 10;
+    return n1 > 40 && n1 < 48 && n2 <= 64 && part * n1 * n2 > (part - 1) * 48 * rows8;
+  }
+  if (H->dtype == SPARC_C128)
+    return p.cfg.hm == 2 && !p.cfg.full && n1 > 56 && n1 <= 64 && 4 * n1 * n2 > 3 * 64 * rows8;
+  return false;
+}
+
 // plan of a single problem; the search is remembered per thread by the sizes it depends on
 static const RowPlan& row_single_plan(const sparc_ham* H, int32_t n_s) {
   struct Entry {
@@ -1224,7 +1246,14 @@ bool row_batch_plan(sparc_ham* const* H, const int* n_s, int n, std::vector<RowP
   out->assign(n, RowPlan());
   for (const auto& g : group)
     if (!row_group_plan(H, n_s, g.second.second, g.first, g.second.first, *out)) return false;
-  return true;
+  // the largest problem decides for the plan
+  int big = 0;
+  int64_t total = 0;
+  for (int p = 0; p < n; ++p) {
+    if ((double)H[p]->n_d * n_s[p] > (double)H[big]->n_d * n_s[big]) big = p;
+    total += n_s[p];
+  }
+  return !row_tiled_better(H[big], (*out)[big], total);
 }
 
 template <typename E>
@@ -1264,14 +1293,9 @@ static int ham_step_t(sparc_ham* H, const void* x, int64_t ldx, const void* z, i
   const void* al = nonlocal ? alpha : nullptr;
   if (row_form(H)) {
     // too few work-groups for a quarter of the CUs (one orbital of a small grid: a step takes
-    // 7 us in either form) leave the point form below.  FP32 rows of 41 to 47 odd nodes, moved
-    // in chunks of one float, stay tiled on a full chip where 48 x 8 tiles cover the plane with
-    // less than an eighth to spare (43 x 47 x 41, 82 orbitals: tiled 32, rows 34 us; 47 x 44^2,
-    // 200: 73 and 88; 43 x 44^2, a seventh to spare: 34 and 29; with 30 orbitals 22 and 17)
+    // 7 us in either form) leave the point form below
     const RowPlan& p = row_single_plan(H, n_s);
-    const bool tile48 = p.cfg.vx * sizeof(R) == 4 && A.n1 > 40 && A.n1 < 48 && A.n2 <= 64 &&
-                        8 * A.n1 * A.n2 > 7 * 48 * ((A.n2 + 7) / 8 * 8) && (double)H->n_d * n_s > 5e6;
-    if (p.cfg.vx && !tile48 && p.wg(n_s) >= H->ctx->n_cu / 4) {
+    if (p.cfg.vx && !row_tiled_better(H, p, n_s) && p.wg(n_s) >= H->ctx->n_cu / 4) {
       row_fill(A, p, n_s);
       SPARC_TRY(hrow_single<E>(H->ctx, A, p.cfg, p.wg(n_s)));
       if (nonlocal) SPARC_TRY(nl_scatter(H, alpha, n_s, a, nullptr, out, ldo));

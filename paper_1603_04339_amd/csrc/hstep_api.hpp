@@ -160,7 +160,9 @@ inline RowPlan row_plan(int n1, int n2, int n3, int cp, int rb, int vx, int vy, 
     if (lds > kRowLds) continue;
     const int64_t occ = std::max(1, std::min<int>((single ? 16 : 12) / (nt / 64), (int)(kRowLds / lds)));
     const double chunks = (double)nt * vy * (double)cb / 16.0, halo = 2.0 * kRowNO * txt * (double)cb / 16.0;
-    const double uneven = nt > 256 && nt % 256 ? 1.12 : 1.0;
+    const bool full = n2 % ty == 0 && txt * tyt == nt;
+    // (the complex double form with masked lanes and two halo chunks a thread spills)
+    const double uneven = (nt > 256 && nt % 256 ? 1.12 : 1.0) * (c128 && hm == 2 && !full ? 1.2 : 1.0);
     for (int nz = 1; nz == 1 || n3 / nz >= 3; ++nz) {
       const int zc = (n3 + nz - 1) / nz, nzr = (n3 + zc - 1) / zc;
       const int64_t wg = (int64_t)tl * nzr * n_s;
@@ -171,7 +173,7 @@ inline RowPlan row_plan(int n1, int n2, int n3, int cp, int rb, int vx, int vy, 
       const double dur = (zc + 1) * step, cost = 2.0 + rounds * dur;
       if (cost < best_cost * 0.999) {
         best_cost = cost;
-        best.cfg = RowCfg{vx, vy, hm, (n2 % ty == 0 && txt * tyt == nt) ? 1 : 0, nt, lds};
+        best.cfg = RowCfg{vx, vy, hm, full ? 1 : 0, nt, lds};
         best.txt = txt;
         best.tyt = tyt;
         best.px = px;

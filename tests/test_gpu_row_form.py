@@ -1,8 +1,8 @@
 """Row form of the stencil step against the oracle: H X and the in-place recurrence at the
 edges of its tiles (rows that no 16-byte chunk divides, tiles with rows past the grid,
 lanes past the tile, the smallest grid it takes, rows wide enough for two halo chunks per
-thread, odd FP32 rows that stay tiled), block pointers off 16-byte alignment, leading
-dimensions above N_d, complex Bloch phases on every face, and several problems of different
+thread, FP32 and complex double rows that stay tiled), block pointers off 16-byte alignment,
+leading dimensions above N_d, complex Bloch phases on every face, and several problems of different
 sizes and chunk widths in one plan.
 Tolerances: the ones of the tiled form (1e-12 of a column's norm in FP64 for H X, 1e-10
 through a filter, 2e-5 / 2e-4 in FP32)."""
@@ -20,7 +20,8 @@ from tests.helpers import oracle_setup, colnorm_err, to_dev, block_to_oracle
 pytestmark = pytest.mark.gpu
 
 GRIDS = [((16, 16, 16), 24), ((24, 20, 18), 24), ((17, 19, 23), 20), ((45, 38, 17), 16), ((18, 50, 16), 16),
-         ((96, 33, 16), 8), ((130, 18, 16), 6), ((20, 16, 40), 1), ((43, 48, 16), 160)]
+         ((96, 33, 16), 8), ((130, 18, 16), 6), ((20, 16, 40), 1), ((43, 48, 16), 160),
+         ((58, 53, 17), 100)]
 TYPES = {"r64": (sp.R64, torch.float64, 1e-12, 1e-10), "r32": (sp.R32, torch.float32, 2e-5, 2e-4),
          "c128": (sp.C128, torch.complex128, 1e-12, 1e-10), "c64": (sp.C64, torch.complex64, 2e-5, 2e-4)}
 
