@@ -28,19 +28,22 @@ __device__ __forceinline__ void nl_scatter_body(int i, int nb0, int n_pts, const
   if (i >= n_pts) return;
   const int64_t g = pts[i];
   const int e0 = ptr[i], ne = ptr[i + 1] - e0;
+  // the values to add to are on their way while the entries are read (40^3, 31 atoms, 56
+  // states: 10.6 us with the loads after them, 9.6 so; 96^3's shared nodes 101 and 80)
+  E yv[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+    if (nb0 + j < n_s) yv[j] = y[g + (int64_t)(nb0 + j) * ldy];
   E acc[NB];
 #pragma unroll
   for (int j = 0; j < NB; ++j) acc[j] = zero<E>();
+#pragma unroll 2
   for (int u = 0; u < ne; ++u) {
     const E c = ent_coef[e0 + u];
     const E* __restrict__ ap = alpha + (int64_t)ent_proj[e0 + u] * lda + nb0;
 #pragma unroll
     for (int j = 0; j < NB; ++j) acc[j] = fmae(acc[j], c, ap[j]);
   }
-  E yv[NB];
-#pragma unroll
-  for (int j = 0; j < NB; ++j)
-    if (nb0 + j < n_s) yv[j] = y[g + (int64_t)(nb0 + j) * ldy];
 #pragma unroll
   for (int j = 0; j < NB; ++j)
     if (nb0 + j < n_s) y[g + (int64_t)(nb0 + j) * ldy] = fmar(yv[j], a, acc[j]);
@@ -83,8 +86,8 @@ __global__ __launch_bounds__(256) void nl_scatter_batched_kernel(const NlBatchAr
                          (typename elem<E>::real)a_dev[P.slot], (E*)P.y, P.ldy);
 }
 
-// the projections of one work-group's sums: wave butterflies, then across the 4 waves
-// through LDS
+// the projections of one work-group's sums: over each wave in registers, then across the 4
+// waves through LDS
 template <typename E, int MAXP, int NB>
 __device__ __forceinline__ void nl_store_projections(const E (&acc)[MAXP][NB], int pb, int np, int nb0, int n_s,
                                                      double dV, E* __restrict__ alpha, int lda) {
@@ -99,7 +102,7 @@ __device__ __forceinline__ void nl_store_projections(const E (&acc)[MAXP][NB], i
       const R* comp = (const R*)&acc[p][j];
 #pragma unroll
       for (int c = 0; c < NV; ++c) {
-        R s = wave_sum(comp[c]);
+        R s = wave_sum_dpp(comp[c]);
         if (lane == 0) red[wv][(p * NB + j) * NV + c] = s;
       }
     }
@@ -133,20 +136,31 @@ __device__ __forceinline__ void nl_gather_body(int a, int nb0, const E* __restri
   int64_t voff[MAXP];
 #pragma unroll
   for (int p = 0; p < MAXP; ++p) voff[p] = (p < np) ? proj_voff[pb + p] : 0;
+  // U support nodes of a thread are loaded together: with few orbitals per work-group the wait
+  // for index and value is what the kernel spends its time on, and the sums at the end (24^3,
+  // 8 atoms, 32 states: 4.5 us one node at a time, 3.7 so, 3.6 with sums in registers instead
+  // of LDS permutes; 40^3, 31 atoms, 56 states: 8.3, 8.0 and 7.5; 64^3 with 4 projectors an
+  // atom, 128 states: 29, 27 and 23)
+  constexpr int U = NB <= 2 ? 4 : 1;
 #pragma unroll 2
-  for (int t = t0 + (int)threadIdx.x; t < t1; t += blockDim.x) {
-    const int64_t g = sup_idx[t];
-    E chi[MAXP];
+  for (int tb = t0 + (int)threadIdx.x; tb < t1; tb += U * 256) {
+    E chi[U][MAXP], xv[U][NB];
 #pragma unroll
-    for (int p = 0; p < MAXP; ++p) chi[p] = (p < np) ? pval[voff[p] + (t - t0)] : zero<E>();
+    for (int u = 0; u < U; ++u) {
+      const bool on = U == 1 || tb + u * 256 < t1;
+      const int t = on ? tb + u * 256 : tb;
+      const int64_t g = sup_idx[t];
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      if (nb0 + j < n_s) {
-        E xv = x[g + (int64_t)(nb0 + j) * ldx];
+      for (int p = 0; p < MAXP; ++p) chi[u][p] = (on && p < np) ? pval[voff[p] + (t - t0)] : zero<E>();
 #pragma unroll
-        for (int p = 0; p < MAXP; ++p) acc[p][j] = fmac(acc[p][j], chi[p], xv);
-      }
+      for (int j = 0; j < NB; ++j) xv[u][j] = (on && nb0 + j < n_s) ? x[g + (int64_t)(nb0 + j) * ldx] : zero<E>();
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int p = 0; p < MAXP; ++p) acc[p][j] = fmac(acc[p][j], chi[u][p], xv[u][j]);
   }
   nl_store_projections<E, MAXP, NB>(acc, pb, np, nb0, n_s, dV, alpha, lda);
 }
@@ -193,7 +207,7 @@ __device__ __forceinline__ float uniform_real(float v) {
 // has added all of theirs before, over the list of shared nodes alone, and here they are only
 // read.  An atom's coefficients are read and replaced by its own work-group.  Bound by memory, by
 // the 128-byte lines of the supports: apart, the two kernels read them twice.  96^3, 64 atoms, 512
-// states, FP64: scatter 621 and gather 375 us, here shared scatter 101 and update 662 (8 orbitals
+// states, FP64: scatter 621 and gather 375 us, here shared scatter 80 and update 662 (8 orbitals
 // per thread 714, 4 with non-temporal loads slower still); 24 FP64 filter steps 77.4 -> 74.2 ms.
 template <typename E, int MAXP, int NB>
 __device__ __forceinline__ void nl_update_body(int a, int nb0, E* __restrict__ y, int64_t ldy, int n_s,
