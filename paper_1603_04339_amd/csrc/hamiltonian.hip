@@ -913,6 +913,34 @@ __device__ __forceinline__ void cg_sums(const CgIter& C, double& g, double& d) {
   d = red[1][0] + red[1][1] + red[1][2] + red[1][3];
 }
 
+// node-wise part of iteration it: the step scalars, then p = r + beta p, s = w + beta s,
+// x += alpha p, r -= alpha s
+__global__ __launch_bounds__(256) void cg_update_kernel(int64_t nd, CgIter C) {
+  double g, d;
+  cg_sums(C, g, d);
+  double beta = 0.0, alpha = g / d;
+  if (C.it > 0) {
+    const double* pv = C.sc + 4 * ((C.it + 1) % 2);
+    beta = g / pv[0];
+    alpha = g / (d - beta * g / pv[2]);
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    double* cv = C.sc + 4 * (C.it % 2);
+    cv[0] = g;
+    cv[1] = d;
+    cv[2] = alpha;
+  }
+  const int64_t t = blockIdx.x * (int64_t)256 + threadIdx.x;
+  if (t >= nd) return;
+  const double rt = C.r[t];
+  const double pn = fma(beta, C.p[t], rt);
+  const double sn = fma(beta, C.s[t], C.w[t]);
+  C.p[t] = pn;
+  C.s[t] = sn;
+  C.x[t] = fma(alpha, pn, C.x[t]);
+  C.r[t] = fma(-alpha, sn, rt);
+}
+
 // r.r of the current residual into sc[8] (for the convergence test)
 __global__ __launch_bounds__(256) void cg_norm_kernel(CgIter C) {
   double g, d;
@@ -957,16 +985,17 @@ __global__ __launch_bounds__(256) void cg_apply_kernel(StepArgs<double> A, CgIte
 
 // One iteration: the step scalars, then node by node s = w + beta s, r -= alpha s, p = r + beta p
 // (the old r), x += alpha p, and w = A r with the block partials of the new r.r and w.r.
-// A work-group takes tiles of 8 x 8 x 4 nodes, a node per thread.  Every thread also makes the
-// new r of one halo node per stencil distance (2 x 32 in x and in y, 2 x 64 in z: 256 at each
-// distance), and the taps are read from LDS, where a line along each direction is contiguous;
-// r, w and s are written to second arrays, since neighbours read the first.  Bound by latency:
-// the loads go out before the partial sums are added up, and each XCD takes neighbouring tiles,
-// whose halos its L2 holds (40^3: 7.6 us, with tiles dealt out in turn 8.9).  Before, the update
-// and A r were two launches of 3.5 and 7.7 us; a 4-step SCF of 96^3 with 12 states 88 -> 69 ms.
-constexpr int kCgX = 8, kCgY = 8, kCgZ = 4;
+// Every thread makes the new r of its node and of the node's y and z taps from the old arrays
+// (all of whose loads go out before the partial sums are added up), and the x taps are read from
+// LDS, where the work-group has the new r of the grid rows that its 256 nodes lie in.  r, w and s
+// are written to second arrays, since neighbours read the first.  Nodes are dealt to blocks as
+// in cg_apply_kernel, so the sums, and with them the iterates, are the same bit by bit as with
+// update and A r in two launches.  Bound by latency; each XCD takes neighbouring blocks, whose
+// taps its L2 holds.  40^3: 7.6 us, update and A r 3.5 and 7.7.  Past 2^19 nodes reading three
+// arrays around every node costs more than the second launch: an SCF of four steps with 12 states
+// at 64^3 28.5 ms in two launches and 26.8 in one, 80^3 50 and 46, 96^3 87 and 91.
+constexpr int64_t kCgStepNodes = int64_t(1) << 19;
 
-// periodic image of coordinate c, at most n below and (n >= 16) less than n past the end
 __device__ __forceinline__ int wrap_index(int c, int n) {
   if (n < 16) return c - floordiv_i(c, n) * n;
   c = c < 0 ? c + n : c;
@@ -974,17 +1003,12 @@ __device__ __forceinline__ int wrap_index(int c, int n) {
 }
 
 template <int NO>
-__global__ __launch_bounds__(256) void cg_step_kernel(StepArgs<double> A, CgIter C, int nx, int ny, int tiles) {
-  constexpr int SX = (kCgX + 2 * NO + 7) / 16 * 16 + 8;   // x lines a quarter of the banks apart
-  __shared__ double ldx[SX * 32], ldy[(kCgY + 2 * NO) * 32], ldz[(kCgZ + 2 * NO) * 64];
+__global__ __launch_bounds__(256) void cg_step_kernel(StepArgs<double> A, CgIter C) {
+  extern __shared__ double rows[];   // [256 + 2 n1]
   __shared__ double red[2][4];
-  const int t = threadIdx.x, lx = t & 7, ly = (t >> 3) & 7, lz = t >> 6;
-  // this thread's halo line: direction, side, the two coordinates along the face
-  const int dir = t < 64 ? 0 : (t < 128 ? 1 : 2);
-  const int side = dir == 2 ? (t - 128) >> 6 : (t >> 5) & 1;
-  const int fi = t & 7, fj = dir == 2 ? (t >> 3) & 7 : (t >> 3) & 3;
-  const int hn = dir == 0 ? A.n1 : (dir == 1 ? A.n2 : A.n3);
-  const int hs = dir == 0 ? 1 : (dir == 1 ? A.n1 : A.n1 * A.n2);
+  const int t = threadIdx.x, n1 = A.n1, n2 = A.n2, n3 = A.n3, plane = n1 * n2, nd = plane * n3;
+  const int G = gridDim.x, q8 = G >> 3, r8 = G & 7, xcd = blockIdx.x & 7;
+  const int block = xcd * q8 + (xcd < r8 ? xcd : r8) + (blockIdx.x >> 3);
   double g = 0.0, d = 0.0;
   for (int i = t; i < C.nparts; i += 256) {
     g += C.part[i];
@@ -993,62 +1017,59 @@ __global__ __launch_bounds__(256) void cg_step_kernel(StepArgs<double> A, CgIter
   const double* pv = C.sc + 4 * ((C.it + 1) % 2);
   const double g_prev = pv[0], a_prev = pv[2];
   double beta = 0.0, alpha = 0.0, a = 0.0, b = 0.0;
-  for (int it = blockIdx.x; it < tiles; it += gridDim.x) {
-    // neighbouring tiles on one XCD
-    const int rem = tiles & 7, xcd = it & 7, tile = xcd * (tiles >> 3) + (xcd < rem ? xcd : rem) + (it >> 3);
-    const int x0 = (tile % nx) * kCgX, y0 = (tile / nx % ny) * kCgY, z0 = tile / (nx * ny) * kCgZ;
-    double rv[NO + 1], wv[NO + 1], sv[NO + 1];
-    const bool in = x0 + lx < A.n1 && y0 + ly < A.n2 && z0 + lz < A.n3;
-    const int own = wrap_index(x0 + lx, A.n1) +
-                    A.n1 * (wrap_index(y0 + ly, A.n2) + A.n2 * wrap_index(z0 + lz, A.n3));
-    rv[0] = C.r[own];
-    wv[0] = C.w[own];
-    sv[0] = C.s[own];
-    const int line = (dir == 0 ? 0 : wrap_index(x0 + fi, A.n1)) +
-                     A.n1 * ((dir == 1 ? 0 : wrap_index(y0 + (dir == 0 ? fi : fj), A.n2)) +
-                             A.n2 * (dir == 2 ? 0 : wrap_index(z0 + fj, A.n3)));
-    const int h0 = dir == 0 ? x0 : (dir == 1 ? y0 : z0), hT = dir == 2 ? kCgZ : kCgX;
+  bool first = true;
+  for (int64_t base = block * (int64_t)256; base < nd; base += G * (int64_t)256) {
+    const int b0 = (int)base, b1 = min(b0 + 256, nd);
+    const bool in = b0 + t < nd;
+    const int own = min(b0 + t, nd - 1);
+    const int i = own % n1, j = own / n1 % n2, k = own / plane;
+    double rv[4 * NO + 1], wv[4 * NO + 1], sv[4 * NO + 1];
+    auto fetch = [&](int u, int at) {
+      rv[u] = C.r[at];
+      wv[u] = C.w[at];
+      sv[u] = C.s[at];
+    };
+    fetch(0, own);
 #pragma unroll
     for (int q = 1; q <= NO; ++q) {
-      const int h = line + hs * wrap_index(h0 + (side ? hT - 1 + q : -q), hn);
-      rv[q] = C.r[h];
-      wv[q] = C.w[h];
-      sv[q] = C.s[h];
+      fetch(4 * q - 3, own + (wrap_index(k + q, n3) - k) * plane);
+      fetch(4 * q - 2, own + (wrap_index(k - q, n3) - k) * plane);
+      fetch(4 * q - 1, own + (wrap_index(j + q, n2) - j) * n1);
+      fetch(4 * q, own + (wrap_index(j - q, n2) - j) * n1);
     }
     const double po = C.p[own], xo = C.x[own];
-    if (it == (int)blockIdx.x) {
+    if (first) {
       g = wave_sum_dpp(g);
       d = wave_sum_dpp(d);
       if ((t & 63) == 0) {
         red[0][t >> 6] = g;
         red[1][t >> 6] = d;
       }
-      __syncthreads();
+    }
+    __syncthreads();   // also: the last block's x taps have been read
+    if (first) {
       g = red[0][0] + red[0][1] + red[0][2] + red[0][3];
       d = red[1][0] + red[1][1] + red[1][2] + red[1][3];
       beta = C.it > 0 ? g / g_prev : 0.0;
       alpha = C.it > 0 ? g / (d - beta * g / a_prev) : g / d;
-      if (blockIdx.x == 0 && t == 0) {
+      if (block == 0 && t == 0) {
         double* cv = C.sc + 4 * (C.it % 2);
         cv[0] = g;
         cv[1] = d;
         cv[2] = alpha;
       }
-    } else {
-      __syncthreads();   // the last tile's taps have been read
+      first = false;
+    }
+    // the rest of the first and last row: nodes [row0, b0) and [b1, row1)
+    const int row0 = b0 / n1 * n1, row1 = ((b1 - 1) / n1 + 1) * n1, lead = b0 - row0, extra = lead + row1 - b1;
+    for (int e = t; e < extra; e += 256) {
+      const int at = e < lead ? row0 + e : b1 + (e - lead);
+      rows[at - row0] = fma(-alpha, fma(beta, C.s[at], C.w[at]), C.r[at]);
     }
     const double sn = fma(beta, sv[0], wv[0]), r0 = fma(-alpha, sn, rv[0]);
-    ldx[(lz * 8 + ly) * SX + NO + lx] = r0;
-    ldy[(NO + ly) * 32 + lz * 8 + lx] = r0;
-    ldz[(NO + lz) * 64 + ly * 8 + lx] = r0;
+    if (in) rows[own - row0] = r0;
 #pragma unroll
-    for (int q = 1; q <= NO; ++q) {
-      const double h = fma(-alpha, fma(beta, sv[q], wv[q]), rv[q]);
-      const int pos = side ? NO + (dir == 2 ? kCgZ : kCgX) - 1 + q : NO - q;
-      if (dir == 0) ldx[(fj * 8 + fi) * SX + pos] = h;
-      else if (dir == 1) ldy[pos * 32 + fj * 8 + fi] = h;
-      else ldz[pos * 64 + fj * 8 + fi] = h;
-    }
+    for (int u = 1; u <= 4 * NO; ++u) rv[u] = fma(-alpha, fma(beta, sv[u], wv[u]), rv[u]);
     __syncthreads();
     if (in) {
       const double pn = fma(beta, po, rv[0]);
@@ -1056,15 +1077,13 @@ __global__ __launch_bounds__(256) void cg_step_kernel(StepArgs<double> A, CgIter
       C.x[own] = fma(alpha, pn, xo);
       C.sn[own] = sn;
       C.rn[own] = r0;
-      const double* cx = ldx + (lz * 8 + ly) * SX + NO + lx;
-      const double* cy = ldy + (NO + ly) * 32 + lz * 8 + lx;
-      const double* cz = ldz + (NO + lz) * 64 + ly * 8 + lx;
+      const double* cx = rows + (own - i - row0);
       double lap = A.centre * r0;
 #pragma unroll
       for (int q = 1; q <= NO; ++q) {
-        lap = fmar(lap, A.tz[q - 1], cz[q * 64] + cz[-q * 64]);
-        lap = fmar(lap, A.tx[q - 1], cx[q] + cx[-q]);
-        lap = fmar(lap, A.ty[q - 1], cy[q * 32] + cy[-q * 32]);
+        lap = fmar(lap, A.tz[q - 1], rv[4 * q - 3] + rv[4 * q - 2]);
+        lap = fmar(lap, A.tx[q - 1], cx[wrap_index(i + q, n1)] + cx[wrap_index(i - q, n1)]);
+        lap = fmar(lap, A.ty[q - 1], rv[4 * q - 1] + rv[4 * q]);
       }
       const double w0 = fmar(lap, A.vb, r0);
       C.wn[own] = w0;
@@ -1072,17 +1091,17 @@ __global__ __launch_bounds__(256) void cg_step_kernel(StepArgs<double> A, CgIter
       b = fma(w0, r0, b);
     }
   }
-  __syncthreads();   // red is read above
   a = wave_sum_dpp(a);
   b = wave_sum_dpp(b);
+  __syncthreads();   // red is read above
   if ((t & 63) == 0) {
     red[0][t >> 6] = a;
     red[1][t >> 6] = b;
   }
   __syncthreads();
   if (t == 0) {
-    C.partn[blockIdx.x] = red[0][0] + red[0][1] + red[0][2] + red[0][3];
-    C.partn[kCgBlocks + blockIdx.x] = red[1][0] + red[1][1] + red[1][2] + red[1][3];
+    C.partn[block] = red[0][0] + red[0][1] + red[0][2] + red[0][3];
+    C.partn[kCgBlocks + block] = red[1][0] + red[1][1] + red[1][2] + red[1][3];
   }
 }
 
@@ -1102,7 +1121,8 @@ static StepArgs<double> cg_args(const sparc_ham* H, double a, double b) {
 }
 
 bool cg_point_form(sparc_ham* H) {
-  if (H->dtype != SPARC_R64 || dirichlet_mask(H->grid) != 0) return false;
+  // periodic grids whose rows fit the iteration's LDS
+  if (H->dtype != SPARC_R64 || dirichlet_mask(H->grid) != 0 || H->grid.n[0] > 2048) return false;
   StepArgs<double> A = cg_args(H, 1.0, 0.0);
   return use_point_form<double>(H, A, 1, heuristic_tile(A.n1, A.n2, sizeof(double)));
 }
@@ -1130,12 +1150,18 @@ int cg_apply(sparc_ham* H, double a, double b, const CgIter& C) {
 int cg_iterate(sparc_ham* H, double a, double b, CgIter& C) {
   if (H->dtype != SPARC_R64) return fail(SPARC_EINVAL, "cg_iterate: FP64 operator only");
   const StepArgs<double> A = cg_args(H, a, b);
-  const int nx = (A.n1 + kCgX - 1) / kCgX, ny = (A.n2 + kCgY - 1) / kCgY, nz = (A.n3 + kCgZ - 1) / kCgZ;
-  const int64_t tiles = (int64_t)nx * ny * nz;
-  if (tiles * (kCgX * kCgY * kCgZ) > (int64_t)INT32_MAX) return fail(SPARC_ESHAPE, "cg_iterate: grid too large");
-  const unsigned blocks = (unsigned)std::min<int64_t>(kCgBlocks, tiles);
+  const unsigned blocks = (unsigned)cg_blocks(H);
+  const int64_t nd = (int64_t)A.n1 * A.n2 * A.n3;
+  if (nd > kCgStepNodes) {
+    if ((nd + 255) / 256 > (int64_t)INT32_MAX) return fail(SPARC_ESHAPE, "cg_iterate: grid too large");
+    cg_update_kernel<<<(unsigned)((nd + 255) / 256), 256, 0, H->ctx->stream>>>(nd, C);
+    SPARC_TRY(check_launch("cg_update_kernel"));
+    C.it++;
+    return cg_apply(H, a, b, C);
+  }
+  const size_t lds = (256 + 2 * (size_t)A.n1) * sizeof(double);
   switch (H->grid.n_o) {
-#define CASE(K) case K: cg_step_kernel<K><<<blocks, 256, 0, H->ctx->stream>>>(A, C, nx, ny, (int)tiles); break;
+#define CASE(K) case K: cg_step_kernel<K><<<blocks, 256, lds, H->ctx->stream>>>(A, C); break;
     CASE(1) CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8)
 #undef CASE
     default: return fail(SPARC_EINVAL, "cg_iterate: n_o=%d unsupported", H->grid.n_o);
@@ -1145,7 +1171,6 @@ int cg_iterate(sparc_ham* H, double a, double b, CgIter& C) {
   std::swap(C.w, C.wn);
   std::swap(C.s, C.sn);
   std::swap(C.part, C.partn);
-  C.nparts = (int)blocks;
   C.it++;
   return SPARC_OK;
 }

@@ -215,7 +215,7 @@ int rr_concurrent(sparc_ctx* ctx, int32_t n_prob, sparc_ham* const* H, void* con
                   const int32_t* n_s, sparc_gemm_mode mode, double* const* ritz, void* work, size_t work_bytes,
                   std::vector<char>& done);
 int heuristic_tile(int n1, int n2, size_t elem_size);
-// Conjugate gradients on A = a (-1/2 Lap_h) + b (FP64, one orbital) in one launch per
+// Conjugate gradients on A = a (-1/2 Lap_h) + b (FP64, one orbital), one launch per
 // iteration, for grids whose stencil step runs in point form (cg_point_form).  In the
 // Chronopoulos-Gear arrangement, which needs one reduction phase per iteration: from
 // g = r.r, d = w.r (w = A r) of the current residual and g, alpha of the previous
@@ -223,11 +223,12 @@ int heuristic_tile(int n1, int n2, size_t elem_size);
 // alpha = g / (d - beta g / alpha_prev) (g / d on the first); then, node by node,
 //   p = r + beta p,  s = w + beta s,  x += alpha p,  r -= alpha s,
 // and w = A r with the block partials of the new g and d.  p and x are updated in place; r, w,
-// s (= A p) and the partials go to rn, wn, sn and partn, and cg_iterate swaps each pair.
-// part, partn: 2 * kCgBlocks doubles of block partials (nparts of them used); sc: two slots of
-// four doubles (g, d, alpha, unused) written by iteration it into slot it % 2, and sc[8] for
-// cg_residual_norm.  The first iteration (it = 0) needs r, w = cg_apply(r) (which leaves its
-// partials, nparts = cg_blocks()) and p = s = 0.
+// s (= A p) and the partials go to rn, wn, sn and partn, and cg_iterate swaps each pair (large
+// grids take two launches, in place).
+// part, partn: 2 * kCgBlocks doubles of block partials (nparts = cg_blocks() of them used); sc:
+// two slots of four doubles (g, d, alpha, unused) written by iteration it into slot it % 2, and
+// sc[8] for cg_residual_norm.  The first iteration (it = 0) needs r, w = cg_apply(r) (which
+// leaves its partials) and p = s = 0.
 constexpr int kCgBlocks = 1024;
 struct CgIter {
   double* r;

@@ -1,9 +1,10 @@
-"""The one-launch conjugate-gradient iteration at the edges of its 8 x 8 x 4 tiles: grids they
-divide, tiles with one node in a direction, directions shorter than a tile and its halo, every
-stencil half-width the halo can have, and more tiles than work-groups.  The SCF is stopped by a
-loose density tolerance in its first iteration, whose Poisson solve runs to a relative residual
-of 1e-4; the residual of the returned potential, taken with the oracle's symbol of the operator,
-may exceed that by the rounding of the recurrence only (1e-4 of it)."""
+"""The one-launch conjugate-gradient iteration at its edges: grids that blocks of 256 nodes divide
+and do not, blocks that end inside a row and rows longer than a block, directions shorter than
+the stencil's reach, every stencil half-width, more blocks than work-groups, and the two-launch
+form above.  The SCF is stopped by a loose density tolerance in its first iteration, whose
+Poisson solve runs to a relative residual of 1e-4; the residual of the returned potential,
+taken with the oracle's symbol of the operator, may exceed that by the rounding of the
+recurrence only (1e-4 of it)."""
 import numpy as np
 import pytest
 
@@ -28,7 +29,8 @@ def ctx():
 
 @pytest.mark.parametrize("n,n_o", [((16, 16, 16), 6), ((17, 25, 21), 6), ((13, 14, 15), 6), ((31, 20, 18), 5),
                                    ((18, 17, 19), 8), ((24, 9, 33), 4), ((12, 11, 10), 3), ((9, 10, 7), 2),
-                                   ((10, 33, 6), 1), ((20, 19, 17), 7), ((66, 68, 70), 6)])
+                                   ((10, 33, 6), 1), ((20, 19, 17), 7), ((300, 9, 8), 4),
+                                   ((66, 68, 70), 6), ((82, 80, 81), 6)])
 def test_potential_residual(ctx, n, n_o):
     ns = 6
     cell, rng = wl.draw_cell(98, sum(n), n, tuple(0.5 * v for v in n), 2, (0,), 1.5, ns)
