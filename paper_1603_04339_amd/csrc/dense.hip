@@ -97,11 +97,17 @@ __global__ __launch_bounds__(256) void chol_scale_kernel(int n, const T* __restr
   }
 }
 
-// factor the diagonal block S[k0:k0+kb, k0:k0+kb] in LDS; also R11^{-1} -> Rinv (kb x kb).
-// Right-looking elimination on unscaled rows: step k subtracts conj(a_ki) a_kj / a_kk from
-// the trailing block, so row k (final after step k - 1) is only read during the step and
-// one barrier per step suffices; the rows are scaled by 1 / sqrt(a_kk) at the end.  The
-// inverse of the triangular factor is formed by 16 x 16 blocks.
+// element of lane l (uniform) in every lane
+__device__ __forceinline__ double lane_of(double v, int l) { return readlane_f64(v, l); }
+__device__ __forceinline__ cd lane_of(cd v, int l) { return {readlane_f64(v.re, l), readlane_f64(v.im, l)}; }
+
+// factor the diagonal block S[k0:k0+kb, k0:k0+kb]; also R11^{-1} -> Rinv (kb x kb).
+// Right-looking elimination on unscaled rows, the block in registers: lane j of every wave has
+// column j, wave g the rows g mod 4.  Step k subtracts conj(a_ki) a_kj / a_kk from the trailing
+// block: row k goes through LDS to every wave, a_ki by lane reads, one barrier a step (two row
+// buffers); the rows are scaled by 1 / sqrt(a_kk) at the end.  Bound by that chain: 56 columns
+// 46 us real, with the block in LDS 57; 64 complex 73 and 88.  The inverse of the
+// triangular factor is formed by 16 x 16 blocks.
 template <typename T>
 __global__ __launch_bounds__(256) void chol_diag_kernel(int n, T* __restrict__ S, int k0, int kb,
                                                         T* __restrict__ Rinv, int* info) {
@@ -109,7 +115,8 @@ __global__ __launch_bounds__(256) void chol_diag_kernel(int n, T* __restrict__ S
   __shared__ T a[CB * LD];
   __shared__ T r[CB * LD];
   __shared__ T tmp[3 * 16 * 16];  // sums of the off-diagonal 16-blocks of the inverse
-  __shared__ double dg[CB];
+  __shared__ double dg[CB], dinv[CB];
+  __shared__ T row[2][CB];
   if (*info != 0) return;
   const int tid = threadIdx.x;
   for (int idx = tid; idx < kb * kb; idx += blockDim.x) {
@@ -117,40 +124,47 @@ __global__ __launch_bounds__(256) void chol_diag_kernel(int n, T* __restrict__ S
     a[i + j * LD] = (i <= j) ? S[(k0 + i) + (int64_t)(k0 + j) * n] : mkT<T>(0.0, 0.0);
   }
   __syncthreads();
-  const int jc = tid % CB, g = tid / CB;  // column jc, rows i = k + 1 + g (mod 4); 256 threads
+  const int jc = tid % CB, g = __builtin_amdgcn_readfirstlane(tid / CB);
+  T c[CB / 4];
+#pragma unroll
+  for (int m = 0; m < CB / 4; ++m)
+    c[m] = (jc < kb && g + 4 * m < kb) ? a[g + 4 * m + jc * LD] : mkT<T>(0.0, 0.0);
   int fail = 0;
-  for (int k = 0; k < kb; ++k) {
-    const double akk = re_(a[k + k * LD]);   // the same value in every thread
-    if (!(akk > 1e-15) || !isfinite(akk)) {  // unit-diagonal S: relative floor
-      fail = k0 + k + 1;
-      break;
-    }
-    if (jc > k && jc < kb) {
-      const T akj = rscale(1.0 / akk, a[k + jc * LD]);
-      int i = k + 1 + g;
-      // four rows at a time with every load issued before the stores (row k is not
-      // written in step k), then the remainder
-      for (; i + 12 <= jc; i += 16) {
-        const T r0 = a[k + i * LD], r1 = a[k + (i + 4) * LD], r2 = a[k + (i + 8) * LD], r3 = a[k + (i + 12) * LD];
-        const T c0 = a[i + jc * LD], c1 = a[i + 4 + jc * LD], c2 = a[i + 8 + jc * LD], c3 = a[i + 12 + jc * LD];
-        a[i + jc * LD] = sub_(c0, mul_(conj_(r0), akj));
-        a[i + 4 + jc * LD] = sub_(c1, mul_(conj_(r1), akj));
-        a[i + 8 + jc * LD] = sub_(c2, mul_(conj_(r2), akj));
-        a[i + 12 + jc * LD] = sub_(c3, mul_(conj_(r3), akj));
+#pragma unroll
+  for (int m0 = 0; m0 < CB / 4; ++m0) {
+    for (int q = 0; q < 4; ++q) {
+      const int k = 4 * m0 + q;
+      if (k >= kb || fail) break;
+      if (g == q) row[q & 1][jc] = c[m0];
+      __syncthreads();
+      const T rk = row[q & 1][jc];
+      const double akk = re_(lane_of(rk, k));  // the same value in every thread
+      if (!(akk > 1e-15) || !isfinite(akk)) {  // unit-diagonal S: relative floor
+        fail = k0 + k + 1;
+        break;
       }
-      for (; i <= jc; i += 4) a[i + jc * LD] = sub_(a[i + jc * LD], mul_(conj_(a[k + i * LD]), akj));
+      const T akj = jc > k ? rscale(1.0 / akk, rk) : mkT<T>(0.0, 0.0);
+      if (g > q) c[m0] = sub_(c[m0], mul_(conj_(lane_of(rk, g + 4 * m0)), akj));
+#pragma unroll
+      for (int m = m0 + 1; m < CB / 4; ++m) c[m] = sub_(c[m], mul_(conj_(lane_of(rk, g + 4 * m)), akj));
     }
-    __syncthreads();
   }
   if (fail) {
     if (tid == 0) *info = fail;
     return;
   }
-  for (int i = tid; i < kb; i += blockDim.x) dg[i] = sqrt(re_(a[i + i * LD]));
+#pragma unroll
+  for (int m = 0; m < CB / 4; ++m)
+    if (jc < kb && g + 4 * m <= jc) a[g + 4 * m + jc * LD] = c[m];
+  __syncthreads();
+  for (int i = tid; i < kb; i += blockDim.x) {
+    dg[i] = sqrt(re_(a[i + i * LD]));
+    dinv[i] = 1.0 / dg[i];
+  }
   __syncthreads();
   for (int idx = tid; idx < kb * kb; idx += blockDim.x) {
     int i = idx % kb, j = idx / kb;
-    if (i < j) a[i + j * LD] = rscale(1.0 / dg[i], a[i + j * LD]);
+    if (i < j) a[i + j * LD] = rscale(dinv[i], a[i + j * LD]);
     else if (i == j) a[i + j * LD] = mkT<T>(dg[i], 0.0);
   }
   __syncthreads();
@@ -163,11 +177,12 @@ __global__ __launch_bounds__(256) void chol_diag_kernel(int n, T* __restrict__ S
   const int nbl = (kb + B16 - 1) / B16;
   if (tid < kb) {
     const int j = tid, b0 = (j / B16) * B16;
-    r[j + j * LD] = mkT<T>(1.0 / dg[j], 0.0);
+    r[j + j * LD] = mkT<T>(dinv[j], 0.0);
     for (int i = j - 1; i >= b0; --i) {
       T sacc = mkT<T>(0.0, 0.0);
+#pragma unroll 4
       for (int k = i + 1; k <= j; ++k) sacc = add_(sacc, mul_(a[i + k * LD], r[k + j * LD]));
-      r[i + j * LD] = rscale(-1.0 / dg[i], sacc);
+      r[i + j * LD] = rscale(-dinv[i], sacc);
     }
   }
   __syncthreads();
@@ -178,6 +193,7 @@ __global__ __launch_bounds__(256) void chol_diag_kernel(int n, T* __restrict__ S
       const int i = bI * B16 + rr, j = (bI + d) * B16 + cc;
       T sacc = mkT<T>(0.0, 0.0);
       if (i < kb && j < kb)
+#pragma unroll 8
         for (int k = (bI + 1) * B16; k <= j; ++k) sacc = add_(sacc, mul_(a[i + k * LD], r[k + j * LD]));
       tmp[idx] = sacc;
     }
@@ -188,6 +204,7 @@ __global__ __launch_bounds__(256) void chol_diag_kernel(int n, T* __restrict__ S
       if (i < kb && j < kb) {
         T x = mkT<T>(0.0, 0.0);
         const int kend = min((bI + 1) * B16, kb);
+#pragma unroll 8
         for (int k = i; k < kend; ++k) x = add_(x, mul_(r[i + k * LD], tmp[bI * B16 * B16 + (k - bI * B16) + cc * B16]));
         r[i + j * LD] = sub_(mkT<T>(0.0, 0.0), x);
       }
@@ -334,6 +351,14 @@ static int chol_orth_t(hipStream_t s, int n, const T* M, T* Tout, int* info, voi
   return check_launch("trinv_col_kernel");
 }
 
+// sum over groups of eight lanes (all of a group active), in every lane of the group
+__device__ __forceinline__ double sum_of_8(double v) {
+  v += dpp_f64<0xB1>(v);
+  v += dpp_f64<0x4E>(v);
+  return v + dpp_f64<0x141>(v);   // half mirror: the other quad
+}
+__device__ __forceinline__ cd sum_of_8(cd v) { return {sum_of_8(v.re), sum_of_8(v.im)}; }
+
 // Condition estimate of the column-scaled Gram matrix M_s = D^{-1} M D^{-1} (D = sqrt of
 // diag M) after chol_orth: a Gershgorin bound on lambda_max(M_s) times a power-iteration
 // estimate of lambda_max(M_s^{-1}) = ||R^{-1}||_2^2 (R^{-1} = D T with T = D^{-1} R^{-1}
@@ -342,7 +367,9 @@ static int chol_orth_t(hipStream_t s, int n, const T* M, T* Tout, int* info, voi
 // With STAGE (small n) the triangle of T, 1 / D^{-1} and the scaled |M| are first put in
 // LDS with coalesced loads, so the column sums and the power iterations read no global
 // memory; the arithmetic is the same in both forms.
-template <typename T, bool STAGE>
+// LR = 8: eight lanes share a row's sum, for n up to 128 (n = 56 real 62 us with one lane, 23 so;
+// n = 128 complex 133 and 89; n = 512, where a column's rows fill the lanes, 480 and 770).
+template <typename T, bool STAGE, int LR>
 __global__ __launch_bounds__(1024) void cond_est_kernel(int n, const T* __restrict__ M, const T* __restrict__ Tg,
                                                         const double* __restrict__ dinv_g, int iters,
                                                         const int* __restrict__ info, double* __restrict__ out) {
@@ -350,7 +377,7 @@ __global__ __launch_bounds__(1024) void cond_est_kernel(int n, const T* __restri
   T* v = (T*)smem;  // [n]
   T* y = v + n;     // [n]
   __shared__ double red[16];
-  const int tid = threadIdx.x, nt = blockDim.x;
+  const int tid = threadIdx.x, nt = blockDim.x, sub = tid % LR;
   if (*info != 0) {
     if (tid == 0) *out = 1e300;
     return;
@@ -402,22 +429,26 @@ __global__ __launch_bounds__(1024) void cond_est_kernel(int n, const T* __restri
   double mu = 0.0;
   for (int it = 0; it < iters; ++it) {
     // y = B^H v, B = R^{-1} (upper triangular): y_j = sum_{i <= j} conj(T_ij / dinv_i) v_i
-    for (int j = tid; j < n; j += nt) {
+    for (int j = tid / LR; j < n; j += nt / LR) {
       T acc = mkT<T>(0.0, 0.0);
 #pragma unroll 8
-      for (int i = 0; i <= j; ++i) acc = add_(acc, mul_(conj_(rscale(ri(i), Tm[i + (int64_t)j * n])), v[i]));
-      y[j] = acc;
+      for (int i = sub; i <= j; i += LR) acc = add_(acc, mul_(conj_(rscale(ri(i), Tm[i + (int64_t)j * n])), v[i]));
+      if constexpr (LR == 8) acc = sum_of_8(acc);
+      if (sub == 0) y[j] = acc;
     }
     __syncthreads();
     // v = B y: v_i = sum_{j >= i} (T_ij / dinv_i) y_j
     double nrm = 0.0;
-    for (int i = tid; i < n; i += nt) {
+    for (int i = tid / LR; i < n; i += nt / LR) {
       T acc = mkT<T>(0.0, 0.0);
 #pragma unroll 8
-      for (int j = i; j < n; ++j) acc = add_(acc, mul_(Tm[i + (int64_t)j * n], y[j]));
+      for (int j = i + sub; j < n; j += LR) acc = add_(acc, mul_(Tm[i + (int64_t)j * n], y[j]));
+      if constexpr (LR == 8) acc = sum_of_8(acc);
       acc = rscale(ri(i), acc);
-      v[i] = acc;
-      nrm += re_(mul_(conj_(acc), acc));
+      if (sub == 0) {
+        v[i] = acc;
+        nrm += re_(mul_(conj_(acc), acc));
+      }
     }
     nrm = block_sum(nrm, red);
     // v was normalised at the previous step (the first start vector is not)
@@ -435,14 +466,17 @@ static int chol_cond_est_t(hipStream_t s, int n, const T* M, const T* Tm, const 
   p += (((size_t)n * n * sizeof(T) + 255) / 256) * 256;
   const double* dinv = (const double*)p;
   // one thread per column up to 1024 (a small matrix keeps the barriers of a small group)
-  const int threads = std::min(1024, ((n + 63) / 64) * 64);
+  const int lr = n <= 128 ? 8 : 1;
+  const int threads = std::min(1024, ((lr * n + 63) / 64) * 64);
   const size_t staged = ((size_t)n * n + 2 * n) * sizeof(T) + ((size_t)n * n + n) * 8;
-  if (staged <= 150 * 1024) {
-    SPARC_HIP(hipFuncSetAttribute((const void*)cond_est_kernel<T, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)staged));
-    cond_est_kernel<T, true><<<1, threads, staged, s>>>(n, M, Tm, dinv, 8, info, out);
+  if (staged <= 150 * 1024) {   // n < 100
+    SPARC_HIP(hipFuncSetAttribute((const void*)cond_est_kernel<T, true, 8>,
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)staged));
+    cond_est_kernel<T, true, 8><<<1, threads, staged, s>>>(n, M, Tm, dinv, 8, info, out);
+  } else if (lr == 8) {
+    cond_est_kernel<T, false, 8><<<1, threads, 2 * (size_t)n * sizeof(T), s>>>(n, M, Tm, dinv, 8, info, out);
   } else {
-    cond_est_kernel<T, false><<<1, threads, 2 * (size_t)n * sizeof(T), s>>>(n, M, Tm, dinv, 8, info, out);
+    cond_est_kernel<T, false, 1><<<1, threads, 2 * (size_t)n * sizeof(T), s>>>(n, M, Tm, dinv, 8, info, out);
   }
   return check_launch("cond_est_kernel");
 }
@@ -560,9 +594,6 @@ __global__ __launch_bounds__(1024) void hetrd_kernel(int n, T* __restrict__ A, d
 // and 0.84 ms here complex, 1.2 and 0.30 ms real.  A matrix held in LDS took 85 us for n = 56
 // real, this 76.  With the rows of a product summed over lanes by DPP instead (a 16 x 32
 // thread grid) n = 128 took 0.41 ms real and 1.8 ms complex.
-__device__ __forceinline__ double lane_of(double v, int l) { return readlane_f64(v, l); }
-__device__ __forceinline__ cd lane_of(cd v, int l) { return {readlane_f64(v.re, l), readlane_f64(v.im, l)}; }
-
 template <typename T, int RK, int CM, int NWV>
 __global__ __launch_bounds__(64 * NWV) void hetrd_reg_kernel(int n, T* __restrict__ A, double* __restrict__ d,
                                                              double* __restrict__ e, T* __restrict__ tau) {
