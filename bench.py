@@ -39,10 +39,10 @@ RR_MODES = {"native": 0, "bf16x3": 1, "bf16x6": 2}
 # HBM traffic of the FP64 c2 stencil-step launch, from rocprofv3 FETCH_SIZE and
 # WRITE_SIZE runs scaled by a plain-copy calibration (profiles/hstep_c2_96cubed_f64.md);
 # valid only for the kernel source it was measured on (checked by hash, else null)
-HSTEP_TRAFFIC = {"bytes_per_launch": 1.801882e+10, "kernel_sources_sha256": "e3584a3ff461bdd6b459fa0718f2d49b7a1e66717f456fe6204e705398a8a482",
+HSTEP_TRAFFIC = {"bytes_per_launch": 1.591595e+10, "kernel_sources_sha256": "81600442e66feff7a096bb078708d88c05452569fa628a0824b7bb515a094fda",
                  "profile": "profiles/hstep_c2_96cubed_f64.md",
                  # the FP32 step of the mixed form on the same block, from the same runs
-                 "bytes_per_launch_f32": 8.2161e+09}
+                 "bytes_per_launch_f32": 7.2678e+09}
 UNIT = "grid-pt·states/s"
 HBM_PEAK_GBS = 8000.0
 
@@ -164,7 +164,7 @@ def measured_traffic(f32=False):
     kernel sources are the ones the counters were taken on."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("hstep_api.hpp", "hstep_impl.hpp"):
+    for f in ("hstep_api.hpp", "hrow_impl.hpp"):
         with open(os.path.join(ROOT, "paper_1603_04339_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     if h.hexdigest() != HSTEP_TRAFFIC["kernel_sources_sha256"]:
@@ -228,6 +228,7 @@ def gamma_leg(sp, ctx, cell, X0, v0, precision, steps, warmup, label, rr_mode=0)
     ro_ms, ro_n = ctx.kernel_time("rotate")
     ga_ms, ga_n = ctx.kernel_time("nl_gather")
     sc_ms, sc_n = ctx.kernel_time("nl_scatter")
+    up_ms, up_n = ctx.kernel_time("nl_update")
     ctx.set_timing(False)
     forces = forces_leg(sp, ctx, ham, cell, X, occ, rho) if dt == sp.R64 else None
     psd = pseudocharge_leg(sp, ctx, cell, rho) if dt == sp.R64 else None
@@ -239,14 +240,14 @@ def gamma_leg(sp, ctx, cell, X0, v0, precision, steps, warmup, label, rr_mode=0)
     return {
         "value": nd * ns / (t_total / steps), "ms_per_step": 1e3 * t_total / steps,
         "filter_ms": filt, "filter_throughput": nd * ns / (filt * 1e-3),
-        "roofline": roofline_obj("hstep (12th-order stencil + V_eff + recurrence, LDS-tiled)", total, hs_ms, hs_n,
+        "roofline": roofline_obj("hstep (12th-order stencil + V_eff + recurrence, row form)", total, hs_ms, hs_n,
                                  measured_traffic(dt == sp.R32) if (dt in (sp.R64, sp.R32)
                                                                     and tuple(cell.n) == (96, 96, 96)
                                                                     and cell.n_s == 512) else None),
         "ritz": ritz.cpu().numpy(), "bounds": (lmin, lmax), "n_proj": ham.n_proj, "forces": forces,
         "pseudocharge": psd, "gram_ms_per_step": gm_ms / steps,
         "step_breakdown_ms": {"stencil": hs_ms / steps, "projector_gather": ga_ms / steps,
-                              "projector_scatter": sc_ms / steps, "grams": gm_ms / steps,
+                              "projector_scatter": sc_ms / steps, "projector_update": up_ms / steps, "grams": gm_ms / steps,
                               "rotations": ro_ms / steps},
     }
 
@@ -632,12 +633,13 @@ def batched_leg(sp, ctx, probs, precision, steps, warmup, n_elec_k=None, rr_mode
     plan.close()
     eb = Xs[0].element_size()
     tot_bytes = sum(step_bytes(p[0].n_d, p[0].n_s, eb, p[0].degree) for p in probs)
-    assert hs_n == max(deg), (hs_n, deg)
+    # one launch per step and chunk width of the row form
+    assert hs_n >= max(deg), (hs_n, deg)
     work = sum(p[0].n_d * p[0].n_s for p in probs)
     filt = float(np.median(filt_ms))
     return {"value": work / (t_total / steps), "ms_per_step": 1e3 * t_total / steps, "filter_ms": filt,
             "filter_throughput": work / (filt * 1e-3),
-            "roofline": roofline_obj("hstep batched over all problems (one launch per recurrence step)",
+            "roofline": roofline_obj("hstep batched over all problems (one launch per recurrence step and chunk width)",
                                      tot_bytes, hs_ms, hs_n), "dtype": {sp.R64: "f64", sp.R32: "f32",
                                                                         sp.C128: "c128", sp.C64: "c64"}[dt]}
 
