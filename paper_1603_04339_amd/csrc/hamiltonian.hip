@@ -1,8 +1,9 @@
 // Application of the finite-difference Hamiltonian to a block of orbitals: the
 // non-local gather (projections of the orbitals onto the Kleinman-Bylander
-// projectors) and scatter kernels, the stencil-step launch logic (tile choice,
-// autotuner, batched step tables) and the H*X entry point.  The stencil step
-// kernels themselves are in hstep_impl.hpp.
+// projectors), scatter and update kernels, the stencil-step launch logic (row or tiled
+// form, tile choice, autotuner, batched step tables), the conjugate-gradient kernels and
+// the H*X entry point.  The stencil step kernels themselves are in hrow_impl.hpp (row
+// form) and hstep_impl.hpp (tiled form).
 #include <algorithm>
 #include <cstdlib>
 #include <map>
