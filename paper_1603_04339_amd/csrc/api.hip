@@ -484,6 +484,7 @@ static int rr_rest(sparc_ham* H, void* X, int64_t ldx, int32_t n, sparc_gemm_mod
 int rr_impl(sparc_ham* H, void* X, int64_t ldx, int32_t n, sparc_gemm_mode mode, double* ritz, RRWork& w,
             int32_t* info_out) {
   hipStream_t s = H->ctx->stream;
+  DeviceScope on(H->ctx->device);
   TimerScope timer_scope(H->ctx);
   // pass 1: T1 from the Gram matrix of X (shifted if it is numerically singular), and the
   // condition estimate of the column-scaled Gram matrix
@@ -593,6 +594,7 @@ int rr_concurrent(sparc_ctx* ctx, int32_t n_prob, sparc_ham* const* H, void* con
   for (size_t i = 1; i < span.size(); ++i)
     if (span[i].first < span[i - 1].second) return SPARC_OK;
   if (dense + blk + alpha + gwb > work_bytes) return SPARC_OK;
+  DeviceScope on(ctx->device);
   SideStreams side(ctx);
   if (!side.ready(n_prob)) return SPARC_OK;
 

@@ -363,6 +363,7 @@ static int row_lds_limit(K kernel, int device) {
   static std::atomic<uint64_t> done{0};
   const uint64_t bit = device < 64 ? 1ull << device : 0;
   if (bit && (done.load() & bit)) return SPARC_OK;
+  DeviceScope on(device);
   SPARC_HIP(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRowLds));
   done.fetch_or(bit);
   return SPARC_OK;

@@ -182,6 +182,21 @@ struct TimerScope {
   ~TimerScope() { g_timer_ctx = nullptr; }
 };
 
+// The calling thread's current device is `device` while the object lives.  Launches and copies
+// follow their stream; streams, events and kernel attributes are made on the current device.
+struct DeviceScope {
+  int before = -1;
+  explicit DeviceScope(int device) {
+    int d = device;
+    if (hipGetDevice(&d) == hipSuccess && d != device && hipSetDevice(device) == hipSuccess) before = d;
+  }
+  ~DeviceScope() {
+    if (before >= 0) hipSetDevice(before);
+  }
+  DeviceScope(const DeviceScope&) = delete;
+  DeviceScope& operator=(const DeviceScope&) = delete;
+};
+
 // Hamiltonian application kernels (hamiltonian.hip)
 //   out = a*(H x) + b*x + c*z ; z may alias out (in-place recurrence), x must not.
 //   Runs the stencil/potential/recurrence kernel, then the non-local scatter into out.
