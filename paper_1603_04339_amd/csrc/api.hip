@@ -313,7 +313,7 @@ int filter_impl(sparc_ham* H, void* X, int64_t ldx, int32_t n_s, int32_t degree,
                 void* Wb, void* alpha) {
   const double c = 0.5 * (lmax + lcut), e = 0.5 * (lmax - lcut);
   const int64_t N = H->n_d;
-  const bool upd = nl_update_applies(H) && nl_update_pairs(H, n_s) >= 2 * (int64_t)H->ctx->n_cu;
+  const bool upd = nl_update_single(H, n_s);
   SPARC_TRY(nl_project(H, X, ldx, n_s, alpha));
   SPARC_TRY(ham_step(H, X, ldx, nullptr, 0, Wb, N, n_s, 1.0 / e, -c / e, 0.0, alpha,
                      upd && degree > 1 ? STEP_NO_NONLOCAL : 0));

@@ -778,6 +778,13 @@ bool nl_update_applies(const sparc_ham* H) {
 }
 int64_t nl_update_pairs(const sparc_ham* H, int32_t n_s) { return (int64_t)H->n_atoms_nl * ((n_s + 3) / 4); }
 
+// A single call's launch has the orbital groups in its grid's second direction, which holds
+// 65535: complex blocks, two orbitals a group, reach that at half the size of the gather's.
+bool nl_update_single(const sparc_ham* H, int32_t n_s) {
+  const int nb = dtype_complex(H->dtype) ? update_nb<cd>() : update_nb<double>();
+  return nl_update_applies(H) && nl_update_pairs(H, n_s) >= 2 * (int64_t)H->ctx->n_cu && (n_s + nb - 1) / nb <= 65535;
+}
+
 template <typename E, int MAXP, int NB>
 static void nl_update_launch(sparc_ham* H, void* alpha, int32_t n_s, double a, void* out, int64_t ldo) {
   typedef typename elem<E>::real R;

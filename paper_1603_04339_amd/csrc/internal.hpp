@@ -220,9 +220,11 @@ int noalloc_scratch_init(int device);
 //   out += a * V_nl-scatter(alpha); a from a device scalar when a_dev != nullptr
 int nl_scatter(sparc_ham* H, const void* alpha, int32_t n_s, double a, const double* a_dev, void* out, int64_t ldo);
 //   out += a * V_nl-scatter(alpha), then alpha = the projections of out; whether the form
-//   applies, and the (atom, 4 orbitals) pairs that decide whether it pays
+//   applies, the (atom, 4 orbitals) pairs that decide whether it pays, and the rule of a
+//   single call
 bool nl_update_applies(const sparc_ham* H);
 int64_t nl_update_pairs(const sparc_ham* H, int32_t n_s);
+bool nl_update_single(const sparc_ham* H, int32_t n_s);
 int nl_update(sparc_ham* H, void* alpha, int32_t n_s, double a, void* out, int64_t ldo);
 // Rayleigh-Ritz of several problems with their dense parts on the context's side streams
 // (api.hip): the problems taken on are marked in done, the others are left untouched
