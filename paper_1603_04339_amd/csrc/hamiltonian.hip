@@ -1001,8 +1001,11 @@ __global__ __launch_bounds__(256) void cg_apply_kernel(StepArgs<double> A, CgIte
 // update and A r in two launches.  Bound by latency; each XCD takes neighbouring blocks, whose
 // taps its L2 holds.  40^3: 7.6 us, update and A r 3.5 and 7.7.  Past 2^19 nodes reading three
 // arrays around every node costs more than the second launch: an SCF of four steps with 12 states
-// at 64^3 28.5 ms in two launches and 26.8 in one, 80^3 50 and 46, 96^3 87 and 91.
+// at 64^3 28.5 ms in two launches and 26.8 in one, 80^3 50 and 46, 96^3 87 and 91.  Rows past
+// 2048 nodes take two launches as well, for their LDS: 34 KB there, four work-groups a CU, and at
+// 4096 nodes more than the 64 KB of an ordinary launch (not timed past 2048).
 constexpr int64_t kCgStepNodes = int64_t(1) << 19;
+constexpr int kCgStepRow = 2048;
 
 __device__ __forceinline__ int wrap_index(int c, int n) {
   if (n < 16) return c - floordiv_i(c, n) * n;
@@ -1129,8 +1132,7 @@ static StepArgs<double> cg_args(const sparc_ham* H, double a, double b) {
 }
 
 bool cg_point_form(sparc_ham* H) {
-  // periodic grids whose rows fit the iteration's LDS
-  if (H->dtype != SPARC_R64 || dirichlet_mask(H->grid) != 0 || H->grid.n[0] > 2048) return false;
+  if (H->dtype != SPARC_R64 || dirichlet_mask(H->grid) != 0) return false;
   StepArgs<double> A = cg_args(H, 1.0, 0.0);
   return use_point_form<double>(H, A, 1, heuristic_tile(A.n1, A.n2, sizeof(double)));
 }
@@ -1155,18 +1157,19 @@ int cg_apply(sparc_ham* H, double a, double b, const CgIter& C) {
   return check_launch("cg_apply_kernel");
 }
 
+int cg_iterate_two(sparc_ham* H, double a, double b, CgIter& C) {
+  if ((H->n_d + 255) / 256 > (int64_t)INT32_MAX) return fail(SPARC_ESHAPE, "cg_iterate: grid too large");
+  cg_update_kernel<<<(unsigned)((H->n_d + 255) / 256), 256, 0, H->ctx->stream>>>(H->n_d, C);
+  SPARC_TRY(check_launch("cg_update_kernel"));
+  C.it++;
+  return cg_apply(H, a, b, C);
+}
+
 int cg_iterate(sparc_ham* H, double a, double b, CgIter& C) {
   if (H->dtype != SPARC_R64) return fail(SPARC_EINVAL, "cg_iterate: FP64 operator only");
   const StepArgs<double> A = cg_args(H, a, b);
   const unsigned blocks = (unsigned)cg_blocks(H);
-  const int64_t nd = (int64_t)A.n1 * A.n2 * A.n3;
-  if (nd > kCgStepNodes) {
-    if ((nd + 255) / 256 > (int64_t)INT32_MAX) return fail(SPARC_ESHAPE, "cg_iterate: grid too large");
-    cg_update_kernel<<<(unsigned)((nd + 255) / 256), 256, 0, H->ctx->stream>>>(nd, C);
-    SPARC_TRY(check_launch("cg_update_kernel"));
-    C.it++;
-    return cg_apply(H, a, b, C);
-  }
+  if (H->n_d > kCgStepNodes || A.n1 > kCgStepRow) return cg_iterate_two(H, a, b, C);
   const size_t lds = (256 + 2 * (size_t)A.n1) * sizeof(double);
   switch (H->grid.n_o) {
 #define CASE(K) case K: cg_step_kernel<K><<<blocks, 256, lds, H->ctx->stream>>>(A, C); break;

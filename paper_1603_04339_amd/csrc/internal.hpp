@@ -241,7 +241,7 @@ int heuristic_tile(int n1, int n2, size_t elem_size);
 //   p = r + beta p,  s = w + beta s,  x += alpha p,  r -= alpha s,
 // and w = A r with the block partials of the new g and d.  p and x are updated in place; r, w,
 // s (= A p) and the partials go to rn, wn, sn and partn, and cg_iterate swaps each pair (large
-// grids take two launches, in place).
+// grids and long rows take two launches, in place).
 // part, partn: 2 * kCgBlocks doubles of block partials (nparts = cg_blocks() of them used); sc:
 // two slots of four doubles (g, d, alpha, unused) written by iteration it into slot it % 2, and
 // sc[8] for cg_residual_norm.  The first iteration (it = 0) needs r, w = cg_apply(r) (which
@@ -263,6 +263,7 @@ bool cg_point_form(sparc_ham* H);
 int cg_blocks(const sparc_ham* H);
 int cg_apply(sparc_ham* H, double a, double b, const CgIter& C);
 int cg_iterate(sparc_ham* H, double a, double b, CgIter& C);
+int cg_iterate_two(sparc_ham* H, double a, double b, CgIter& C);   // always in two launches
 int cg_residual_norm(sparc_ham* H, const CgIter& C);
 // projections and scatters of several problems in one launch each (hamiltonian.hip): one
 // argument block per problem in a device table, work-group offsets per problem
