@@ -573,7 +573,9 @@ int rr_concurrent(sparc_ctx* ctx, int32_t n_prob, sparc_ham* const* H, void* con
                   const int32_t* n_s, sparc_gemm_mode mode, double* const* ritz, void* work, size_t work_bytes,
                   std::vector<char>& done) {
   // calls that a single call would refuse, blocks that overlap and split products (their pieces
-  // need the second block) are left to it, as is kernel timing, which follows one stream
+  // need the second block) are left to it, as is kernel timing, which follows one stream.  So is
+  // the first call of a shape on a context that autotunes: its products are timed one after another,
+  // not beside the dense chains of other problems
   if (n_prob < 2 || mode != SPARC_GEMM_NATIVE || ctx->timing || !work) return SPARC_OK;
   size_t blk = 0, alpha = 0, gwb = 0, dense = al((size_t)n_prob * sizeof(RRFirst));
   std::vector<std::pair<uintptr_t, uintptr_t>> span;
@@ -581,6 +583,7 @@ int rr_concurrent(sparc_ctx* ctx, int32_t n_prob, sparc_ham* const* H, void* con
     if (!H[p] || H[p]->ctx != ctx || !X[p] || !ritz[p] || n_s[p] < 1 || n_s[p] > 2048 || n_s[p] > H[p]->n_d ||
         ldx[p] < H[p]->n_d || work_bytes < rr_layout(H[p], n_s[p], nullptr, 0, nullptr))
       return SPARC_OK;
+    if (ctx->autotune && !rr_products_tuned(H[p]->dtype, H[p]->n_d, n_s[p])) return SPARC_OK;
     const size_t eb = elem_bytes(H[p]->dtype);
     blk = std::max(blk, al((size_t)H[p]->n_d * n_s[p] * eb));
     alpha = std::max(alpha, al(alpha_bytes(H[p], n_s[p])));

@@ -598,9 +598,17 @@ static int gram_launch(hipStream_t s, int64_t N, int na, int nb, const E* A, int
 // reuse it.
 struct GemmChoice { int T; int64_t slabs; };
 static std::mutex g_gemm_tune_mu;
-static std::map<std::tuple<int64_t, int, int, int, int, int>, GemmChoice> g_gemm_tune;
+// N, n_a, n_b, element type, Hermitian result (Gram) or upper-triangular Q (rotation), and 0 / 2:
+// a Gram of one / two operands, 1: a rotation
+typedef std::tuple<int64_t, int, int, int, int, int> GemmKey;
+static std::map<GemmKey, GemmChoice> g_gemm_tune;
 
-static bool gemm_lookup(const std::tuple<int64_t, int, int, int, int, int>& key, GemmChoice* c) {
+template <typename E>
+static GemmKey gemm_key(int64_t N, int na, int nb, int flag, int kind) {
+  return GemmKey(N, na, nb, (int)(sizeof(E) * 2 + (elem<E>::is_cplx ? 1 : 0)), flag, kind);
+}
+
+static bool gemm_lookup(const GemmKey& key, GemmChoice* c) {
   std::lock_guard<std::mutex> lk(g_gemm_tune_mu);
   auto it = g_gemm_tune.find(key);
   if (it == g_gemm_tune.end()) return false;
@@ -608,9 +616,26 @@ static bool gemm_lookup(const std::tuple<int64_t, int, int, int, int, int>& key,
   return true;
 }
 
-static void gemm_store(const std::tuple<int64_t, int, int, int, int, int>& key, GemmChoice c) {
+static void gemm_store(const GemmKey& key, GemmChoice c) {
   std::lock_guard<std::mutex> lk(g_gemm_tune_mu);
   g_gemm_tune[key] = c;
+}
+
+template <typename E>
+static bool rr_products_tuned_t(int64_t N, int n) {
+  GemmChoice c;
+  return gemm_lookup(gemm_key<E>(N, n, n, 1, 0), &c) && gemm_lookup(gemm_key<E>(N, n, n, 1, 2), &c) &&
+         gemm_lookup(gemm_key<E>(N, n, n, 0, 1), &c);
+}
+
+bool rr_products_tuned(sparc_dtype dt, int64_t N, int n) {
+  switch (dt) {
+    case SPARC_R64: return rr_products_tuned_t<double>(N, n);
+    case SPARC_R32: return rr_products_tuned_t<float>(N, n);
+    case SPARC_C128: return rr_products_tuned_t<cd>(N, n);
+    case SPARC_C64: return rr_products_tuned_t<cf>(N, n);
+  }
+  return false;
 }
 
 template <typename E>
@@ -653,7 +678,7 @@ static int gram_t(hipStream_t s, int64_t N, int na, int nb, const E* A, int64_t 
     return gram_launch<E>(s, N, na, nb, A, lda, B, ldb, C, ldc, work, work_bytes, n_cu, herm, mode, c.T, c.slabs);
   // kind 0: one operand (A^H A), 2: two (they read twice the data)
   const int kind = (A == B && lda == ldb) ? 0 : 2;
-  const auto key = std::make_tuple(N, na, nb, (int)(sizeof(E) * 2 + (elem<E>::is_cplx ? 1 : 0)), herm ? 1 : 0, kind);
+  const GemmKey key = gemm_key<E>(N, na, nb, herm ? 1 : 0, kind);
   if (!gemm_lookup(key, &c)) {
     hipEvent_t e0, e1;
     SPARC_HIP(hipEventCreate(&e0));
@@ -894,7 +919,7 @@ static int rotate_t(hipStream_t s, int64_t N, int n_in, int n_out, const E* A, i
   // tuned like the Gram's when the context asks for it (Out is rewritten by every candidate)
   int T = n_out <= 32 ? 32 : (n_out <= 64 || elem<E>::is_cplx) ? 64 : 128;
   if (tune && tune->autotune) {
-    const auto key = std::make_tuple(N, n_in, n_out, (int)(sizeof(E) * 2 + (elem<E>::is_cplx ? 1 : 0)), q_upper, 1);
+    const GemmKey key = gemm_key<E>(N, n_in, n_out, q_upper, 1);
     GemmChoice c{T, 0};
     if (!gemm_lookup(key, &c)) {
       hipEvent_t e0, e1;

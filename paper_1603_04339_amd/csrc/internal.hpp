@@ -359,6 +359,8 @@ int gram(hipStream_t s, sparc_dtype dt, int64_t N, int32_t n_a, int32_t n_b, con
 //   q_upper: Q is upper triangular (entries below the diagonal are not read).
 int rotate(hipStream_t s, sparc_dtype dt, int64_t N, int32_t n_in, int32_t n_out, const void* A, int64_t lda,
            const void* Q, int32_t ldq, void* Out, int64_t ldo, int q_upper = 0, sparc_ctx* tune = nullptr);
+//   whether the three N x n products of a one-pass Rayleigh-Ritz have their timed choices
+bool rr_products_tuned(sparc_dtype dt, int64_t N, int n);
 // Out = A Q with split-BF16 (x3) products from pre-split operands (FP32 / complex64
 // blocks, n_in a multiple of 16): a_pieces holds N * n_in * 2 pieces of 2 bytes per
 // real part (the size of one FP32 / complex64 N x n_in block), q_pieces 2 * n_in * n_out

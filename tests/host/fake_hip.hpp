@@ -34,7 +34,7 @@ inline int current = 0;
 inline double readback = 0.0;   // what small device-to-host copies return (in every double)
 inline std::vector<Launch> launches;
 inline std::vector<int> streams_made, events_made;   // the device of each
-inline int n_malloc = 0, n_memcpy = 0, n_sync = 0;
+inline int n_malloc = 0, n_memcpy = 0, n_sync = 0, n_event_sync = 0;
 inline hipError_t last = hipSuccess;
 // registered by the library's constructors, which run before this program's own
 inline std::map<const void*, std::string>& kernels() {
@@ -63,7 +63,7 @@ inline void clear() {
   launches.clear();
   streams_made.clear();
   events_made.clear();
-  n_malloc = n_memcpy = n_sync = 0;
+  n_malloc = n_memcpy = n_sync = n_event_sync = 0;
 }
 
 inline int device_of(hipStream_t s) { return s ? ((Stream*)s)->device : current; }
@@ -189,5 +189,5 @@ FAKE_EXPORT hipError_t hipEventDestroy(hipEvent_t e) { delete (fake::Event*)e; r
 FAKE_EXPORT hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
   return ((fake::Event*)e)->device == fake::device_of(s) ? hipSuccess : hipErrorInvalidHandle;
 }
-FAKE_EXPORT hipError_t hipEventSynchronize(hipEvent_t) { ++fake::n_sync; return hipSuccess; }
+FAKE_EXPORT hipError_t hipEventSynchronize(hipEvent_t) { ++fake::n_event_sync; return hipSuccess; }
 FAKE_EXPORT hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 1.0f; return hipSuccess; }
