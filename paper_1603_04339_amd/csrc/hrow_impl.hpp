@@ -357,14 +357,15 @@ __global__ __launch_bounds__(kRowThreads) void hrow_batched_kernel(const StepArg
   hrow_body<E, VX, VY, HM, FULL, HASZ>(A, L, (A.txt * A.tyt + 63) / 64 * 64, row_lds);
 }
 
-// the kernels' dynamic LDS limit, raised once per kernel and device
-template <typename K>
-static int row_lds_limit(K kernel, int device) {
+// a kernel's dynamic LDS limit, raised once per device (the kernel is the template's argument:
+// the forms of one element type share a function type)
+template <auto Kernel>
+static int row_lds_limit(int device) {
   static std::atomic<uint64_t> done{0};
   const uint64_t bit = device < 64 ? 1ull << device : 0;
   if (bit && (done.load() & bit)) return SPARC_OK;
   DeviceScope on(device);
-  SPARC_HIP(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRowLds));
+  SPARC_HIP(hipFuncSetAttribute((const void*)Kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRowLds));
   done.fetch_or(bit);
   return SPARC_OK;
 }
@@ -375,13 +376,13 @@ static int row_launch(sparc_ctx* ctx, const StepArgs<E>* one, const void* probs,
   if (total > (int64_t)INT32_MAX) return fail(SPARC_ESHAPE, "stencil step: too many work-groups");
   int t;
   if (one) {
-    auto k = hrow_kernel<E, VX, VY, HM, FULL, HASZ>;
-    SPARC_TRY(row_lds_limit(k, ctx->device));
+    constexpr auto k = hrow_kernel<E, VX, VY, HM, FULL, HASZ>;
+    SPARC_TRY(row_lds_limit<k>(ctx->device));
     t = timer_begin(ctx, "hstep");
     k<<<(unsigned)total, c.nt, c.lds, ctx->stream>>>(*one);
   } else {
-    auto k = hrow_batched_kernel<E, VX, VY, HM, FULL, HASZ>;
-    SPARC_TRY(row_lds_limit(k, ctx->device));
+    constexpr auto k = hrow_batched_kernel<E, VX, VY, HM, FULL, HASZ>;
+    SPARC_TRY(row_lds_limit<k>(ctx->device));
     t = timer_begin(ctx, "hstep");
     k<<<(unsigned)total, c.nt, c.lds, ctx->stream>>>((const StepArgs<E>*)probs, wg, n);
   }
