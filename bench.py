@@ -432,7 +432,7 @@ def run_gamma(args, sp, wl, cell, X0, v0, cpu=None):
     import torch
     log(f"[bench] {args.config}: n={cell.n} N_s={cell.n_s} m={cell.degree}")
     ctx = sp.Context(0)
-    sp.set_autotune(ctx, not args.no_autotune)  # stencil tile and GEMM shapes timed in the warm-up
+    sp.set_autotune(ctx, not args.no_autotune)  # stencil plans and GEMM shapes timed in the warm-up
     main = gamma_leg(sp, ctx, cell, X0, v0, args.precision, args.steps, args.warmup, args.precision,
                      rr_mode=RR_MODES[args.rr])
     nd, ns = cell.n_d, cell.n_s
@@ -566,7 +566,7 @@ def batched_leg(sp, ctx, probs, precision, steps, warmup, n_elec_k=None, rr_mode
     else:
         dt = sp.R64 if precision == "f64" else sp.R32
         tdt = torch.float64 if precision == "f64" else torch.float32
-    sp.set_autotune(ctx, autotune)   # the plan times every tile shape on the largest problem
+    sp.set_autotune(ctx, autotune)   # the plan times the stencil shapes on its own batched step
     hams, Xs, bounds, ritz = [], [], [], []
     for cell, k, X0, v0, _ in probs:
         kk = k if k is not None else (0.0, 0.0, 0.0)

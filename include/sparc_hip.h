@@ -166,7 +166,7 @@ int fd_hamiltonian_apply(sparc_ham* ham, const void* X, int64_t ldx, void* Y, in
  * (fd_hamiltonian_apply_noalloc_max_bytes() = 16 MiB; one copy per device, resident
  * until the process ends, its address looked up by sparc_ctx_create) instead of a
  * workspace.  Allocates nothing, creates no events and never synchronises; the stencil
- * tile is the heuristic one, or one the context's autotuner has already chosen.
+ * shape is the heuristic one, or one the context's autotuner has already chosen.
  * Every call on one device shares that array: calls that overlap on one device (two
  * streams, two threads) race and must be ordered by the caller.  Errors: as
  * fd_hamiltonian_apply; ENOMEM when the projections (SPARC_OP_APPLY bytes of
@@ -265,9 +265,13 @@ size_t sparc_rr_batched_workspace_bytes(int32_t n_prob, sparc_ham* const* H, con
 int rayleigh_ritz_batched(sparc_ctx* ctx, int32_t n_prob, sparc_ham* const* H, void* const* X,
                           const int64_t* ldx, const int32_t* n_s, sparc_gemm_mode mode,
                           double* const* ritz_dev, void* work, size_t work_bytes);
-/* Stencil tile autotuning: when enabled, the first non-in-place stencil step of a new
- * (grid, n_s, dtype, n_o) shape times every tile shape once (HIP events on the
- * context's stream) and the fastest is cached for the process. */
+/* Autotuning: when enabled, the first non-in-place stencil step of a new (grid, n_s,
+ * dtype, n_o) shape and the creation of a filter plan over new problem shapes time the
+ * shapes of the step's form once (HIP events on the context's stream), every tile, or, on
+ * periodic cells with n_o = 6 whose steps run over whole grid rows, up to four plans of
+ * tile height and z chunks; the fastest is cached for the process.  The results of a step
+ * are the same in all of them.  Rayleigh–Ritz times the tile edges and slab counts of its
+ * N_d-long products likewise (a slab count changes their order of summation). */
 int sparc_ctx_set_autotune(sparc_ctx* ctx, int enable);
 
 /* Minimal self-consistent field (Sec. 2 SCF fixed point with mixing, Sec. 3.4

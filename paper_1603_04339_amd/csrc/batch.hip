@@ -71,6 +71,34 @@ static int scatter_nb(const sparc_filter_plan* P, int j) {
   return P->update && j + 1 < P->max_deg ? kSharedNB : kScatterNB;
 }
 
+// step j of the row form: one launch per chunk width (the step's problems are in that order)
+static int row_step(sparc_filter_plan* P, int j, int hasz) {
+  const auto& mem = P->members[j];
+  const int* wg = P->host_wg.data() + P->wg_off[j];
+  for (size_t a = 0, b; a < mem.size(); a = b) {
+    const RowCfg& c = P->row[mem[a]].cfg;
+    for (b = a + 1; b < mem.size() && P->row[mem[b]].cfg.vx == c.vx;) ++b;
+    SPARC_TRY(row_table_launch(P->ctx, P->dt, c, P->dev_tables + P->table_off[j] + a * step_args_bytes(P->dt),
+                               P->dev_wg + P->wg_off[j] + a, (int)(b - a), wg[b] - wg[a], hasz));
+  }
+  return SPARC_OK;
+}
+
+// the problems of each step; in the row form by chunk width, and long work-groups first
+static void plan_members(sparc_filter_plan* P) {
+  std::vector<int> order(P->n_prob);
+  for (int p = 0; p < P->n_prob; ++p) order[p] = p;
+  if (!P->row.empty())
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+      const RowPlan &x = P->row[a], &y = P->row[b];
+      return x.cfg.vx != y.cfg.vx ? x.cfg.vx > y.cfg.vx : x.dur > y.dur;
+    });
+  P->members.assign(P->max_deg, {});
+  for (int j = 0; j < P->max_deg; ++j)
+    for (int p : order)
+      if (P->deg[p] > j) P->members[j].push_back(p);
+}
+
 // the step sequence of all problems (enqueued directly, or recorded into the graph)
 static int plan_enqueue(sparc_filter_plan* P) {
   const size_t eb = elem_bytes(P->dt);
@@ -82,14 +110,7 @@ static int plan_enqueue(sparc_filter_plan* P) {
       SPARC_TRY(nl_gather_batched(P->ctx, P->dt, P->maxp, P->dev_gather + t0, P->dev_goff + o0, P->n_gather[j],
                                   P->gather_wg[j]));
     if (!P->row.empty()) {
-      // one launch per chunk width (the step's problems are in that order)
-      for (size_t a = 0, b; a < mem.size(); a = b) {
-        const RowCfg& c = P->row[mem[a]].cfg;
-        for (b = a + 1; b < mem.size() && P->row[mem[b]].cfg.vx == c.vx;) ++b;
-        const int* wg = P->host_wg.data() + P->wg_off[j];
-        SPARC_TRY(row_table_launch(P->ctx, P->dt, c, P->dev_tables + P->table_off[j] + a * step_args_bytes(P->dt),
-                                   P->dev_wg + P->wg_off[j] + a, (int)(b - a), wg[b] - wg[a], j > 0));
-      }
+      SPARC_TRY(row_step(P, j, j > 0));
     } else {
       SPARC_TRY(step_table_launch(P->ctx, P->dt, P->n_o, P->tile, P->dev_tables + P->table_off[j],
                                   P->dev_wg + P->wg_off[j], (int)mem.size(), P->total_wg[j], P->dir, P->nl_lds[j]));
@@ -177,86 +198,81 @@ static int plan_tables(sparc_filter_plan* P, const double* lcut, const double* l
   return SPARC_OK;
 }
 
-// Stencil tile of a plan when the context autotunes: every shape is timed on the plan's
-// own batched step over all problems, in the recurrence's memory pattern (X_p read,
-// W_p read and written: x = X_p, z = out = W_p), three launches back to back after a
-// warm-up, best of two such runs; X is only read and W is workspace.  The choice is
-// kept per set of problem shapes.
+// Stencil shape of a plan when the context autotunes: every tile shape, or the row plans worth a
+// trial, timed on the plan's own batched step over all problems, in the recurrence's memory
+// pattern (X_p read, W_p read and written: x = X_p, z = out = W_p); X is only read and W is
+// workspace.  The choice is kept per set of problem shapes.
 static std::mutex g_plan_tune_mu;
-static std::map<std::vector<int>, int> g_plan_tune;
+static std::map<std::vector<int>, int> g_plan_tune;   // tile, or pick of row_batch_plan
 
-static int plan_tune_tile(sparc_filter_plan* P) {
-  std::vector<int> key;
+// one trial: ms of the plan's first step (it has every problem as a member) in shape t (tiled
+// form) or with P->row
+static int plan_trial(sparc_filter_plan* P, int t, float* ms) {
+  sparc_ctx* ctx = P->ctx;
+  const int n = P->n_prob;
+  std::vector<StepDesc> d(n);
+  std::vector<sparc_ham*> hs(n);
+  plan_members(P);
+  for (int i = 0; i < n; ++i) {
+    const int p = P->members[0][i];
+    StepDesc& s = d[i];
+    hs[i] = P->H[p];
+    s.n_s = P->n_s[p];
+    s.x = P->X[p]; s.ldx = P->ldx[p];
+    s.z = P->W[p]; s.ldz = P->H[p]->n_d;
+    s.out = P->W[p]; s.ldo = P->H[p]->n_d;
+    s.a = 0.05; s.b = 0.0; s.c = 0.0;
+    s.alpha = P->row.empty() && nl_step_fused(P->H[p], t) ? P->alpha[p] : nullptr;
+    s.row = P->row.empty() ? nullptr : &P->row[p];
+  }
+  char* tab = P->host_tables.data() + P->table_off[0];
+  int* wg = P->host_wg.data() + P->wg_off[0];
+  const size_t tab_bytes = (P->max_deg > 1 ? P->table_off[1] : P->table_bytes) - P->table_off[0];
+  size_t lds = 0;
+  const int64_t tot = step_table_build(hs.data(), d.data(), n, t, tab, wg, &lds);
+  if (tot < 0) return fail(SPARC_EINVAL, "filter plan: bad dtype");
+  SPARC_HIP(hipMemcpyAsync(P->dev_tables + P->table_off[0], tab, tab_bytes, hipMemcpyHostToDevice, ctx->stream));
+  SPARC_HIP(hipMemcpyAsync(P->dev_wg + P->wg_off[0], wg, (size_t)(n + 1) * sizeof(int), hipMemcpyHostToDevice,
+                           ctx->stream));
+  return tune_burst(ctx, [&]() {
+    if (!P->row.empty()) return row_step(P, 0, 1);
+    return step_table_launch(ctx, P->dt, P->n_o, t, P->dev_tables + P->table_off[0], P->dev_wg + P->wg_off[0], n, tot,
+                             P->dir, lds);
+  }, ms);
+}
+
+static int plan_tune(sparc_filter_plan* P) {
+  const bool row = !P->row.empty();
+  std::vector<int> key{row ? 1 : 0};
   for (int p = 0; p < P->n_prob; ++p) {
     const sparc_ham* h = P->H[p];
     key.insert(key.end(), {h->grid.n[0], h->grid.n[1], h->grid.n[2], P->n_s[p], (int)h->dtype, h->grid.n_o,
                            dirichlet_mask(h->grid)});
   }
+  int best = row ? 0 : P->tile;
+  bool known = false;
   {
     std::lock_guard<std::mutex> lk(g_plan_tune_mu);
     auto it = g_plan_tune.find(key);
-    if (it != g_plan_tune.end()) { P->tile = it->second; return SPARC_OK; }
-  }
-  sparc_ctx* ctx = P->ctx;
-  const int n = P->n_prob;
-  std::vector<StepDesc> d(n);
-  std::vector<sparc_ham*> hs(P->H);
-  hipEvent_t e0, e1;
-  SPARC_HIP(hipEventCreate(&e0));
-  SPARC_HIP(hipEventCreate(&e1));
-  const bool timing = ctx->timing;
-  ctx->timing = false;
-  int best = P->tile, rc = SPARC_OK;
-  float best_ms = 1e30f;
-  char* tab = P->host_tables.data() + P->table_off[0];
-  int* wg = P->host_wg.data() + P->wg_off[0];
-  // step 0 has every problem as a member: its table and offsets hold n blocks
-  const size_t tab_bytes = (P->max_deg > 1 ? P->table_off[1] : P->table_bytes) - P->table_off[0];
-  for (int t = 0; t < tile_shape_count() && rc == SPARC_OK; ++t) {
-    if (tile_shape_threads(t) > 1024) continue;
-    for (int p = 0; p < n; ++p) {
-      StepDesc& s = d[p];
-      const int64_t nd = P->H[p]->n_d;
-      s.n_s = P->n_s[p];
-      s.x = P->X[p]; s.ldx = P->ldx[p];
-      s.z = P->W[p]; s.ldz = nd;
-      s.out = P->W[p]; s.ldo = nd;
-      s.a = 0.05; s.b = 0.0; s.c = 0.0;
-      s.alpha = nl_step_fused(P->H[p], t) ? P->alpha[p] : nullptr;
+    if (it != g_plan_tune.end()) {
+      best = it->second;
+      known = true;
     }
-    size_t lds = 0;
-    const int64_t tot = step_table_build(hs.data(), d.data(), n, t, tab, wg, &lds);
-    if (tot < 0) { rc = fail(SPARC_EINVAL, "filter plan: bad dtype"); break; }
-    hipError_t e = hipMemcpyAsync(P->dev_tables + P->table_off[0], tab, tab_bytes, hipMemcpyHostToDevice, ctx->stream);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(P->dev_wg + P->wg_off[0], wg, (size_t)(n + 1) * sizeof(int), hipMemcpyHostToDevice,
-                         ctx->stream);
-    if (e != hipSuccess) { rc = fail(SPARC_EDEVICE, "filter plan: %s", hipGetErrorString(e)); break; }
-    auto launch = [&]() {
-      return step_table_launch(ctx, P->dt, P->n_o, t, P->dev_tables + P->table_off[0], P->dev_wg + P->wg_off[0], n,
-                               tot, P->dir, lds);
-    };
-    rc = launch();  // warm-up
-    float t_best = 1e30f;
-    for (int r = 0; r < 2 && rc == SPARC_OK; ++r) {
-      hipEventRecord(e0, ctx->stream);
-      for (int q = 0; q < 3 && rc == SPARC_OK; ++q) rc = launch();
-      hipEventRecord(e1, ctx->stream);
-      if (rc != SPARC_OK) break;
-      hipEventSynchronize(e1);
-      float ms = 0;
-      hipEventElapsedTime(&ms, e0, e1);
-      t_best = std::min(t_best, ms);
-    }
-    if (rc == SPARC_OK && t_best < best_ms) { best_ms = t_best; best = t; }
   }
-  ctx->timing = timing;
-  hipEventDestroy(e0);
-  hipEventDestroy(e1);
-  if (rc != SPARC_OK) return rc;
-  P->tile = best;
-  std::lock_guard<std::mutex> lk(g_plan_tune_mu);
-  g_plan_tune[key] = best;
+  if (!known) {
+    float best_ms = 1e30f, ms;
+    for (int t = 0; row || t < tile_shape_count(); ++t) {
+      if (row && !row_batch_plan(P->H.data(), P->n_s.data(), P->n_prob, &P->row, t)) break;
+      if (!row && tile_shape_threads(t) > 1024) continue;
+      SPARC_TRY(plan_trial(P, t, &ms));
+      if (ms < best_ms) { best_ms = ms; best = t; }
+    }
+    std::lock_guard<std::mutex> lk(g_plan_tune_mu);
+    g_plan_tune[key] = best;
+  }
+  if (row) row_batch_plan(P->H.data(), P->n_s.data(), P->n_prob, &P->row, best);
+  else P->tile = best;
+  plan_members(P);
   return SPARC_OK;
 }
 
@@ -342,22 +358,12 @@ int sparc_filter_plan_create(sparc_ctx* ctx, int32_t n_prob, sparc_ham* const* H
   P->maxp = 0;
   for (int p = 0; p < n_prob; ++p) P->maxp = std::max(P->maxp, H[p]->max_proj_per_atom);
   P->nl_lds.assign(P->max_deg, 0);
-  P->members.resize(P->max_deg);
   P->total_wg.assign(P->max_deg, 0);
-  // the row form where every problem allows it, else the tiled form; the problems of a step
-  // are ordered by chunk width, each width being one launch
+  // the row form where every problem allows it, else the tiled form
   if (!row_batch_plan(P->H.data(), P->n_s.data(), n_prob, &P->row)) P->row.clear();
-  std::vector<int> order(n_prob);
-  for (int p = 0; p < n_prob; ++p) order[p] = p;
-  if (!P->row.empty())
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
-      const RowPlan &x = P->row[a], &y = P->row[b];   // long work-groups first
-      return x.cfg.vx != y.cfg.vx ? x.cfg.vx > y.cfg.vx : x.dur > y.dur;
-    });
+  plan_members(P);
   size_t toff = 0, woff = 0;
   for (int j = 0; j < P->max_deg; ++j) {
-    for (int p : order)
-      if (degree[p] > j) P->members[j].push_back(p);
     P->table_off.push_back(toff);
     P->wg_off.push_back(woff);
     toff += P->members[j].size() * ab;
@@ -366,15 +372,16 @@ int sparc_filter_plan_create(sparc_ctx* ctx, int32_t n_prob, sparc_ham* const* H
   P->host_tables.assign(P->table_bytes, 0);
   P->host_wg.assign((size_t)P->max_deg * (n_prob + 1), 0);
   P->host_a.assign((size_t)P->max_deg * n_prob, 0.0);
-  // stencil tile: autotuned on the largest problem when the context asks for it
+  // stencil shape: the model's or heuristic one of the largest problem, or a timed one when the
+  // context asks for it
   int big = 0;
   for (int p = 1; p < n_prob; ++p)
     if ((double)H[p]->n_d * n_s[p] > (double)H[big]->n_d * n_s[big]) big = p;
   P->tile = heuristic_tile(H[big]->grid.n[0], H[big]->grid.n[1], elem_bytes(P->dt));
   P->dir = 0;
   for (int p = 0; p < n_prob; ++p) P->dir |= dirichlet_mask(H[p]->grid) != 0 ? 1 : 0;
-  if (ctx->autotune && P->row.empty()) {
-    int rc = plan_tune_tile(P);
+  if (ctx->autotune) {
+    int rc = plan_tune(P);
     if (rc != SPARC_OK) { delete P; return rc; }
   }
   for (int p = 0; p < n_prob; ++p) P->fused.push_back(P->row.empty() && nl_step_fused(H[p], P->tile) ? 1 : 0);

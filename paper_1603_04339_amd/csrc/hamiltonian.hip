@@ -654,80 +654,66 @@ int heuristic_tile(int n1, int n2, size_t elem_size) {
 }
 
 // ------------------------------------------------------------ autotuner
-// The first non-in-place step for a new (grid, states, type, stencil) key times every
-// tile shape the way the filter runs it: recurrence steps (two blocks read, one written:
-// out = a H x + b x + 0 * out) three times back to back after a warm-up, best of two
-// such runs, with HIP events on the context's stream, and keeps the fastest.  x is only
-// read; out (the caller's output block) is overwritten by the real launch that follows.
-// Later steps with that key reuse the choice.
+// The first non-in-place step for a new (grid, states, type, stencil) key times the shapes of
+// the form it takes, tile shapes or row plans, the way the filter runs them: recurrence steps
+// (two blocks read, one written: out = a H x + b x + 0 * out) three times back to back after a
+// warm-up, best of two such runs, with HIP events on the context's stream, and keeps the
+// fastest.  x is only read; out (the caller's output block) is overwritten by the real launch
+// that follows.  Later steps with that key reuse the choice.  A node's arithmetic is the same in
+// every shape of a form.
+typedef std::tuple<int, int, int, int, int, int> TuneKey;
 static std::mutex g_tune_mu;
-static std::map<std::tuple<int, int, int, int, int, int>, int> g_tune_cache;
+static std::map<TuneKey, int> g_tune_cache;
+static std::map<TuneKey, RowPlan> g_row_tune;
 
-static bool tune_lookup(const std::tuple<int, int, int, int, int, int>& key, int* t) {
+static TuneKey tune_key(const sparc_ham* H, int32_t n_s) {
+  return TuneKey(H->grid.n[0], H->grid.n[1], H->grid.n[2], n_s, (int)H->dtype, H->grid.n_o);
+}
+
+template <typename C>
+static bool tune_lookup(const std::map<TuneKey, C>& cache, const sparc_ham* H, int32_t n_s, C* c) {
   std::lock_guard<std::mutex> lk(g_tune_mu);
-  auto it = g_tune_cache.find(key);
-  if (it == g_tune_cache.end()) return false;
-  *t = it->second;
+  auto it = cache.find(tune_key(H, n_s));
+  if (it == cache.end()) return false;
+  *c = it->second;
   return true;
 }
 
-int tuned_tile(sparc_ham* H, int32_t n_s, int* t) {
-  return tune_lookup(std::make_tuple(H->grid.n[0], H->grid.n[1], H->grid.n[2], n_s, (int)H->dtype, H->grid.n_o), t)
-             ? 1 : 0;
-}
-
-void tune_store(sparc_ham* H, int32_t n_s, int t) {
+template <typename C>
+static void tune_store(std::map<TuneKey, C>& cache, const sparc_ham* H, int32_t n_s, const C& c) {
   std::lock_guard<std::mutex> lk(g_tune_mu);
-  g_tune_cache[std::make_tuple(H->grid.n[0], H->grid.n[1], H->grid.n[2], n_s, (int)H->dtype, H->grid.n_o)] = t;
+  cache[tune_key(H, n_s)] = c;
 }
 
 int tile_shape_count() { return kNumTiles; }
 int tile_shape_threads(int t) { return (t >= 0 && t < kNumTiles) ? kTiles[t].tx * kTiles[t].ty : 0; }
 
-constexpr int kTuneBurst = 3;  // launches timed back to back
-constexpr int kTuneRuns = 2;   // best of
+// the trial step: the recurrence operand is read as the filter reads Y_{j-1}
+template <typename E>
+static StepArgs<E> trial_step(const StepArgs<E>& A) {
+  StepArgs<E> B = A;
+  B.z = A.out;
+  B.ldz = A.ldo;
+  B.zc = 0;
+  return B;
+}
 
 template <typename E>
 static int autotune(sparc_ham* H, StepArgs<E>& A, int32_t n_s, int* best, double a, const void* alpha) {
-  sparc_ctx* ctx = H->ctx;
-  hipEvent_t e0, e1;
-  SPARC_HIP(hipEventCreate(&e0));
-  SPARC_HIP(hipEventCreate(&e1));
-  const bool timing = ctx->timing;
-  ctx->timing = false;
   float best_ms = 1e30f;
   *best = heuristic_tile(A.n1, A.n2, sizeof(E));
-  int rc = SPARC_OK;
-  for (int t = 0; t < kNumTiles && rc == SPARC_OK; ++t) {
+  for (int t = 0; t < kNumTiles; ++t) {
     if (kTiles[t].tx * kTiles[t].ty > 1024) continue;
-    StepArgs<E> B = A;
-    B.z = A.out;  // the recurrence operand: read as the filter reads Y_{j-1}
-    B.ldz = A.ldo;
-    B.zc = 0;
-    nl_fill(H, B, t, a, alpha, n_s);
-    const StepArgs<E> B0 = B;
-    rc = hstep_single<E>(ctx, B, n_s, H->grid.n_o, t);  // warm-up
-    float t_best = 1e30f;
-    for (int r = 0; r < kTuneRuns && rc == SPARC_OK; ++r) {
-      hipEventRecord(e0, ctx->stream);
-      for (int q = 0; q < kTuneBurst && rc == SPARC_OK; ++q) {
-        B = B0;
-        rc = hstep_single<E>(ctx, B, n_s, H->grid.n_o, t);
-      }
-      hipEventRecord(e1, ctx->stream);
-      if (rc != SPARC_OK) break;
-      hipEventSynchronize(e1);
-      float ms = 0;
-      hipEventElapsedTime(&ms, e0, e1);
-      t_best = std::min(t_best, ms);
-    }
-    if (rc == SPARC_OK && t_best < best_ms) { best_ms = t_best; *best = t; }
+    StepArgs<E> B0 = trial_step(A);
+    nl_fill(H, B0, t, a, alpha, n_s);
+    float ms;
+    SPARC_TRY(tune_burst(H->ctx, [&]() {
+      StepArgs<E> B = B0;
+      return hstep_single<E>(H->ctx, B, n_s, H->grid.n_o, t);
+    }, &ms));
+    if (ms < best_ms) { best_ms = ms; *best = t; }
   }
-  ctx->timing = timing;
-  hipEventDestroy(e0);
-  hipEventDestroy(e1);
-  if (rc != SPARC_OK) return rc;
-  tune_store(H, n_s, *best);
+  tune_store(g_tune_cache, H, n_s, *best);
   return SPARC_OK;
 }
 
@@ -1229,6 +1215,21 @@ static bool row_tiled_better(const sparc_ham* H, const RowPlan& p, int64_t n_s) 
   return false;
 }
 
+// Plans worth a trial, the model's choice first: the cheapest pairs of
+// tile height and z chunk, up to four within a third of the best (the model's largest miss).
+constexpr size_t kRowTrials = 4;
+static std::vector<RowPlan> row_trials(const RowPlan& best, std::vector<RowPlan> all) {
+  std::vector<RowPlan> out{best};
+  std::stable_sort(all.begin(), all.end(), [](const RowPlan& x, const RowPlan& y) { return x.cost < y.cost; });
+  for (const RowPlan& p : all) {
+    if (out.size() == kRowTrials || p.cost > 1.34 * best.cost) break;
+    bool seen = false;
+    for (const RowPlan& q : out) seen = seen || (q.tyt == p.tyt && q.zchunk == p.zchunk);
+    if (!seen) out.push_back(p);
+  }
+  return out;
+}
+
 // plan of a single problem; the search is remembered per thread by the sizes it depends on
 static const RowPlan& row_single_plan(const sparc_ham* H, int32_t n_s) {
   struct Entry {
@@ -1250,9 +1251,26 @@ static const RowPlan& row_single_plan(const sparc_ham* H, int32_t n_s) {
   return e.plan;
 }
 
+template <typename E>
+static int row_autotune(sparc_ham* H, const StepArgs<E>& A, int32_t n_s, const RowPlan& model, RowPlan* best) {
+  const int cp = dtype_complex(H->dtype) ? 2 : 1, rb = real_bytes(H);
+  std::vector<RowPlan> all;
+  row_plan(A.n1, A.n2, A.n3, cp, rb, model.cfg.vx, model.cfg.vy, n_s, H->ctx->n_cu, kRowThreads, false, &all);
+  float best_ms = 1e30f;
+  for (const RowPlan& p : row_trials(model, all)) {
+    StepArgs<E> B = trial_step(A);
+    row_fill(B, p, n_s);
+    float ms;
+    SPARC_TRY(tune_burst(H->ctx, [&]() { return hrow_single<E>(H->ctx, B, p.cfg, p.wg(n_s)); }, &ms));
+    if (ms < best_ms) { best_ms = ms; *best = p; }
+  }
+  tune_store(g_row_tune, H, n_s, *best);
+  return SPARC_OK;
+}
+
 // Problems of one chunk width share a launch, and its work-group size: the one of the
 // group's largest problem.  Each is planned as if its launch were copies of it.
-static bool row_group_plan(sparc_ham* const* H, const int* n_s, const std::vector<int>& mem, int vx, int vy,
+static bool row_group_plan(sparc_ham* const* H, const int* n_s, const std::vector<int>& mem, int vx, int vy, int pick,
                            std::vector<RowPlan>& out) {
   const int cp = dtype_complex(H[0]->dtype) ? 2 : 1, rb = real_bytes(H[0]);
   double total = 0;
@@ -1262,17 +1280,25 @@ static bool row_group_plan(sparc_ham* const* H, const int* n_s, const std::vecto
     total += size(p);
     if (size(p) > size(big)) big = p;
   }
-  auto plan = [&](int p, int max_nt) {
+  auto plan = [&](int p, int max_nt, std::vector<RowPlan>* all = nullptr) {
     const sparc_grid& g = H[p]->grid;
     const int64_t ns = std::max<int64_t>(n_s[p], (int64_t)(total / (double)H[p]->n_d));
-    return row_plan(g.n[0], g.n[1], g.n[2], cp, rb, vx, vy, ns, H[p]->ctx->n_cu, max_nt, true);
+    return row_plan(g.n[0], g.n[1], g.n[2], cp, rb, vx, vy, ns, H[p]->ctx->n_cu, max_nt, true, all);
   };
-  int nt = plan(big, kRowThreads).cfg.nt;
+  RowPlan lead = plan(big, kRowThreads);
+  if (pick > 0) {
+    std::vector<RowPlan> all;
+    plan(big, kRowThreads, &all);
+    const std::vector<RowPlan> trials = row_trials(lead, all);
+    if ((size_t)pick >= trials.size()) return false;
+    lead = trials[pick];
+  }
+  int nt = lead.cfg.nt;
   for (int p : mem)
     if (plan(p, nt).cfg.vx == 0) nt = kRowThreads;   // a problem that needs more threads than the largest one
   RowCfg c{vx, vy, 1, 1, 0, 0};
   for (int p : mem) {
-    out[p] = plan(p, nt);
+    out[p] = pick > 0 && p == big ? lead : plan(p, nt);
     if (out[p].cfg.vx == 0) return false;
     c.hm = std::max(c.hm, out[p].cfg.hm);
     c.full = c.full && out[p].cfg.full;
@@ -1283,27 +1309,29 @@ static bool row_group_plan(sparc_ham* const* H, const int* n_s, const std::vecto
   return true;
 }
 
-bool row_batch_plan(sparc_ham* const* H, const int* n_s, int n, std::vector<RowPlan>* out) {
+bool row_batch_plan(sparc_ham* const* H, const int* n_s, int n, std::vector<RowPlan>* out, int pick) {
   const int cp = dtype_complex(H[0]->dtype) ? 2 : 1, rb = real_bytes(H[0]);
   std::map<int, std::pair<int, std::vector<int>>> group;   // by chunk width: rows per thread, members
+  int big = 0, big_vx = 0;
+  int64_t total = 0;
   for (int p = 0; p < n; ++p) {
     if (!row_form(H[p])) return false;
     int vx, vy;
     row_chunk(H[p]->grid.n[0], cp, rb, &vx, &vy);
     group[vx].first = vy;
     group[vx].second.push_back(p);
+    if (p == 0 || (double)H[p]->n_d * n_s[p] > (double)H[big]->n_d * n_s[big]) {
+      big = p;
+      big_vx = vx;
+    }
+    total += n_s[p];
   }
   out->assign(n, RowPlan());
   for (const auto& g : group)
-    if (!row_group_plan(H, n_s, g.second.second, g.first, g.second.first, *out)) return false;
+    if (!row_group_plan(H, n_s, g.second.second, g.first, g.second.first, g.first == big_vx ? pick : 0, *out))
+      return false;
   // the largest problem decides for the plan
-  int big = 0;
-  int64_t total = 0;
-  for (int p = 0; p < n; ++p) {
-    if ((double)H[p]->n_d * n_s[p] > (double)H[big]->n_d * n_s[big]) big = p;
-    total += n_s[p];
-  }
-  return !row_tiled_better(H[big], (*out)[big], total);
+  return pick > 0 || !row_tiled_better(H[big], (*out)[big], total);
 }
 
 template <typename E>
@@ -1344,8 +1372,11 @@ static int ham_step_t(sparc_ham* H, const void* x, int64_t ldx, const void* z, i
   if (row_form(H)) {
     // too few work-groups for a quarter of the CUs (one orbital of a small grid: a step takes
     // 7 us in either form) leave the point form below
-    const RowPlan& p = row_single_plan(H, n_s);
+    RowPlan p = row_single_plan(H, n_s);
     if (p.cfg.vx && !row_tiled_better(H, p, n_s) && p.wg(n_s) >= H->ctx->n_cu / 4) {
+      if (H->ctx->autotune && !tune_lookup(g_row_tune, H, n_s, &p) && !(flags & STEP_NO_TUNE) && z == nullptr &&
+          out != x)
+        SPARC_TRY(row_autotune(H, A, n_s, p, &p));
       row_fill(A, p, n_s);
       SPARC_TRY(hrow_single<E>(H->ctx, A, p.cfg, p.wg(n_s)));
       if (nonlocal) SPARC_TRY(nl_scatter(H, alpha, n_s, a, nullptr, out, ldo));
@@ -1358,7 +1389,7 @@ static int ham_step_t(sparc_ham* H, const void* x, int64_t ldx, const void* z, i
     if (nonlocal) SPARC_TRY(nl_scatter(H, alpha, n_s, a, nullptr, out, ldo));
     return SPARC_OK;
   }
-  if (H->ctx->autotune && !tuned_tile(H, n_s, &t) && !(flags & STEP_NO_TUNE) && z == nullptr && out != x)
+  if (H->ctx->autotune && !tune_lookup(g_tune_cache, H, n_s, &t) && !(flags & STEP_NO_TUNE) && z == nullptr && out != x)
     SPARC_TRY(autotune(H, A, n_s, &t, a, al));
   const bool fused = nl_fill(H, A, t, a, al, n_s);
   SPARC_TRY(hstep_single<E>(H->ctx, A, n_s, H->grid.n_o, t));

@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
+#include <vector>
 
 #include "devmath.hpp"
 
@@ -119,6 +120,7 @@ struct RowPlan {
   RowCfg cfg{};
   int txt = 0, tyt = 0, px = 0, tiles = 0, zchunk = 0, nz = 0;
   double dur = 0;   // modelled time of a work-group
+  double cost = 0;  // and of the launch, us
   int64_t wg(int n_s) const { return (int64_t)tiles * nz * n_s; }
 };
 
@@ -135,9 +137,9 @@ struct RowPlan {
 // over which the choice costs 3 % on average against the fastest pair (80^3 x 60 complex64 at
 // worst, 233 against 174 us; tiled form 241).
 // shared: the launch holds other problems too, so rounds need not be whole, and what is lost
-// is part of the last work-groups' time.
+// is part of the last work-groups' time.  all: every candidate is added to it.
 inline RowPlan row_plan(int n1, int n2, int n3, int cp, int rb, int vx, int vy, int64_t n_s, int n_cu, int max_nt,
-                        bool shared) {
+                        bool shared, std::vector<RowPlan>* all = nullptr) {
   RowPlan best;
   const int txt = n1 * cp / vx;
   const int hc = (kRowNO * cp + vx - 1) / vx;
@@ -171,16 +173,22 @@ inline RowPlan row_plan(int n1, int n2, int n3, int cp, int rb, int vx, int vy, 
       const double step = uneven * std::max((single ? 1.7 : 1.3) + 0.3e-3 * chunks, k * (rate * chunks + halo_rate * halo));
       const double rounds = shared ? std::max(1.0, r) + 0.7 : (r < 6 ? std::ceil(r) : r + 0.5);
       const double dur = (zc + 1) * step, cost = 2.0 + rounds * dur;
-      if (cost < best_cost * 0.999) {
-        best_cost = cost;
-        best.cfg = RowCfg{vx, vy, hm, full ? 1 : 0, nt, lds};
-        best.txt = txt;
-        best.tyt = tyt;
-        best.px = px;
-        best.tiles = tl;
-        best.zchunk = zc;
-        best.nz = nzr;
-        best.dur = dur / k;
+      if (all || cost < best_cost * 0.999) {
+        RowPlan p;
+        p.cfg = RowCfg{vx, vy, hm, full ? 1 : 0, nt, lds};
+        p.txt = txt;
+        p.tyt = tyt;
+        p.px = px;
+        p.tiles = tl;
+        p.zchunk = zc;
+        p.nz = nzr;
+        p.dur = dur / k;
+        p.cost = cost;
+        if (all) all->push_back(p);
+        if (cost < best_cost * 0.999) {
+          best_cost = cost;
+          best = p;
+        }
       }
       if (wg > 16 * (int64_t)n_cu) break;
     }

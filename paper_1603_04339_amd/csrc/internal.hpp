@@ -64,7 +64,7 @@ struct sparc_ctx {
   hipStream_t stream;
   int n_cu;
   double* scalars;  // device scratch for scalar results (64 doubles), owned by the context
-  bool autotune = false;  // time the stencil tile shapes on first use of a problem shape
+  bool autotune = false;  // time stencil plans and products on first use of a problem shape
   // optional kernel timing: HIP events recorded around launches on `stream`
   bool timing = false;
   struct TimeRec {
@@ -174,6 +174,32 @@ inline int check_launch(const char* what) {
 // kernel timing (setup.hip): begin returns a record index (or -1 when timing is off)
 int timer_begin(sparc_ctx* c, const char* name);
 void timer_end(sparc_ctx* c, int idx);
+// Shortest of two bursts of three calls of launch() on the context's stream, in ms, after a
+// warm-up call (the stencil tuners)
+template <typename F>
+int tune_burst(sparc_ctx* c, F&& launch, float* ms) {
+  hipEvent_t e0, e1;
+  SPARC_HIP(hipEventCreate(&e0));
+  SPARC_HIP(hipEventCreate(&e1));
+  const bool timing = c->timing;
+  c->timing = false;
+  *ms = 1e30f;
+  int rc = launch();
+  for (int r = 0; r < 2 && rc == SPARC_OK; ++r) {
+    hipEventRecord(e0, c->stream);
+    for (int q = 0; q < 3 && rc == SPARC_OK; ++q) rc = launch();
+    hipEventRecord(e1, c->stream);
+    if (rc != SPARC_OK) break;
+    hipEventSynchronize(e1);
+    float t = 0;
+    hipEventElapsedTime(&t, e0, e1);
+    if (t < *ms) *ms = t;
+  }
+  c->timing = timing;
+  hipEventDestroy(e0);
+  hipEventDestroy(e1);
+  return rc;
+}
 // context whose timer records this thread's GEMM launches, set for the duration of the call
 // that issues them (a context may be gone by the next one)
 extern thread_local sparc_ctx* g_timer_ctx;
@@ -329,11 +355,11 @@ int step_table_launch(sparc_ctx* ctx, sparc_dtype dt, int no, int tile, const vo
                       int n, int64_t total, int dir, size_t nl_lds = 0);
 // row form of the step (hstep_api.hpp): plans of n problems that share one launch (false:
 // some problem needs the tiled form), and the launch of such a table (hasz: every step of
-// it reads the recurrence operand)
-bool row_batch_plan(sparc_ham* const* H, const int* n_s, int n, std::vector<struct RowPlan>* out);
+// it reads the recurrence operand).  pick: the largest problem takes its pick-th plan by
+// modelled time (false past the last one worth a trial); the results are the same in all
+bool row_batch_plan(sparc_ham* const* H, const int* n_s, int n, std::vector<struct RowPlan>* out, int pick = 0);
 int row_table_launch(sparc_ctx* ctx, sparc_dtype dt, const struct RowCfg& c, const void* dev_table, const int* dev_wg,
                      int n, int64_t total, int hasz);
-int tuned_tile(sparc_ham* H, int32_t n_s, int* t);
 // stencil tile shapes (hstep_api.hpp): count and threads per work-group of shape t
 int tile_shape_count();
 int tile_shape_threads(int t);

@@ -35,6 +35,7 @@ inline double readback = 0.0;   // what small device-to-host copies return (in e
 inline std::vector<Launch> launches;
 inline std::vector<int> streams_made, events_made;   // the device of each
 inline int n_malloc = 0, n_memcpy = 0, n_sync = 0, n_event_sync = 0;
+inline float (*elapsed)() = nullptr;   // what the next pair of events is apart (1 ms without one)
 inline hipError_t last = hipSuccess;
 // registered by the library's constructors, which run before this program's own
 inline std::map<const void*, std::string>& kernels() {
@@ -190,4 +191,7 @@ FAKE_EXPORT hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
   return ((fake::Event*)e)->device == fake::device_of(s) ? hipSuccess : hipErrorInvalidHandle;
 }
 FAKE_EXPORT hipError_t hipEventSynchronize(hipEvent_t) { ++fake::n_event_sync; return hipSuccess; }
-FAKE_EXPORT hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 1.0f; return hipSuccess; }
+FAKE_EXPORT hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) {
+  *ms = fake::elapsed ? fake::elapsed() : 1.0f;
+  return hipSuccess;
+}
