@@ -154,12 +154,14 @@ struct sparc_ham {
   double gtap[3][8];    // FD gradient weights w~_p / h_s per direction, p = 1..n_o
   bool nl_fused;        // the stencil step applies the projectors (tables built)
   NlTileTable nlt[kNlTileShapes];
+  // projector update (empty where it never applies):
   int32_t* sup_mark;    // [n_sup] sup_idx, as ~g for nodes in several supports
   int64_t n_shared;     // nodes in several supports
   int32_t* sh_pts;      // their nodes, CSR, projectors and coefficients, as nl_pts .. ent_coef
   int32_t* sh_ptr;
   int32_t* sh_proj;
   void* sh_coef;
+  char* nl_mem;         // holds sup_ptr .. sh_coef
 };
 
 namespace sparc {

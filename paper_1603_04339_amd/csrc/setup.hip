@@ -234,6 +234,34 @@ static int upload(const std::vector<T>& h, T** d) {
   return SPARC_OK;
 }
 
+// Tables that share one allocation and one copy, each on a 256-byte boundary (an allocation and a
+// copy for each of the 16 cost about 15 us: creating a Hamiltonian of 24^3 with 8 atoms 0.65 ms, so
+// 0.41; 40^3 with 31 atoms 1.58 and 1.34)
+struct TableUpload {
+  struct Part {
+    const void* src;
+    size_t bytes, at;
+    char** dst;
+  };
+  std::vector<Part> parts;
+  size_t total = 0;
+  template <typename T>
+  void add(const std::vector<T>& h, T** d) {
+    parts.push_back({h.data(), h.size() * sizeof(T), total, (char**)d});
+    total += (h.size() * sizeof(T) + 255) / 256 * 256 + (h.empty() ? 256 : 0);
+  }
+  int run(char** mem) {
+    SPARC_HIP(hipMalloc((void**)mem, total));
+    std::vector<char> stage(total);
+    for (const Part& p : parts) {
+      if (p.bytes) memcpy(stage.data() + p.at, p.src, p.bytes);
+      *p.dst = *mem + p.at;
+    }
+    SPARC_HIP(hipMemcpy(*mem, stage.data(), total, hipMemcpyHostToDevice));
+    return SPARC_OK;
+  }
+};
+
 }  // namespace sparc
 
 using namespace sparc;
@@ -503,16 +531,24 @@ int sparc_ham_create(sparc_ctx* ctx, const sparc_grid* grid, const sparc_atoms* 
           cim[e] = T.vim[vi];
         }
   }
-  // nodes in the supports of several atoms, and their entries
-  std::vector<int32_t> sup_mark(T.sup_idx), sh_pts, sh_ptr, sh_proj;
+  // the projector scatter inside the stencil step, on request (SPARC_NL_FUSED=1): the
+  // separate projection and scatter kernels are the default, as fast or faster on the
+  // measured cells (FP64 within 2 %, FP32 and complex slower fused)
+  const char* fenv = getenv("SPARC_NL_FUSED");
+  const bool fuse = fenv && fenv[0] == '1';
+  H->nl_fused = H->n_proj > 0 && H->max_proj_per_atom <= 4 && fuse;
+  // what the projector update reads (where it applies): the support indices with the nodes of
+  // several supports marked, and those nodes with their entries
+  std::vector<int32_t> mark, sh_pts, sh_ptr, sh_proj;
   std::vector<double> shre, shim;
-  {
-    std::vector<char> times(nd, 0);
-    for (int32_t g : T.sup_idx) times[g] = (char)std::min(2, times[g] + 1);
-    for (int32_t& g : sup_mark)
-      if (times[g] > 1) g = ~g;
+  if (nl_update_applies(H)) {
+    mark = T.sup_idx;
+    for (int a = 0; a < H->n_atoms_nl; ++a)
+      for (int t = T.sup_ptr[a]; t < T.sup_ptr[a + 1]; ++t)
+        if (cnt[mark[t] + 1] > T.atom_pbeg[a + 1] - T.atom_pbeg[a]) mark[t] = ~mark[t];
     for (size_t i = 0; i < nl_pts.size(); ++i) {
-      if (times[nl_pts[i]] < 2) continue;
+      const int a = ent_key[nl_ptr[i]] >> 2;
+      if (cnt[nl_pts[i] + 1] == T.atom_pbeg[a + 1] - T.atom_pbeg[a]) continue;
       sh_pts.push_back(nl_pts[i]);
       sh_ptr.push_back((int32_t)sh_proj.size());
       for (int32_t e = nl_ptr[i]; e < nl_ptr[i + 1]; ++e) {
@@ -524,26 +560,30 @@ int sparc_ham_create(sparc_ctx* ctx, const sparc_grid* grid, const sparc_atoms* 
     sh_ptr.push_back((int32_t)sh_proj.size());
     H->n_shared = (int64_t)sh_pts.size();
   }
-  // the projector scatter inside the stencil step, on request (SPARC_NL_FUSED=1): the
-  // separate projection and scatter kernels are the default, as fast or faster on the
-  // measured cells (FP64 within 2 %, FP32 and complex slower fused)
-  const char* fenv = getenv("SPARC_NL_FUSED");
-  const bool fuse = fenv && fenv[0] == '1';
-  H->nl_fused = H->n_proj > 0 && H->max_proj_per_atom <= 4 && fuse;
   std::vector<char> pv, ec, gm, sc;
   pack(dtype, T.vre, T.vim, pv);
   pack(dtype, ere, eim, ec);
   pack(dtype, shre, shim, sc);
   std::vector<double> zeros(T.gamma.size(), 0.0);
   pack(dtype_single(dtype) ? SPARC_R32 : SPARC_R64, T.gamma, zeros, gm);
-  if ((rc = upload(T.sup_ptr, &H->sup_ptr)) || (rc = upload(T.sup_idx, &H->sup_idx)) ||
-      (rc = upload(T.atom_id, &H->nl_atom)) ||
-      (rc = upload(T.atom_pbeg, &H->atom_pbeg)) || (rc = upload(T.proj_voff, &H->proj_voff)) ||
-      (rc = upload(pv, (char**)&H->pval)) || (rc = upload(gm, (char**)&H->gamma_d)) ||
-      (rc = upload(nl_pts, &H->nl_pts)) || (rc = upload(nl_ptr, &H->nl_ptr)) || (rc = upload(ent_proj, &H->ent_proj)) ||
-      (rc = upload(ec, (char**)&H->ent_coef)) || (rc = upload(sup_mark, &H->sup_mark)) ||
-      (rc = upload(sh_pts, &H->sh_pts)) || (rc = upload(sh_ptr, &H->sh_ptr)) ||
-      (rc = upload(sh_proj, &H->sh_proj)) || (rc = upload(sc, (char**)&H->sh_coef))) {
+  TableUpload up;
+  up.add(T.sup_ptr, &H->sup_ptr);
+  up.add(T.sup_idx, &H->sup_idx);
+  up.add(T.atom_id, &H->nl_atom);
+  up.add(T.atom_pbeg, &H->atom_pbeg);
+  up.add(T.proj_voff, &H->proj_voff);
+  up.add(pv, (char**)&H->pval);
+  up.add(gm, (char**)&H->gamma_d);
+  up.add(nl_pts, &H->nl_pts);
+  up.add(nl_ptr, &H->nl_ptr);
+  up.add(ent_proj, &H->ent_proj);
+  up.add(ec, (char**)&H->ent_coef);
+  up.add(mark, &H->sup_mark);
+  up.add(sh_pts, &H->sh_pts);
+  up.add(sh_ptr, &H->sh_ptr);
+  up.add(sh_proj, &H->sh_proj);
+  up.add(sc, (char**)&H->sh_coef);
+  if ((rc = up.run(&H->nl_mem))) {
     sparc_ham_destroy(H);
     return rc;
   }
@@ -562,9 +602,8 @@ int sparc_ham_create(sparc_ctx* ctx, const sparc_grid* grid, const sparc_atoms* 
 
 void sparc_ham_destroy(sparc_ham* H) {
   if (!H) return;
-  void* ptrs[] = {H->vloc, H->veff, H->veff32, H->sup_ptr, H->sup_idx, H->atom_pbeg, H->proj_voff,
-                  H->pval, H->gamma_d, H->nl_pts, H->nl_ptr, H->ent_proj, H->ent_coef,
-                  H->sup_mark, H->sh_pts, H->sh_ptr, H->sh_proj, H->sh_coef, H->atom_R, H->atom_D, H->atom_W, H->force_part, H->nl_atom, H->zplane};
+  void* ptrs[] = {H->vloc,   H->veff,       H->veff32, H->nl_mem, H->atom_R, H->atom_D,
+                  H->atom_W, H->force_part, H->zplane};
   for (void* p : ptrs)
     if (p) hipFree(p);
   nl_tables_free(H);
