@@ -156,7 +156,9 @@ constexpr int kForceThreads = 512;
 // NO > 0: the stencil half-width, on grids without Dirichlet faces and with at least NO nodes
 // per direction: the taps' offsets and images are made once per node, and all taps of an
 // orbital are in flight together.  NO = 0: any.  Bound by the cache's rate for scattered
-// doubles.  64^3, 32 atoms, 128 states: 98 us, in the general form 304.
+// doubles.  64^3, 32 atoms, 128 states: 98 us, in the general form 304.  The call around it, complex
+// double, 48^3, 16 atoms, 128 states: 55 us, in the general form 187, and 306 with the taps in
+// scratch memory, where a select between whole complex values leaves them (so by parts).
 template <typename E, int MAXP, int NB, int NO>
 __global__ __launch_bounds__(kForceThreads) void force_nl_kernel(const E* __restrict__ x, int64_t ldx, int n_s,
                                                        const int32_t* __restrict__ sup_ptr,
@@ -252,10 +254,12 @@ __global__ __launch_bounds__(kForceThreads) void force_nl_kernel(const E* __rest
               for (int p = 0; p < NO; ++p) {
                 if constexpr (elem<E>::is_cplx) {
                   const E rp = rot(vp[p], rot_p[d].re, rot_p[d].im), rm = rot(vm[p], rot_m[d].re, rot_m[d].im);
-                  vp[p] = wp[p] ? rp : vp[p];
-                  vm[p] = wm[p] ? rm : vm[p];
+                  const E u = {wp[p] ? rp.re : vp[p].re, wp[p] ? rp.im : vp[p].im};
+                  const E v = {wm[p] ? rm.re : vm[p].re, wm[p] ? rm.im : vm[p].im};
+                  gs[j] = fmar(gs[j], (R)G.w[d][p], u - v);
+                } else {
+                  gs[j] = fmar(gs[j], (R)G.w[d][p], vp[p] - vm[p]);
                 }
-                gs[j] = fmar(gs[j], (R)G.w[d][p], vp[p] - vm[p]);
               }
             }
           }
