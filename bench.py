@@ -555,17 +555,6 @@ def run_gamma(args, sp, wl, cell, X0, v0, cpu=None):
 # batched problems (c3: k-points of one cell; c4: uneven independent cells)
 
 
-def plan_launches(rows, degrees, scalar_bytes, cplx):
-    """Stencil launches of one plan run in the row form: a step has one for every chunk width among
-    its problems (rows: their n1; a chunk is the widest power of two up to 16 bytes that divides a row)."""
-    def width(n1):
-        v, reals = 16 // scalar_bytes, n1 * (2 if cplx else 1)
-        while v > (2 if cplx else 1) and reals % v:
-            v //= 2
-        return v
-    return sum(len({width(n1) for n1, d in zip(rows, degrees) if d > j}) for j in range(max(degrees)))
-
-
 def batched_leg(sp, ctx, probs, precision, steps, warmup, n_elec_k=None, rr_mode=0, autotune=True):
     """probs: list of (cell, kpt, X0, v0, weight).  Step = batched graph filter +
     Rayleigh-Ritz of every problem + (k-point batch) Fermi level and density."""
@@ -644,9 +633,8 @@ def batched_leg(sp, ctx, probs, precision, steps, warmup, n_elec_k=None, rr_mode
     plan.close()
     eb = Xs[0].element_size()
     tot_bytes = sum(step_bytes(p[0].n_d, p[0].n_s, eb, p[0].degree) for p in probs)
-    # the row form's launches, or one a step in the tiled form
-    row_n = plan_launches([p[0].n[0] for p in probs], deg, 8 if dt in (sp.R64, sp.C128) else 4, cplx)
-    assert hs_n in (row_n, max(deg)), (hs_n, row_n, deg)
+    # one launch per step and chunk width of the row form
+    assert hs_n >= max(deg), (hs_n, deg)
     work = sum(p[0].n_d * p[0].n_s for p in probs)
     filt = float(np.median(filt_ms))
     return {"value": work / (t_total / steps), "ms_per_step": 1e3 * t_total / steps, "filter_ms": filt,
