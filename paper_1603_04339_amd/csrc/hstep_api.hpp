@@ -125,17 +125,19 @@ struct RowPlan {
 };
 
 // Tile height and z chunks for chunk shape (vx, vy); work-groups of at most max_nt threads.
-// The cost of a candidate is its rounds of resident work-groups (k per CU) times its plane
-// steps, a step taking the longer of its latency, 1.3 us + 0.3 ns per 16 bytes of the tile,
-// and the CU's rate, k times (1.9 ns per 16 bytes of the tile, 2.7 in chunks narrower than
-// that, + 0.43 ns per 16 bytes of its y halo; complex double, whose x taps read a chunk each,
-// 2.4 and 1.1); more than four waves that do not fill the four SIMDs evenly cost 12 %.  Chunks
-// of one float hold half the registers of the others, so four waves fit a SIMD instead of
-// three, and a step's latency is 1.7 us (55 blocks with rows of 21 to 91 nodes: the choice costs
-// 0.6 % on average, with the other chunks' numbers 10 %).  Fitted
-// to 1200 timed (tile, chunk) pairs of 41 blocks, 24^3 x 1 to 96^3 x 192 in all four types,
-// over which the choice costs 3 % on average against the fastest pair (80^3 x 60 complex64 at
-// worst, 233 against 174 us; tiled form 241).
+// The cost of a candidate is its rounds of resident work-groups (k per CU) times its plane steps (and
+// the prologue's).  A step takes the root of the squares of its latency, a base and a share per 16
+// bytes of the tile, more with fewer than eight waves on the CU, and of the CU's time for the tiles
+// of all k, by 16 bytes of tile and of y halo; more than four waves that do not fill the four SIMDs
+// evenly cost by how uneven they are, and the complex double form with masked lanes and two halo
+// chunks a thread, which spills, 1.6 times.  Chunks narrower than 16 bytes and complex double ones,
+// whose x taps read a chunk each, have rates of their own; chunks of one float hold half the
+// registers, so four waves fit a SIMD instead of three, and a latency of their own.
+// Fitted to 12300 timed (tile, chunk) pairs of 952 blocks from 16^3 x 2 to 96^3 x 512 in all four types.
+// Over these the choice costs 1.3 % on average against the fastest timed pair in FP64, 1.6 in FP32, 2.4
+// and 3.0 in complex double and single (with the longer of latency and rate in a step's place and
+// fixed prices for uneven waves 3.9 to 8.5 %: 80^3 x 60 FP64 207 us then and 179 now, tiled 180;
+// 48^3 x 384 FP32 160 and 126, tiled 156; 40^3 x 300 complex double 399 and 309, tiled 371).
 // shared: the launch holds other problems too, so rounds need not be whole, and what is lost
 // is part of the last work-groups' time.  all: every candidate is added to it.
 inline RowPlan row_plan(int n1, int n2, int n3, int cp, int rb, int vx, int vy, int64_t n_s, int n_cu, int max_nt,
@@ -146,7 +148,11 @@ inline RowPlan row_plan(int n1, int n2, int n3, int cp, int rb, int vx, int vy, 
   const int px = txt + 2 * hc;
   const size_t cb = (size_t)vx * rb;
   const bool c128 = cp == 2 && rb == 8, single = cb == 4;
-  const double rate = c128 ? 2.4e-3 : (cb < 16 ? 2.7e-3 : 1.9e-3), halo_rate = c128 ? 1.1e-3 : 0.43e-3;
+  // step latency, its growth and the CU's rates, us (per 16 bytes of the tile or its halo); the
+  // price of few waves and of uneven SIMDs; planes that a chunk's first loads cost
+  const double lat = single ? 1.45 : (c128 ? 1.55 : 1.1), lat_chunk = c128 ? 0.22e-3 : 0.26e-3;
+  const double rate = c128 ? 1.55e-3 : (cb < 16 ? 2.7e-3 : 1.9e-3), halo_rate = c128 ? 0.94e-3 : 0.43e-3;
+  const double few_waves = c128 ? 0.8 : 0.4, uneven_simds = c128 ? 1.0 : 0.5, prologue = c128 ? 2.0 : 1.0;
   double best_cost = 1e300;
   int last = 0;
   for (int tiles = 1; tiles <= n2; ++tiles) {
@@ -163,16 +169,18 @@ inline RowPlan row_plan(int n1, int n2, int n3, int cp, int rb, int vx, int vy, 
     const int64_t occ = std::max(1, std::min<int>((single ? 16 : 12) / (nt / 64), (int)(kRowLds / lds)));
     const double chunks = (double)nt * vy * (double)cb / 16.0, halo = 2.0 * kRowNO * txt * (double)cb / 16.0;
     const bool full = n2 % ty == 0 && txt * tyt == nt;
-    // (the complex double form with masked lanes and two halo chunks a thread spills)
-    const double uneven = (nt > 256 && nt % 256 ? 1.12 : 1.0) * (c128 && hm == 2 && !full ? 1.2 : 1.0);
+    const double simd = (nt + 255) / 256 * 256.0 / nt;   // waves of the fullest SIMD to the average
+    const double slow = (nt > 256 ? 1.0 + uneven_simds * (simd - 1.0) : 1.0) * (c128 && hm == 2 && !full ? 1.6 : 1.0);
     for (int nz = 1; nz == 1 || n3 / nz >= 3; ++nz) {
       const int zc = (n3 + nz - 1) / nz, nzr = (n3 + zc - 1) / zc;
       const int64_t wg = (int64_t)tl * nzr * n_s;
       const int64_t k = std::max<int64_t>(1, std::min<int64_t>(occ, (wg + n_cu - 1) / n_cu));
       const double r = (double)wg / ((double)n_cu * k);
-      const double step = uneven * std::max((single ? 1.7 : 1.3) + 0.3e-3 * chunks, k * (rate * chunks + halo_rate * halo));
+      const double few = 1.0 + few_waves * std::max(0.0, 1.0 - k * nt / 512.0);
+      const double step =
+          slow * std::hypot(few * (lat + lat_chunk * chunks), k * (rate * chunks + halo_rate * halo));
       const double rounds = shared ? std::max(1.0, r) + 0.7 : (r < 6 ? std::ceil(r) : r + 0.5);
-      const double dur = (zc + 1) * step, cost = 2.0 + rounds * dur;
+      const double dur = (zc + prologue) * step, cost = 2.0 + rounds * dur;
       if (all || cost < best_cost * 0.999) {
         RowPlan p;
         p.cfg = RowCfg{vx, vy, hm, full ? 1 : 0, nt, lds};
