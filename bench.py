@@ -633,13 +633,12 @@ def batched_leg(sp, ctx, probs, precision, steps, warmup, n_elec_k=None, rr_mode
     plan.close()
     eb = Xs[0].element_size()
     tot_bytes = sum(step_bytes(p[0].n_d, p[0].n_s, eb, p[0].degree) for p in probs)
-    # one launch per step and chunk width of the row form
-    assert hs_n >= max(deg), (hs_n, deg)
+    assert hs_n == max(deg), (hs_n, deg)
     work = sum(p[0].n_d * p[0].n_s for p in probs)
     filt = float(np.median(filt_ms))
     return {"value": work / (t_total / steps), "ms_per_step": 1e3 * t_total / steps, "filter_ms": filt,
             "filter_throughput": work / (filt * 1e-3),
-            "roofline": roofline_obj("hstep batched over all problems (one launch per recurrence step and chunk width)",
+            "roofline": roofline_obj("hstep batched over all problems (one launch per recurrence step)",
                                      tot_bytes, hs_ms, hs_n), "dtype": {sp.R64: "f64", sp.R32: "f32",
                                                                         sp.C128: "c128", sp.C64: "c64"}[dt]}
 

@@ -71,28 +71,18 @@ static int scatter_nb(const sparc_filter_plan* P, int j) {
   return P->update && j + 1 < P->max_deg ? kSharedNB : kScatterNB;
 }
 
-// step j of the row form: one launch per chunk width (the step's problems are in that order)
+// step j of the row form
 static int row_step(sparc_filter_plan* P, int j, int hasz) {
-  const auto& mem = P->members[j];
-  const int* wg = P->host_wg.data() + P->wg_off[j];
-  for (size_t a = 0, b; a < mem.size(); a = b) {
-    const RowCfg& c = P->row[mem[a]].cfg;
-    for (b = a + 1; b < mem.size() && P->row[mem[b]].cfg.vx == c.vx;) ++b;
-    SPARC_TRY(row_table_launch(P->ctx, P->dt, c, P->dev_tables + P->table_off[j] + a * step_args_bytes(P->dt),
-                               P->dev_wg + P->wg_off[j] + a, (int)(b - a), wg[b] - wg[a], hasz));
-  }
-  return SPARC_OK;
+  return row_table_launch(P->ctx, P->dt, P->row[0].cfg, P->dev_tables + P->table_off[j], P->dev_wg + P->wg_off[j],
+                          (int)P->members[j].size(), P->total_wg[j], hasz);
 }
 
-// the problems of each step; in the row form by chunk width, and long work-groups first
+// the problems of each step; in the row form long work-groups first
 static void plan_members(sparc_filter_plan* P) {
   std::vector<int> order(P->n_prob);
   for (int p = 0; p < P->n_prob; ++p) order[p] = p;
   if (!P->row.empty())
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
-      const RowPlan &x = P->row[a], &y = P->row[b];
-      return x.cfg.vx != y.cfg.vx ? x.cfg.vx > y.cfg.vx : x.dur > y.dur;
-    });
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return P->row[a].dur > P->row[b].dur; });
   P->members.assign(P->max_deg, {});
   for (int j = 0; j < P->max_deg; ++j)
     for (int p : order)
@@ -231,6 +221,7 @@ static int plan_trial(sparc_filter_plan* P, int t, float* ms) {
   size_t lds = 0;
   const int64_t tot = step_table_build(hs.data(), d.data(), n, t, tab, wg, &lds);
   if (tot < 0) return fail(SPARC_EINVAL, "filter plan: bad dtype");
+  P->total_wg[0] = tot;
   SPARC_HIP(hipMemcpyAsync(P->dev_tables + P->table_off[0], tab, tab_bytes, hipMemcpyHostToDevice, ctx->stream));
   SPARC_HIP(hipMemcpyAsync(P->dev_wg + P->wg_off[0], wg, (size_t)(n + 1) * sizeof(int), hipMemcpyHostToDevice,
                            ctx->stream));

@@ -1193,7 +1193,7 @@ static bool row_form(const sparc_ham* H) {
 
 static int real_bytes(const sparc_ham* H) { return dtype_single(H->dtype) ? 4 : 8; }
 
-// Where the tiled form is faster than plan p for n_s orbitals on a full
+// Where the tiled form is faster than plan p, in chunks of vx values, for n_s orbitals on a full
 // chip.  FP32 rows of 41 to 47 nodes, moved in chunks of one or two floats, where 48 x 8 tiles cover
 // the plane with less than an eighth (a tenth) to spare (43 x 47 x 41, 82 orbitals: tiled 32, rows 34
 // us; 47 x 44^2, 200: 73 and 88; 43 x 44^2, a seventh to spare: 34 and 29; with 30 orbitals 22 and 17;
@@ -1207,20 +1207,28 @@ static int real_bytes(const sparc_ham* H) { return dtype_single(H->dtype) ? 4 : 
 // 32 by at most 24 nodes with more than 2.4 million values, which leave a CU one or two row tiles
 // (11 blocks: tiled takes 0.91 of the time on average, 0.77 to 1.16; 32 x 20 x 31 with 512 orbitals
 // 0.77; past 24 rows 1.06 to 1.16).
-static bool row_tiled_better(const sparc_ham* H, const RowPlan& p, int64_t n_s) {
+static bool row_tiled_better(const sparc_ham* H, const RowPlan& p, int vx, int64_t n_s) {
   const sparc_grid& g = H->grid;
   const int64_t n1 = g.n[0], n2 = g.n[1], rows8 = (n2 + 7) / 8 * 8;
   const double values = (double)H->n_d * (double)n_s;
-  if (H->dtype == SPARC_R32 && p.cfg.vx == 1 && n1 <= 32 && p.cfg.hm == 2 && values > 4e6) return true;
+  if (H->dtype == SPARC_R32 && vx == 1 && n1 <= 32 && p.cfg.hm == 2 && values > 4e6) return true;
   if (H->dtype == SPARC_C128 && n1 >= 28 && n1 <= 32 && n2 <= 24 && values > 2.4e6) return true;
   if (values <= 5e6) return false;
-  if (H->dtype == SPARC_R32 && p.cfg.vx < 4) {
-    const int64_t part = p.cfg.vx == 1 ? 8 : 10;
+  if (H->dtype == SPARC_R32 && vx < 4) {
+    const int64_t part = vx == 1 ? 8 : 10;
     return n1 > 40 && n1 < 48 && n2 <= 64 && part * n1 * n2 > (part - 1) * 48 * rows8;
   }
   if (H->dtype == SPARC_C128)
     return p.cfg.hm == 2 && !p.cfg.full && n1 > 56 && n1 <= 64 && 4 * n1 * n2 > 3 * 64 * rows8;
   return false;
+}
+
+// FP32 plans of several chunk widths, nearly all in chunks of one or two floats, whose kernel has
+// the registers of the widest: 2 to 8 million values take the tiled form (11 plans: 0.82 to 1.18 of
+// the time, 0.95 on average; below, where neither fills the chip, 1.01 to 1.31; with less than four
+// fifths of the values in narrow chunks 1.14 on average).
+static bool row_mixed_tiled(sparc_dtype dt, double values, double narrow) {
+  return dt == SPARC_R32 && narrow > 0.8 * values && values > 2e6 && values < 8e6;
 }
 
 // Plans worth a trial, the model's choice first: the cheapest pairs of
@@ -1253,7 +1261,7 @@ static const RowPlan& row_single_plan(const sparc_ham* H, int32_t n_s) {
     const int cp = dtype_complex(H->dtype) ? 2 : 1, rb = real_bytes(H);
     int vx, vy;
     row_chunk(key[0], cp, rb, &vx, &vy);
-    e.plan = row_plan(key[0], key[1], key[2], cp, rb, vx, vy, n_s, H->ctx->n_cu, kRowThreads, false);
+    e.plan = row_plan(key[0], key[1], key[2], cp, rb, vx, vy, n_s, H->ctx->n_cu);
     std::copy(key, key + 6, e.key);
   }
   return e.plan;
@@ -1263,7 +1271,7 @@ template <typename E>
 static int row_autotune(sparc_ham* H, const StepArgs<E>& A, int32_t n_s, const RowPlan& model, RowPlan* best) {
   const int cp = dtype_complex(H->dtype) ? 2 : 1, rb = real_bytes(H);
   std::vector<RowPlan> all;
-  row_plan(A.n1, A.n2, A.n3, cp, rb, model.cfg.vx, model.cfg.vy, n_s, H->ctx->n_cu, kRowThreads, false, &all);
+  row_plan(A.n1, A.n2, A.n3, cp, rb, model.cfg.vx, model.cfg.vy, n_s, H->ctx->n_cu, RowLaunch(), &all);
   float best_ms = 1e30f;
   for (const RowPlan& p : row_trials(model, all)) {
     StepArgs<E> B = trial_step(A);
@@ -1276,70 +1284,91 @@ static int row_autotune(sparc_ham* H, const StepArgs<E>& A, int32_t n_s, const R
   return SPARC_OK;
 }
 
-// Problems of one chunk width share a launch, and its work-group size: the one of the
-// group's largest problem.  Each is planned as if its launch were copies of it.
-static bool row_group_plan(sparc_ham* const* H, const int* n_s, const std::vector<int>& mem, int vx, int vy, int pick,
-                           std::vector<RowPlan>& out) {
-  const int cp = dtype_complex(H[0]->dtype) ? 2 : 1, rb = real_bytes(H[0]);
-  double total = 0;
-  int big = mem[0];
-  auto size = [&](int p) { return (double)H[p]->n_d * n_s[p]; };
-  for (int p : mem) {
-    total += size(p);
-    if (size(p) > size(big)) big = p;
-  }
-  auto plan = [&](int p, int max_nt, std::vector<RowPlan>* all = nullptr) {
-    const sparc_grid& g = H[p]->grid;
-    const int64_t ns = std::max<int64_t>(n_s[p], (int64_t)(total / (double)H[p]->n_d));
-    return row_plan(g.n[0], g.n[1], g.n[2], cp, rb, vx, vy, ns, H[p]->ctx->n_cu, max_nt, true, all);
-  };
-  RowPlan lead = plan(big, kRowThreads);
-  if (pick > 0) {
-    std::vector<RowPlan> all;
-    plan(big, kRowThreads, &all);
-    const std::vector<RowPlan> trials = row_trials(lead, all);
-    if ((size_t)pick >= trials.size()) return false;
-    lead = trials[pick];
-  }
-  int nt = lead.cfg.nt;
-  for (int p : mem)
-    if (plan(p, nt).cfg.vx == 0) nt = kRowThreads;   // a problem that needs more threads than the largest one
-  RowCfg c{vx, vy, 1, 1, 0, 0};
-  for (int p : mem) {
-    out[p] = pick > 0 && p == big ? lead : plan(p, nt);
-    if (out[p].cfg.vx == 0) return false;
-    c.hm = std::max(c.hm, out[p].cfg.hm);
-    c.full = c.full && out[p].cfg.full;
-    c.nt = std::max(c.nt, out[p].cfg.nt);
-    c.lds = std::max(c.lds, out[p].cfg.lds);
-  }
-  for (int p : mem) out[p].cfg = c;
-  return true;
-}
-
+// The problems of a plan share a launch, and its work-group size.  Each is planned as if the
+// launch were copies of it.  Problems of several chunk widths go together too: 94 such plans of 2 to
+// 5 problems take 10 % less time in FP64, 12 % in FP32 and 9 % in complex single than with a launch
+// for each width, which was slower than the tiled form for every third of them (four blocks of 63 x 63 x
+// 37 to 42 x 50 x 37, FP64, 20 steps: 1137 us, in one launch 1006, tiled 1160; 40^3 x 30, 41 x 40^2 x 30
+// and 17 x 18 x 19 x 10 1388, 1195, 1119).
 bool row_batch_plan(sparc_ham* const* H, const int* n_s, int n, std::vector<RowPlan>* out, int pick) {
   const int cp = dtype_complex(H[0]->dtype) ? 2 : 1, rb = real_bytes(H[0]);
-  std::map<int, std::pair<int, std::vector<int>>> group;   // by chunk width: rows per thread, members
-  int big = 0, big_vx = 0;
-  int64_t total = 0;
-  for (int p = 0; p < n; ++p) {
-    if (!row_form(H[p])) return false;
+  double total = 0, narrow = 0;
+  int big = 0;
+  bool uneven = false, mixed = false;   // grids, chunk widths differ
+  auto size = [&](int p) { return (double)H[p]->n_d * n_s[p]; };
+  auto same_grid = [&](int p, int q) { return std::equal(H[p]->grid.n, H[p]->grid.n + 3, H[q]->grid.n); };
+  auto width = [&](int p) {
     int vx, vy;
     row_chunk(H[p]->grid.n[0], cp, rb, &vx, &vy);
-    group[vx].first = vy;
-    group[vx].second.push_back(p);
-    if (p == 0 || (double)H[p]->n_d * n_s[p] > (double)H[big]->n_d * n_s[big]) {
-      big = p;
-      big_vx = vx;
-    }
-    total += n_s[p];
+    return vx;
+  };
+  for (int p = 0; p < n; ++p) {
+    if (!row_form(H[p])) return false;
+    total += size(p);
+    if (width(p) * rb < 16) narrow += size(p);
+    if (size(p) > size(big)) big = p;
+    uneven = uneven || !same_grid(p, 0);
+    mixed = mixed || width(p) != width(0);
   }
+  auto plan = [&](int p, int nt, std::vector<RowPlan>* all = nullptr) {
+    const sparc_grid& g = H[p]->grid;
+    const int64_t ns = std::max<int64_t>(n_s[p], (int64_t)(total / (double)H[p]->n_d));
+    int vx, vy;
+    row_chunk(g.n[0], cp, rb, &vx, &vy);
+    RowLaunch launch{nt ? nt : kRowThreads, nt, uneven, mixed};
+    return row_plan(g.n[0], g.n[1], g.n[2], cp, rb, vx, vy, ns, H[p]->ctx->n_cu, launch, all);
+  };
+  // the threads of a work-group: of those that the problems would take by themselves, the ones
+  // that cost the launch least
+  std::vector<RowPlan> best(n), trial(n);
+  double best_cost = 1e300;
+  auto consider = [&](int nt) {
+    double cost = 0;
+    for (int p = 0; p < n; ++p) {
+      const int q = p > 0 && same_grid(p, p - 1) ? p - 1 : -1;
+      trial[p] = q >= 0 ? trial[q] : plan(p, nt);
+      if (trial[p].cfg.vx == 0) return;
+      cost += size(p) * trial[p].cost;
+    }
+    if (cost < best_cost) {
+      best_cost = cost;
+      best = trial;
+    }
+  };
+  std::vector<int> sizes;
+  for (int p = 0; p < n; ++p)
+    if (p == 0 || !same_grid(p, p - 1)) sizes.push_back(plan(p, 0).cfg.nt);
+  std::sort(sizes.begin(), sizes.end());
+  sizes.erase(std::unique(sizes.begin(), sizes.end()), sizes.end());
+  for (int nt : sizes)
+    if (nt > 0) consider(nt);
+  if (best_cost == 1e300) consider(kRowThreads);
+  if (best_cost == 1e300) return false;
+  if (pick > 0) {
+    std::vector<RowPlan> all;
+    plan(big, best[big].cfg.nt, &all);
+    const std::vector<RowPlan> trials = row_trials(best[big], all);
+    if ((size_t)pick >= trials.size()) return false;
+    best[big] = trials[pick];
+  }
+  RowCfg c{mixed ? 0 : width(0), best[0].cfg.vy, 1, 1, 0, 0};
+  int64_t states = 0;
+  for (int p = 0; p < n; ++p) {
+    const RowCfg& q = best[p].cfg;
+    c.hm = std::max(c.hm, q.hm);
+    c.full = c.full && q.full;
+    c.nt = std::max(c.nt, q.nt);
+    c.lds = std::max(c.lds, q.lds);
+    states += n_s[p];
+  }
+  const bool tiled = row_tiled_better(H[big], best[big], width(big), states) ||
+                     (mixed && row_mixed_tiled(H[0]->dtype, total, narrow));
   out->assign(n, RowPlan());
-  for (const auto& g : group)
-    if (!row_group_plan(H, n_s, g.second.second, g.first, g.second.first, g.first == big_vx ? pick : 0, *out))
-      return false;
-  // the largest problem decides for the plan
-  return pick > 0 || !row_tiled_better(H[big], (*out)[big], total);
+  for (int p = 0; p < n; ++p) {
+    (*out)[p] = best[p];
+    (*out)[p].cfg = c;
+  }
+  return pick > 0 || !tiled;
 }
 
 template <typename E>
@@ -1381,7 +1410,7 @@ static int ham_step_t(sparc_ham* H, const void* x, int64_t ldx, const void* z, i
     // too few work-groups for a quarter of the CUs (one orbital of a small grid: a step takes
     // 7 us in either form) leave the point form below
     RowPlan p = row_single_plan(H, n_s);
-    if (p.cfg.vx && !row_tiled_better(H, p, n_s) && p.wg(n_s) >= H->ctx->n_cu / 4) {
+    if (p.cfg.vx && !row_tiled_better(H, p, p.cfg.vx, n_s) && p.wg(n_s) >= H->ctx->n_cu / 4) {
       if (H->ctx->autotune && !tune_lookup(g_row_tune, H, n_s, &p) && !(flags & STEP_NO_TUNE) && z == nullptr &&
           out != x)
         SPARC_TRY(row_autotune(H, A, n_s, p, &p));

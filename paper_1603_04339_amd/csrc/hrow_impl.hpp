@@ -339,11 +339,11 @@ __global__ __launch_bounds__(kRowThreads) void hrow_kernel(StepArgs<E> A) {
 // Several problems in one launch.  Problem p has the work-groups wg_off[p] <= b <
 // wg_off[p+1], padded to a multiple of 8 (the offsets start at wg_off[0]: problems further
 // down a table): every XCD takes a contiguous eighth of each problem, so that problems
-// whose work-groups take longer than the others' load all of them alike.
-template <typename E, int VX, int VY, int HM, bool FULL, bool HASZ>
-__global__ __launch_bounds__(kRowThreads) void hrow_batched_kernel(const StepArgs<E>* __restrict__ probs,
-                                                                   const int* __restrict__ wg_off, int n_probs) {
-  extern __shared__ __align__(16) char row_lds[];
+// whose work-groups take longer than the others' load all of them alike.  Returns the
+// work-group's problem and its index there.
+template <typename E>
+__device__ __forceinline__ const StepArgs<E>& row_problem(const StepArgs<E>* __restrict__ probs,
+                                                          const int* __restrict__ wg_off, int n_probs, int64_t* L) {
   const int xcd = blockIdx.x & 7, b = wg_off[0] + (int)(blockIdx.x & ~7u);
   int lo = 0, hi = n_probs - 1;
   while (lo < hi) {
@@ -351,10 +351,35 @@ __global__ __launch_bounds__(kRowThreads) void hrow_batched_kernel(const StepArg
     if (wg_off[mid] <= b) lo = mid;
     else hi = mid - 1;
   }
-  const StepArgs<E>& A = probs[lo];
-  const int64_t L = (int64_t)xcd * ((wg_off[lo + 1] - wg_off[lo]) >> 3) + ((b - wg_off[lo]) >> 3);
+  *L = (int64_t)xcd * ((wg_off[lo + 1] - wg_off[lo]) >> 3) + ((b - wg_off[lo]) >> 3);
+  return probs[lo];
+}
+
+template <typename E, int VX, int VY, int HM, bool FULL, bool HASZ>
+__global__ __launch_bounds__(kRowThreads) void hrow_batched_kernel(const StepArgs<E>* __restrict__ probs,
+                                                                   const int* __restrict__ wg_off, int n_probs) {
+  extern __shared__ __align__(16) char row_lds[];
+  int64_t L;
+  const StepArgs<E>& A = row_problem(probs, wg_off, n_probs, &L);
   if (L >= (int64_t)A.tiles * A.nz * A.ns) return;
   hrow_body<E, VX, VY, HM, FULL, HASZ>(A, L, (A.txt * A.tyt + 63) / 64 * 64, row_lds);
+}
+
+// Problems of several chunk widths in one launch: the width is its problem's for all of a work-group.
+template <typename E, bool HASZ>
+__global__ __launch_bounds__(kRowThreads) void hrow_mixed_kernel(const StepArgs<E>* __restrict__ probs,
+                                                                 const int* __restrict__ wg_off, int n_probs) {
+  extern __shared__ __align__(16) char row_lds[];
+  constexpr int CP = elem<E>::is_cplx ? 2 : 1, WIDE = 16 / (int)sizeof(typename elem<E>::real);
+  int64_t L;
+  const StepArgs<E>& A = row_problem(probs, wg_off, n_probs, &L);
+  if (L >= (int64_t)A.tiles * A.nz * A.ns) return;
+  const int nt = (A.txt * A.tyt + 63) / 64 * 64, vx = A.n1 * CP / A.txt;
+  if (vx == WIDE) hrow_body<E, WIDE, 2, 2, false, HASZ>(A, L, nt, row_lds);
+  if constexpr (WIDE / 2 >= CP)
+    if (vx == WIDE / 2) hrow_body<E, WIDE / 2, 4, 2, false, HASZ>(A, L, nt, row_lds);
+  if constexpr (WIDE / 4 >= CP)
+    if (vx == WIDE / 4) hrow_body<E, WIDE / 4, 4, 2, false, HASZ>(A, L, nt, row_lds);
 }
 
 // a kernel's dynamic LDS limit, raised once per device (the kernel is the template's argument:
@@ -388,6 +413,17 @@ static int row_launch(sparc_ctx* ctx, const StepArgs<E>* one, const void* probs,
   }
   timer_end(ctx, t);
   return check_launch("hrow_kernel");
+}
+
+template <typename E, bool HASZ>
+static int row_mixed_launch(sparc_ctx* ctx, const void* probs, const int* wg, int n, int64_t total, const RowCfg& c) {
+  if (total > (int64_t)INT32_MAX) return fail(SPARC_ESHAPE, "stencil step: too many work-groups");
+  constexpr auto k = hrow_mixed_kernel<E, HASZ>;
+  SPARC_TRY(row_lds_limit<k>(ctx->device));
+  const int t = timer_begin(ctx, "hstep");
+  k<<<(unsigned)total, c.nt, c.lds, ctx->stream>>>((const StepArgs<E>*)probs, wg, n);
+  timer_end(ctx, t);
+  return check_launch("hrow_mixed_kernel");
 }
 
 template <typename E, int VX, int VY>
@@ -426,6 +462,10 @@ int hrow_single(sparc_ctx* ctx, const StepArgs<E>& A, const RowCfg& c, int64_t t
 template <typename E>
 int hrow_batched(sparc_ctx* ctx, const void* dprobs, const int* dwg, int n, int64_t total, const RowCfg& c, int hasz) {
   if (total <= 0) return SPARC_OK;
+  if constexpr (!(elem<E>::is_cplx && sizeof(typename elem<E>::real) == 8))   // (one width)
+    if (c.vx == 0)
+      return hasz ? row_mixed_launch<E, true>(ctx, dprobs, dwg, n, total, c)
+                  : row_mixed_launch<E, false>(ctx, dprobs, dwg, n, total, c);
   return row_any<E>(ctx, nullptr, dprobs, dwg, n, total, c, hasz);
 }
 

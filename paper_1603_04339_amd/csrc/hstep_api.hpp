@@ -97,7 +97,7 @@ constexpr int kRowNO = 6;          // stencil half-width of the row form's kerne
 constexpr int kRowThreads = 768;   // most threads of a row-form work-group (168 registers each)
 constexpr size_t kRowLds = 163840; // LDS of a CU
 struct RowCfg {
-  int vx, vy;   // reals along x and rows per thread
+  int vx, vy;   // reals along x and rows per thread (vx = 0: problems of several widths)
   int hm;       // y-halo chunks per thread (1 or 2)
   int full;     // every thread and every row of every tile is inside the grid
   int nt;       // threads per work-group
@@ -124,7 +124,15 @@ struct RowPlan {
   int64_t wg(int n_s) const { return (int64_t)tiles * nz * n_s; }
 };
 
-// Tile height and z chunks for chunk shape (vx, vy); work-groups of at most max_nt threads.
+// What a launch of several problems imposes on the plan of one of them.
+struct RowLaunch {
+  int max_nt = kRowThreads;   // most threads of a work-group
+  int nt = 0;                 // the launch's threads per work-group (0: the plan's own)
+  bool uneven = false;        // grids differ
+  bool mixed = false;         // chunk widths differ: one kernel, with the registers of all
+};
+
+// Tile height and z chunks for chunk shape (vx, vy).
 // The cost of a candidate is its rounds of resident work-groups (k per CU) times its plane steps (and
 // the prologue's).  A step takes the root of the squares of its latency, a base and a share per 16
 // bytes of the tile, more with fewer than eight waves on the CU, and of the CU's time for the tiles
@@ -138,10 +146,10 @@ struct RowPlan {
 // and 3.0 in complex double and single (with the longer of latency and rate in a step's place and
 // fixed prices for uneven waves 3.9 to 8.5 %: 80^3 x 60 FP64 207 us then and 179 now, tiled 180;
 // 48^3 x 384 FP32 160 and 126, tiled 156; 40^3 x 300 complex double 399 and 309, tiled 371).
-// shared: the launch holds other problems too, so rounds need not be whole, and what is lost
-// is part of the last work-groups' time.  all: every candidate is added to it.
-inline RowPlan row_plan(int n1, int n2, int n3, int cp, int rb, int vx, int vy, int64_t n_s, int n_cu, int max_nt,
-                        bool shared, std::vector<RowPlan>* all = nullptr) {
+// Launches of uneven grids: rounds need not be whole, and what is lost is part of the last
+// work-groups' time.  all: every candidate is added to it.
+inline RowPlan row_plan(int n1, int n2, int n3, int cp, int rb, int vx, int vy, int64_t n_s, int n_cu,
+                        const RowLaunch& launch = RowLaunch(), std::vector<RowPlan>* all = nullptr) {
   RowPlan best;
   const int txt = n1 * cp / vx;
   const int hc = (kRowNO * cp + vx - 1) / vx;
@@ -161,12 +169,13 @@ inline RowPlan row_plan(int n1, int n2, int n3, int cp, int rb, int vx, int vy, 
     last = ty;
     const int tyt = ty / vy, tl = (n2 + ty - 1) / ty;
     const int nt = (txt * tyt + 63) / 64 * 64;
-    if (nt > max_nt) continue;
+    if (nt > launch.max_nt) continue;
     const int hm = (2 * kRowNO * txt + nt - 1) / nt;
     if (hm > 2) break;   // lower tiles need more
     const size_t lds = (size_t)(2 * (ty + 2 * kRowNO) * px + 1) * cb;
     if (lds > kRowLds) continue;
-    const int64_t occ = std::max(1, std::min<int>((single ? 16 : 12) / (nt / 64), (int)(kRowLds / lds)));
+    const int64_t occ = std::max(1, std::min<int>((single && !launch.mixed ? 16 : 12) / (std::max(nt, launch.nt) / 64),
+                                                  (int)(kRowLds / lds)));
     const double chunks = (double)nt * vy * (double)cb / 16.0, halo = 2.0 * kRowNO * txt * (double)cb / 16.0;
     const bool full = n2 % ty == 0 && txt * tyt == nt;
     const double simd = (nt + 255) / 256 * 256.0 / nt;   // waves of the fullest SIMD to the average
@@ -179,7 +188,7 @@ inline RowPlan row_plan(int n1, int n2, int n3, int cp, int rb, int vx, int vy, 
       const double few = 1.0 + few_waves * std::max(0.0, 1.0 - k * nt / 512.0);
       const double step =
           slow * std::hypot(few * (lat + lat_chunk * chunks), k * (rate * chunks + halo_rate * halo));
-      const double rounds = shared ? std::max(1.0, r) + 0.7 : (r < 6 ? std::ceil(r) : r + 0.5);
+      const double rounds = launch.uneven ? std::max(1.0, r) + 0.3 : (r < 6 ? std::ceil(r) : r + 0.5);
       const double dur = (zc + prologue) * step, cost = 2.0 + rounds * dur;
       if (all || cost < best_cost * 0.999) {
         RowPlan p;
