@@ -21,14 +21,14 @@ namespace sparc {
 // in one vector load.
 template <typename E, int NB>
 __device__ __forceinline__ void nl_scatter_body(int i, int nb0, int n_pts, const int32_t* __restrict__ pts,
-                                                const int32_t* __restrict__ ptr,
+                                                const int32_t* __restrict__ beg, const int32_t* __restrict__ end,
                                                 const int32_t* __restrict__ ent_proj,
                                                 const E* __restrict__ ent_coef, const E* __restrict__ alpha,
                                                 int lda, int n_s, typename elem<E>::real a, E* __restrict__ y,
                                                 int64_t ldy) {
   if (i >= n_pts) return;
   const int64_t g = pts[i];
-  const int e0 = ptr[i], ne = ptr[i + 1] - e0;
+  const int e0 = beg[i], ne = end[i] - e0;
   // the values to add to are on their way while the entries are read (40^3, 31 atoms, 56
   // states: 10.6 us with the loads after them, 9.6 so; 96^3's shared nodes 101 and 80)
   E yv[NB];
@@ -52,7 +52,8 @@ __device__ __forceinline__ void nl_scatter_body(int i, int nb0, int n_pts, const
 
 template <typename E, int NB>
 __global__ __launch_bounds__(256) void nl_scatter_kernel(int n_pts, const int32_t* __restrict__ pts,
-                                                         const int32_t* __restrict__ ptr,
+                                                         const int32_t* __restrict__ beg,
+                                                         const int32_t* __restrict__ end,
                                                          const int32_t* __restrict__ ent_proj,
                                                          const E* __restrict__ ent_coef,
                                                          const E* __restrict__ alpha, int lda, int n_s,
@@ -61,8 +62,8 @@ __global__ __launch_bounds__(256) void nl_scatter_kernel(int n_pts, const int32_
   // orbital groups fastest in the grid: consecutive work-groups share the same nodes'
   // entry lists (from L2)
   if (a_dev) a = (typename elem<E>::real)(*a_dev);
-  nl_scatter_body<E, NB>(blockIdx.y * blockDim.x + threadIdx.x, blockIdx.x * NB, n_pts, pts, ptr, ent_proj, ent_coef,
-                         alpha, lda, n_s, a, y, ldy);
+  nl_scatter_body<E, NB>(blockIdx.y * blockDim.x + threadIdx.x, blockIdx.x * NB, n_pts, pts, beg, end, ent_proj,
+                         ent_coef, alpha, lda, n_s, a, y, ldy);
 }
 
 // Several problems in one launch (work-group b of problem p as in nl_gather_batched_kernel;
@@ -82,8 +83,8 @@ __global__ __launch_bounds__(256) void nl_scatter_batched_kernel(const NlBatchAr
   const NlBatchArgs& P = probs[lo];
   const int local = b - off[lo];
   const int groups = (P.n_s + NB - 1) / NB;
-  nl_scatter_body<E, NB>((local / groups) * 256 + (int)threadIdx.x, (local % groups) * NB, P.n_pts, P.pts, P.ptr,
-                         P.ent_proj, (const E*)P.ent_coef, (const E*)P.alpha, P.lda, P.n_s,
+  nl_scatter_body<E, NB>((local / groups) * 256 + (int)threadIdx.x, (local % groups) * NB, P.n_pts, P.pts, P.beg,
+                         P.end, P.ent_proj, (const E*)P.ent_coef, (const E*)P.alpha, P.lda, P.n_s,
                          (typename elem<E>::real)a_dev[P.slot], (E*)P.y, P.ldy);
 }
 
@@ -532,7 +533,8 @@ void nl_batch_args(const sparc_ham* H, const void* x, int64_t ldx, void* y, int6
   o->dV = H->dV;
   o->alpha = alpha;
   o->pts = H->nl_pts;
-  o->ptr = H->nl_ptr;
+  o->beg = H->nl_ptr;
+  o->end = H->nl_ptr + 1;
   o->ent_proj = H->ent_proj;
   o->ent_coef = H->ent_coef;
   const int gnb = dtype_complex(H->dtype) ? 4 : 8;
@@ -553,9 +555,8 @@ int nl_update_args(const sparc_ham* H, void* y, int64_t ldy, int n_s, void* alph
 int nl_shared_args(const sparc_ham* H, int nb, NlBatchArgs* o) {
   o->n_pts = (int)H->n_shared;
   o->pts = H->sh_pts;
-  o->ptr = H->sh_ptr;
-  o->ent_proj = H->sh_proj;
-  o->ent_coef = H->sh_coef;
+  o->beg = H->sh_beg;
+  o->end = H->sh_end;
   return (int)((H->n_shared + 255) / 256) * ((o->n_s + nb - 1) / nb);
 }
 
@@ -723,8 +724,8 @@ static void nl_scatter_launch(sparc_ham* H, const void* alpha, int32_t n_s, doub
   typedef typename elem<E>::real R;
   dim3 grid((unsigned)((n_s + NB - 1) / NB), (unsigned)((H->n_nlpts + 255) / 256));
   nl_scatter_kernel<E, NB><<<grid, 256, 0, H->ctx->stream>>>(
-      (int)H->n_nlpts, H->nl_pts, H->nl_ptr, H->ent_proj, (const E*)H->ent_coef, (const E*)alpha, alpha_ld(n_s), n_s,
-      (R)a, a_dev, (E*)out, ldo);
+      (int)H->n_nlpts, H->nl_pts, H->nl_ptr, H->nl_ptr + 1, H->ent_proj, (const E*)H->ent_coef, (const E*)alpha,
+      alpha_ld(n_s), n_s, (R)a, a_dev, (E*)out, ldo);
 }
 
 // 16 orbitals per thread, or 4 when that would leave fewer than four work-groups per CU
@@ -787,8 +788,8 @@ static int nl_update_t(sparc_ham* H, void* alpha, int32_t n_s, double a, void* o
     int t = timer_begin(H->ctx, "nl_scatter");
     dim3 grid((unsigned)((n_s + kSharedNB - 1) / kSharedNB), (unsigned)((H->n_shared + 255) / 256));
     nl_scatter_kernel<E, kSharedNB><<<grid, 256, 0, H->ctx->stream>>>(
-        (int)H->n_shared, H->sh_pts, H->sh_ptr, H->sh_proj, (const E*)H->sh_coef, (const E*)alpha, alpha_ld(n_s), n_s,
-        (R)a, nullptr, (E*)out, ldo);
+        (int)H->n_shared, H->sh_pts, H->sh_beg, H->sh_end, H->ent_proj, (const E*)H->ent_coef, (const E*)alpha,
+        alpha_ld(n_s), n_s, (R)a, nullptr, (E*)out, ldo);
     timer_end(H->ctx, t);
     SPARC_TRY(check_launch("nl_scatter_kernel"));
   }

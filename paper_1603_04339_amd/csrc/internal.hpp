@@ -157,11 +157,10 @@ struct sparc_ham {
   // projector update (empty where it never applies):
   int32_t* sup_mark;    // [n_sup] sup_idx, as ~g for nodes in several supports
   int64_t n_shared;     // nodes in several supports
-  int32_t* sh_pts;      // their nodes, CSR, projectors and coefficients, as nl_pts .. ent_coef
-  int32_t* sh_ptr;
-  int32_t* sh_proj;
-  void* sh_coef;
-  char* nl_mem;         // holds sup_ptr .. sh_coef
+  int32_t* sh_pts;      // them, and where their entries in ent_proj and ent_coef begin and end
+  int32_t* sh_beg;
+  int32_t* sh_end;
+  char* nl_mem;         // holds sup_ptr .. sh_end
 };
 
 namespace sparc {
@@ -306,7 +305,7 @@ struct NlBatchArgs {
   const void* pval;
   double dV;
   void* alpha;
-  const int32_t *pts, *ptr, *ent_proj;   // update launch: pts = sup_mark
+  const int32_t *pts, *beg, *end, *ent_proj;   // update launch: pts = sup_mark
   const void* ent_coef;                  // update launch: gamma per projector
 };
 constexpr int kScatterNB = 16;  // orbitals per thread of a batched scatter, and over shared nodes

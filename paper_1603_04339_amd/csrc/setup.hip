@@ -234,30 +234,37 @@ static int upload(const std::vector<T>& h, T** d) {
   return SPARC_OK;
 }
 
-// Tables that share one allocation and one copy, each on a 256-byte boundary (an allocation and a
-// copy for each of the 16 cost about 15 us: creating a Hamiltonian of 24^3 with 8 atoms 0.65 ms, so
-// 0.41; 40^3 with 31 atoms 1.58 and 1.34)
+// Tables that share one allocation, each on a 256-byte boundary: the small ones come first and go up
+// in one copy, the others in a copy each (an allocation and a copy for each of the 16 cost about 15 us:
+// creating a Hamiltonian of 24^3 with 8 atoms 0.65 ms, so 0.41; 40^3 with 31 atoms 1.58 and 1.34)
 struct TableUpload {
+  static constexpr size_t kSmall = size_t(1) << 16;
   struct Part {
     const void* src;
-    size_t bytes, at;
+    size_t bytes;
     char** dst;
   };
   std::vector<Part> parts;
-  size_t total = 0;
   template <typename T>
-  void add(const std::vector<T>& h, T** d) {
-    parts.push_back({h.data(), h.size() * sizeof(T), total, (char**)d});
-    total += (h.size() * sizeof(T) + 255) / 256 * 256 + (h.empty() ? 256 : 0);
-  }
+  void add(const std::vector<T>& h, T** d) { parts.push_back({h.data(), h.size() * sizeof(T), (char**)d}); }
   int run(char** mem) {
-    SPARC_HIP(hipMalloc((void**)mem, total));
-    std::vector<char> stage(total);
+    std::stable_partition(parts.begin(), parts.end(), [](const Part& p) { return p.bytes <= kSmall; });
+    std::vector<size_t> at;
+    size_t total = 0, small = 0;
     for (const Part& p : parts) {
-      if (p.bytes) memcpy(stage.data() + p.at, p.src, p.bytes);
-      *p.dst = *mem + p.at;
+      at.push_back(total);
+      total += (std::max<size_t>(p.bytes, 1) + 255) / 256 * 256;
+      if (p.bytes <= kSmall) small = total;
     }
-    SPARC_HIP(hipMemcpy(*mem, stage.data(), total, hipMemcpyHostToDevice));
+    SPARC_HIP(hipMalloc((void**)mem, total));
+    std::vector<char> stage(small);
+    for (size_t i = 0; i < parts.size(); ++i) {
+      const Part& p = parts[i];
+      *p.dst = *mem + at[i];
+      if (p.bytes > kSmall) SPARC_HIP(hipMemcpy(*p.dst, p.src, p.bytes, hipMemcpyHostToDevice));
+      else if (p.bytes) memcpy(stage.data() + at[i], p.src, p.bytes);
+    }
+    if (small) SPARC_HIP(hipMemcpy(*mem, stage.data(), small, hipMemcpyHostToDevice));
     return SPARC_OK;
   }
 };
@@ -538,9 +545,8 @@ int sparc_ham_create(sparc_ctx* ctx, const sparc_grid* grid, const sparc_atoms* 
   const bool fuse = fenv && fenv[0] == '1';
   H->nl_fused = H->n_proj > 0 && H->max_proj_per_atom <= 4 && fuse;
   // what the projector update reads (where it applies): the support indices with the nodes of
-  // several supports marked, and those nodes with their entries
-  std::vector<int32_t> mark, sh_pts, sh_ptr, sh_proj;
-  std::vector<double> shre, shim;
+  // several supports marked, and those nodes with the range of their entries
+  std::vector<int32_t> mark, sh_pts, sh_beg, sh_end;
   if (nl_update_applies(H)) {
     mark = T.sup_idx;
     for (int a = 0; a < H->n_atoms_nl; ++a)
@@ -548,22 +554,16 @@ int sparc_ham_create(sparc_ctx* ctx, const sparc_grid* grid, const sparc_atoms* 
         if (cnt[mark[t] + 1] > T.atom_pbeg[a + 1] - T.atom_pbeg[a]) mark[t] = ~mark[t];
     for (size_t i = 0; i < nl_pts.size(); ++i) {
       const int a = ent_key[nl_ptr[i]] >> 2;
-      if (cnt[nl_pts[i] + 1] == T.atom_pbeg[a + 1] - T.atom_pbeg[a]) continue;
+      if (nl_ptr[i + 1] - nl_ptr[i] == T.atom_pbeg[a + 1] - T.atom_pbeg[a]) continue;
       sh_pts.push_back(nl_pts[i]);
-      sh_ptr.push_back((int32_t)sh_proj.size());
-      for (int32_t e = nl_ptr[i]; e < nl_ptr[i + 1]; ++e) {
-        sh_proj.push_back(ent_proj[e]);
-        shre.push_back(ere[e]);
-        shim.push_back(eim[e]);
-      }
+      sh_beg.push_back(nl_ptr[i]);
+      sh_end.push_back(nl_ptr[i + 1]);
     }
-    sh_ptr.push_back((int32_t)sh_proj.size());
     H->n_shared = (int64_t)sh_pts.size();
   }
-  std::vector<char> pv, ec, gm, sc;
+  std::vector<char> pv, ec, gm;
   pack(dtype, T.vre, T.vim, pv);
   pack(dtype, ere, eim, ec);
-  pack(dtype, shre, shim, sc);
   std::vector<double> zeros(T.gamma.size(), 0.0);
   pack(dtype_single(dtype) ? SPARC_R32 : SPARC_R64, T.gamma, zeros, gm);
   TableUpload up;
@@ -580,9 +580,8 @@ int sparc_ham_create(sparc_ctx* ctx, const sparc_grid* grid, const sparc_atoms* 
   up.add(ec, (char**)&H->ent_coef);
   up.add(mark, &H->sup_mark);
   up.add(sh_pts, &H->sh_pts);
-  up.add(sh_ptr, &H->sh_ptr);
-  up.add(sh_proj, &H->sh_proj);
-  up.add(sc, (char**)&H->sh_coef);
+  up.add(sh_beg, &H->sh_beg);
+  up.add(sh_end, &H->sh_end);
   if ((rc = up.run(&H->nl_mem))) {
     sparc_ham_destroy(H);
     return rc;
