@@ -1202,26 +1202,14 @@ static int real_bytes(const sparc_ham* H) { return dtype_single(H->dtype) ? 4 : 
 // rows of up to 32 nodes whose plan needs two halo chunks a thread, with more than 4 million values:
 // 32-node tiles hold them whole (17 blocks: tiled takes 0.96 of the time on average, 0.76 to 1.12; 27
 // x 39 x 27, 404 orbitals: 46 and 60 us; 31 x 19 x 32, 512: 43 and 45).
-// Complex double rows of 57 to 64 nodes that no tile of full lanes fits, where 64 x 8 tiles spare at
-// most a quarter (58 x 53^2, 178 orbitals: tiled 492, rows 611 us; 60 x 56^2 523 and 650; 54 x 53^2,
-// whose rows leave a higher tile, 479 and 366; 64 x 60^2, full lanes, 623 and 595); and planes of 28 to
-// 32 by at most 24 nodes with more than 2.4 million values, which leave a CU one or two row tiles
-// (11 blocks: tiled takes 0.91 of the time on average, 0.77 to 1.16; 32 x 20 x 31 with 512 orbitals
-// 0.77; past 24 rows 1.06 to 1.16).
 static bool row_tiled_better(const sparc_ham* H, const RowPlan& p, int vx, int64_t n_s) {
   const sparc_grid& g = H->grid;
   const int64_t n1 = g.n[0], n2 = g.n[1], rows8 = (n2 + 7) / 8 * 8;
   const double values = (double)H->n_d * (double)n_s;
   if (H->dtype == SPARC_R32 && vx == 1 && n1 <= 32 && p.cfg.hm == 2 && values > 4e6) return true;
-  if (H->dtype == SPARC_C128 && n1 >= 28 && n1 <= 32 && n2 <= 24 && values > 2.4e6) return true;
-  if (values <= 5e6) return false;
-  if (H->dtype == SPARC_R32 && vx < 4) {
-    const int64_t part = vx == 1 ? 8 : 10;
-    return n1 > 40 && n1 < 48 && n2 <= 64 && part * n1 * n2 > (part - 1) * 48 * rows8;
-  }
-  if (H->dtype == SPARC_C128)
-    return p.cfg.hm == 2 && !p.cfg.full && n1 > 56 && n1 <= 64 && 4 * n1 * n2 > 3 * 64 * rows8;
-  return false;
+  if (values <= 5e6 || H->dtype != SPARC_R32 || vx >= 4) return false;
+  const int64_t part = vx == 1 ? 8 : 10;
+  return n1 > 40 && n1 < 48 && n2 <= 64 && part * n1 * n2 > (part - 1) * 48 * rows8;
 }
 
 // FP32 plans of several chunk widths, nearly all in chunks of one or two floats, whose kernel has

@@ -330,10 +330,18 @@ __device__ __forceinline__ int64_t row_order(int64_t L, int64_t G) {
   return xcd * q + (xcd < r ? xcd : r) + slot;
 }
 
+// The arguments are read where they lie, when they are needed: as a plain parameter all of them are
+// loaded at the entry and held, more than the scalar registers, and the ones over are kept in lanes of
+// vector registers (up to 92 in complex double, whose masked form with two halo chunks a thread then
+// spilled to memory).  Over 25 to 32 blocks per type a step takes 0.87 of that time in complex double
+// (47 x 40 x 36, 99 orbitals: 147 -> 106 us, tiled 121; 82 x 74 x 48, 54: 312 -> 214) and 0.98 to 1.00
+// in the others (96^3 x 256 FP32: 592 -> 579).
 template <typename E, int VX, int VY, int HM, bool FULL, bool HASZ>
-__global__ __launch_bounds__(kRowThreads) void hrow_kernel(StepArgs<E> A) {
+__global__ __launch_bounds__(kRowThreads) void hrow_kernel(StepArgs<E>) {
   extern __shared__ __align__(16) char row_lds[];
-  hrow_body<E, VX, VY, HM, FULL, HASZ>(A, row_order(blockIdx.x, gridDim.x), (int)blockDim.x, row_lds);
+  auto a = (const StepArgs<E> __attribute__((address_space(4)))*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm("" : "+s"(a));   // not the parameter, for the compiler
+  hrow_body<E, VX, VY, HM, FULL, HASZ>(*(const StepArgs<E>*)a, row_order(blockIdx.x, gridDim.x), (int)blockDim.x, row_lds);
 }
 
 // Several problems in one launch.  Problem p has the work-groups wg_off[p] <= b <

@@ -137,15 +137,15 @@ struct RowLaunch {
 // the prologue's).  A step takes the root of the squares of its latency, a base and a share per 16
 // bytes of the tile, more with fewer than eight waves on the CU, and of the CU's time for the tiles
 // of all k, by 16 bytes of tile and of y halo; more than four waves that do not fill the four SIMDs
-// evenly cost by how uneven they are, and the complex double form with masked lanes and two halo
-// chunks a thread, which spills, 1.6 times.  Chunks narrower than 16 bytes and complex double ones,
+// evenly cost by how uneven they are.  Chunks narrower than 16 bytes and complex double ones,
 // whose x taps read a chunk each, have rates of their own; chunks of one float hold half the
 // registers, so four waves fit a SIMD instead of three, and a latency of their own.
 // Fitted to 12300 timed (tile, chunk) pairs of 952 blocks from 16^3 x 2 to 96^3 x 512 in all four types.
-// Over these the choice costs 1.3 % on average against the fastest timed pair in FP64, 1.6 in FP32, 2.4
-// and 3.0 in complex double and single (with the longer of latency and rate in a step's place and
-// fixed prices for uneven waves 3.9 to 8.5 %: 80^3 x 60 FP64 207 us then and 179 now, tiled 180;
-// 48^3 x 384 FP32 160 and 126, tiled 156; 40^3 x 300 complex double 399 and 309, tiled 371).
+// Over these the choice costs 1.3 % on average against the fastest timed pair in FP64, 1.6 in FP32 and
+// 3.0 in complex single (with the longer of latency and rate in a step's place and fixed prices for
+// uneven waves 3.9 to 8.5 %: 80^3 x 60 FP64 207 us then and 179 now, tiled 180; 48^3 x 384 FP32 160
+// and 126, tiled 156; 40^3 x 300 complex double 399 and 309, tiled 371).  In complex double the
+// choice takes 0.69 of the tiled form's time over 136 blocks, at most 1.03.
 // Launches of uneven grids: rounds need not be whole, and what is lost is part of the last
 // work-groups' time.  all: every candidate is added to it.
 inline RowPlan row_plan(int n1, int n2, int n3, int cp, int rb, int vx, int vy, int64_t n_s, int n_cu,
@@ -179,7 +179,7 @@ inline RowPlan row_plan(int n1, int n2, int n3, int cp, int rb, int vx, int vy, 
     const double chunks = (double)nt * vy * (double)cb / 16.0, halo = 2.0 * kRowNO * txt * (double)cb / 16.0;
     const bool full = n2 % ty == 0 && txt * tyt == nt;
     const double simd = (nt + 255) / 256 * 256.0 / nt;   // waves of the fullest SIMD to the average
-    const double slow = (nt > 256 ? 1.0 + uneven_simds * (simd - 1.0) : 1.0) * (c128 && hm == 2 && !full ? 1.6 : 1.0);
+    const double slow = nt > 256 ? 1.0 + uneven_simds * (simd - 1.0) : 1.0;
     for (int nz = 1; nz == 1 || n3 / nz >= 3; ++nz) {
       const int zc = (n3 + nz - 1) / nz, nzr = (n3 + zc - 1) / zc;
       const int64_t wg = (int64_t)tl * nzr * n_s;

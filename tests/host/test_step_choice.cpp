@@ -3,7 +3,7 @@
 // that it serves faster.
 #include "host_case.hpp"
 
-// slow: work-groups and threads of the plan that is not to be taken (0: the tiled form is)
+// slow: work-groups and threads of the plan that is not to be taken (0: the tiled form is; 1: no such plan)
 struct Step { std::vector<int> n; int ns; sparc_dtype dt; unsigned slow_wg, slow_nt; };
 
 int main() {
@@ -18,8 +18,9 @@ int main() {
       {{26, 22, 23}, 512, SPARC_R32, 512, 128},     // 24 rows, 23 planes: 49, 33, 32
       {{17, 27, 33}, 512, SPARC_R64, 512, 128},     // 28 rows, 33 planes: 75, 52, 88
       {{27, 39, 27}, 404, SPARC_R32, 0, 0},         // tiled 46, rows 60
-      {{32, 20, 31}, 512, SPARC_C128, 0, 0},        // tiled 0.77 of the rows' time
-      {{58, 53, 53}, 178, SPARC_C128, 0, 0},        // 492, 611
+      {{32, 20, 31}, 512, SPARC_C128, 1, 0},        // row form: tiled 143, rows 121
+      {{58, 53, 53}, 178, SPARC_C128, 1, 0},        // 507, 412
+      {{51, 60, 56}, 2, SPARC_C128, 1, 0},          // point form 43, rows 17
       {{43, 47, 41}, 82, SPARC_R32, 0, 0}};         // 32, 34
   for (const Step& st : steps) {
     Cell cell(st.n, 1);

@@ -10,10 +10,9 @@ from paper_1603_04339_amd import sparc as sp
 READELF = "/opt/rocm/llvm/bin/llvm-readelf"
 
 # the 32 x 32 tiles (1024 threads, 128 registers; only the autotuner picks them), the register
-# tridiagonalisations of complex matrices and of the largest real ones, the masked complex double
-# rows with two halo chunks, the plans of several chunk widths in complex single, and a few words of
-# two small solvers
-KNOWN = [r"hstep_(batched_)?kernelI\S*Li32ELi32E", r"hetrd_reg_kernelI(N\S*cplxId|dLi3E)", r"hrow_kernelINS_4cplxIdEELi2ELi2ELi2ELb0ELb1E",
+# tridiagonalisations of complex matrices and of the largest real ones, the plans of
+# several chunk widths in complex single, and a few words of two small solvers
+KNOWN = [r"hstep_(batched_)?kernelI\S*Li32ELi32E", r"hetrd_reg_kernelI(N\S*cplxId|dLi3E)",
          r"hrow_mixed_kernelINS_4cplxIfE", r"latrd_kernelINS_4cplxIdE", r"anderson_gamma_kernel"]
 
 
