@@ -1181,13 +1181,16 @@ int cg_residual_norm(sparc_ham* H, const CgIter& C) {
 // ------------------------------------------------------------ row form
 // The row form (hrow_impl.hpp) serves cells that are periodic in every direction with the
 // 12th-order stencil and at least 16 nodes per direction (its halos wrap at most once); a
-// forced tile shape and the fused projector scatter keep the tiled kernel.  So do wide
-// complex128 grids that 16 x 16 tiles cover exactly: their rows leave a work-group 16 rows
-// only (80^3 x 60: tiled 403 us, rows 431; at 64^3 x 60 202 and 184, at 48^3 x 1000 1450 and
-// 1430, and rows win wherever the tiles do not fit, 45 x 37 x 50 x 40: 79 and 74).
+// forced tile shape and the fused projector scatter keep the tiled kernel.  So do complex128
+// grids that 16 x 16 tiles cover exactly with rows past 96 nodes that do not fill whole waves:
+// eight rows a work-group are left (112 x 112 x 48 with 30 orbitals: 252 us in either form, in a
+// plan tiled 232 and rows 249; 112 x 32 x 64, 100: 314 and 322, 288 and 311).  Up to 96 nodes, and
+// at 128, rows are faster (96^3 x 24: 313 and 249; 80^3 x 20: 160 and 131, x 60: 408 and 361;
+// 128 x 96 x 64, 8: 109 and 81), also in plans (273 and 251, 152 and 135, 355 and 361, 98 and 88).
 static bool row_form(const sparc_ham* H) {
   const sparc_grid& g = H->grid;
-  if (H->dtype == SPARC_C128 && g.n[0] > 64 && g.n[0] % 16 == 0 && g.n[1] % 16 == 0) return false;
+  if (H->dtype == SPARC_C128 && g.n[0] > 96 && g.n[0] % 64 != 0 && g.n[0] % 16 == 0 && g.n[1] % 16 == 0)
+    return false;
   return g.n_o == kRowNO && dirichlet_mask(g) == 0 && g.n[0] >= 16 && g.n[1] >= 16 && g.n[2] >= 16 && !H->nl_fused &&
          !getenv("SPARC_HSTEP_TILE");
 }

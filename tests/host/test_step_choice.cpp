@@ -21,6 +21,9 @@ int main() {
       {{32, 20, 31}, 512, SPARC_C128, 1, 0},        // row form: tiled 143, rows 121
       {{58, 53, 53}, 178, SPARC_C128, 1, 0},        // 507, 412
       {{51, 60, 56}, 2, SPARC_C128, 1, 0},          // point form 43, rows 17
+      {{96, 96, 96}, 24, SPARC_C128, 1, 0},         // tiled 313, rows 249
+      {{128, 96, 64}, 8, SPARC_C128, 1, 0},         // 109, 81
+      {{112, 112, 48}, 30, SPARC_C128, 0, 0},       // in a plan 232, 249
       {{43, 47, 41}, 82, SPARC_R32, 0, 0}};         // 32, 34
   for (const Step& st : steps) {
     Cell cell(st.n, 1);
