@@ -721,10 +721,12 @@ __global__ __launch_bounds__(64 * NWV) void hetrd_reg_kernel(int n, T* __restric
       if (lane + 64 * k == n - 1 && q + NWV * m == n - 1) d[n - 1] = re_(a[k][m]);
 }
 
-// Whether the register form takes n, and its launch.  The line is where the matrix no longer
-// fits the registers of eight waves.  A whole small Rayleigh-Ritz step, panel form against
-// this: real n = 64 898 and 542 us, 96 1559 and 982, 128 2043 and 1225, 160 2632 and 2109,
-// 192 3137 and 2576; complex n = 64 1359 and 818, 96 2030 and 1432, 128 2816 and 1855.
+// Whether the register form takes n, and its launch.  The line lies a little past where the matrix
+// fits the registers of eight waves: the largest forms keep some of it in scratch memory (real 192:
+// 66 registers, 228 bytes a lane; complex 128: 28 and 136) and are still ahead of the panel form.  A
+// whole small Rayleigh-Ritz step, panel form against this: real n = 64 898 and 542 us, 96 1559 and
+// 982, 128 2043 and 1225, 160 2632 and 2109, 192 3137 and 2576; complex n = 64 1359 and 818, 96 2030
+// and 1432, 128 2816 and 1855.
 template <typename T>
 static bool hetrd_reg_fits(int n) {
   return n > 1 && n <= (sizeof(T) == 16 ? 128 : 192);

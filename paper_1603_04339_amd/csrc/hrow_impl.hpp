@@ -17,10 +17,11 @@
 // rows of 96 nodes fetch 0.38 extra values.  Large blocks are then bound by HBM: a bare
 // z-march (two reads, one write, no stencil) over the same 96^3 x 512 blocks streams 5.1-5.4
 // TB/s (memory is walked in one stream per work-group; a single linear walk reaches 6.4).
-// Measured per recurrence step, FP64 (32 x 16-tile kernel -> this one): 96^3 x 512 2.51 ->
-// 2.13 ms (4.33 -> 5.1 TB/s of 24 B per node; 14.8 -> 9.5 GB fetched), 80^3 x 256 0.79 ->
-// 0.71 ms, 64^3 x 128 0.195 -> 0.150 ms, 48^3 x 64 49 -> 42 us, 40^3 x 56 34 -> 23 us,
-// 32^3 x 32 17.6 -> 8.9 us.
+// Measured per step of a filter, FP64 (32 x 16-tile kernel or point form -> this one, as planned):
+// 96^3 x 512 2.51 -> 2.19 ms, 80^3 x 256 0.78 -> 0.68 ms, 64^3 x 128 0.203 -> 0.151 ms, 48^3 x 64 47
+// -> 43 us, 40^3 x 56 34 -> 24 us, 32^3 x 32 42 -> 11.5 us.  A recurrence step of 96^3 x 512 takes
+// 2.27 ms as planned, three z chunks (14.8 -> 11.6 GB fetched), and 2.20 in one chunk, which the
+// tuner finds (9.4 GB; 5.0 TB/s of 24 B per node).
 // Registers are what limits the tile: VX = 2, VY = 2 doubles hold 104 for the queue, so the
 // taps are applied in small groups of LDS reads pinned in order (the scheduler would
 // otherwise hoist all 24 reads and spill).
