@@ -596,6 +596,14 @@ int rr_concurrent(sparc_ctx* ctx, int32_t n_prob, sparc_ham* const* H, void* con
   std::sort(span.begin(), span.end());
   for (size_t i = 1; i < span.size(); ++i)
     if (span[i].first < span[i - 1].second) return SPARC_OK;
+  // Two to four problems of a few states, a complex state counted as three: the chains are short, and the
+  // events and stream waits cost more (24^3, 4 + 4 states: one by one 299 us, side by side 342; 9 + 9 363
+  // and 394, 12 + 12 389 and 400, 8 + 20 390 and 392, 16 + 16 435 and 399; complex 2 + 2 385 and 421, 4 + 4
+  // 422 and 430, 8 + 8 498 and 449; four problems of 2 states 570 and 622, of 4 613 and 630, of 8 706
+  // and 640, four complex ones of 2 756 and 692)
+  int64_t states = 0;
+  for (int p = 0; p < n_prob; ++p) states += n_s[p] * (dtype_complex(H[p]->dtype) ? 3 : 1);
+  if (n_prob <= 4 && states <= (n_prob == 2 ? 24 : 16)) return SPARC_OK;
   if (dense + blk + alpha + gwb > work_bytes) return SPARC_OK;
   DeviceScope on(ctx->device);
   SideStreams side(ctx);

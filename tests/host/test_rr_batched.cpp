@@ -1,7 +1,7 @@
 // Batched Rayleigh-Ritz: on a context that autotunes, the first call of a shape times its products
 // with nothing on the side streams; later calls use those and time nothing.  The side streams
 // stay idle too where the workspace does not hold the problems' dense parts next to the blocks,
-// with kernel timing on, and for split products.
+// with kernel timing on, for split products, and for two to four problems of a few states.
 #include "host_case.hpp"
 
 static sparc_ctx* ctx;
@@ -53,6 +53,8 @@ int main() {
   CHECK(s.side > 0 && s.timed == 0);
   CHECK(run({tiny, tiny, tiny, tiny}, 480).side == 0);   // dense parts larger than the blocks
   CHECK(run({f, f}, 32, SPARC_GEMM_BF16X3).side == 0);
+  CHECK(run({h, f}, 12).side == 0 && run({g, g}, 4).side == 0 && run({h, f, h, f}, 4).side == 0);
+  CHECK(run({h, f}, 13).side > 0 && run({g, g}, 5).side > 0 && run({h, f, h, f}, 5).side > 0);
   CHECK(sparc_ctx_set_timing(ctx, 1) == SPARC_OK);
   CHECK(run({h, g}, 30).side == 0);
   CHECK(sparc_ctx_set_timing(ctx, 0) == SPARC_OK);
